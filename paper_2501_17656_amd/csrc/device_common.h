@@ -313,4 +313,64 @@ __device__ inline double near_entry(const KernelParams& kp, const PointScale& ps
 __device__ inline double shfl_xor(double v, int m) { return __shfl_xor(v, m, 64); }
 __device__ inline float shfl_xor(float v, int m) { return __shfl_xor(v, m, 64); }
 
+// Sum over the 8 lanes that share b (lane bits 3..5 = a) of T values each,
+// as a butterfly transpose-reduce: afterwards lane (a, b) holds the full sum
+// of value index a (T = 8), or of index a >> (3 - log2 T) for smaller T.
+template <int T, typename Tv>
+__device__ inline Tv transpose_reduce_a(Tv (&z)[T], int a) {
+  if constexpr (T == 1) {
+    Tv s = z[0];
+    s += shfl_xor(s, 8);
+    s += shfl_xor(s, 16);
+    s += shfl_xor(s, 32);
+    return s;
+  } else {
+    // halve the value set at each step, masks 32, 16, 8 (a bits 2, 1, 0)
+    constexpr int H = T / 2;
+    const bool hi = (a >> 2) & 1;
+    Tv v1[H];
+#pragma unroll
+    for (int k = 0; k < H; ++k) {
+      const Tv keep = hi ? z[k + H] : z[k];
+      const Tv send = hi ? z[k] : z[k + H];
+      v1[k] = keep + shfl_xor(send, 32);
+    }
+    if constexpr (H == 1) {
+      Tv s = v1[0];
+      s += shfl_xor(s, 16);
+      s += shfl_xor(s, 8);
+      return s;
+    } else {
+      constexpr int Q = H / 2;
+      const bool mid = (a >> 1) & 1;
+      Tv v2[Q];
+#pragma unroll
+      for (int k = 0; k < Q; ++k) {
+        const Tv keep = mid ? v1[k + Q] : v1[k];
+        const Tv send = mid ? v1[k] : v1[k + Q];
+        v2[k] = keep + shfl_xor(send, 16);
+      }
+      if constexpr (Q == 1) {
+        Tv s = v2[0];
+        s += shfl_xor(s, 8);
+        return s;
+      } else {
+        const bool lo = a & 1;
+        const Tv keep = lo ? v2[1] : v2[0];
+        const Tv send = lo ? v2[0] : v2[1];
+        return keep + shfl_xor(send, 8);
+      }
+    }
+  }
+}
+
+// Value index held by lane a after transpose_reduce_a.
+template <int T>
+__device__ inline int reduced_index(int a) {
+  if constexpr (T == 1) return 0;
+  else if constexpr (T == 2) return (a >> 2) & 1;
+  else if constexpr (T == 4) return ((a >> 2) & 1) * 2 + ((a >> 1) & 1);
+  else return ((a >> 2) & 1) * 4 + ((a >> 1) & 1) * 2 + (a & 1);
+}
+
 }  // namespace h2mg

@@ -101,7 +101,11 @@ T* upload(H2& h, const std::vector<T>& v) {
 }
 
 constexpr int CHUNK = 16;      // stored blocks per GEMV task
-constexpr int NEAR_CHUNK = 4;  // close leaf pairs per near-field task
+// Near-field tasks: with fewer waves than this the 1024 SIMDs (three resident
+// waves each) get less than four rounds, and the last, partly filled one
+// shows; beyond it a longer task saves row partials.
+constexpr int NEAR_WAVES = 12288;
+constexpr int NEAR_PAIRS = 4;  // most close leaf pairs per task
 
 // Tasks and column lists of the stored blocks [first, first + count) of one
 // depth (sorted by row gid, then column gid).
@@ -312,14 +316,30 @@ h2mg_status build_h2(const double* points_dev, int64_t n, int dim, const h2mg_ke
         }
       NearField& nf = h.near;
       nf.npairs = int(prow.size());
-      std::vector<int> task, rtp(h.nleaf + 1, 0), cptr(h.nleaf + 1, 0), cpair;
+      // Row chunks: as few of at most 64 rows as cover a leaf, of equal
+      // length.  Fewer pairs per task, then a wave per chunk, then shorter
+      // chunks (down to 16 rows, where forming the column sums begins to
+      // cost) until there are NEAR_WAVES waves.
+      const int per_task = std::max(1, std::min(NEAR_PAIRS, nf.npairs / NEAR_WAVES));
+      auto set_chunk = [&](int rows) {
+        nf.chunk = (rows + 7) / 8 * 8;
+        nf.nchunk = (h.leaf_max + nf.chunk - 1) / nf.chunk;
+      };
+      const int chunks = (h.leaf_max + 63) / 64;
+      set_chunk((h.leaf_max + chunks - 1) / chunks);
+      nf.nsplit = nf.npairs < NEAR_WAVES ? nf.nchunk : 1;
+      while (int64_t(nf.npairs) * nf.nsplit < NEAR_WAVES && nf.chunk > 16) {
+        set_chunk(std::max(16, nf.chunk / 2));
+        nf.nsplit = nf.nchunk;
+      }
+      std::vector<int> task, rtp(h.nleaf + 1, 0), cptr(h.nleaf + 1, 0), slot(nf.npairs, -1);
       for (int p = 0; p < nf.npairs;) {
         int e2 = p;
         while (e2 < nf.npairs && prow[e2] == prow[p]) ++e2;
-        for (int c = p; c < e2; c += NEAR_CHUNK) {
+        for (int c = p; c < e2; c += per_task) {
           task.push_back(prow[p]);
           task.push_back(c);
-          task.push_back(std::min(e2, c + NEAR_CHUNK));
+          task.push_back(std::min(e2, c + per_task));
           rtp[prow[p] + 1]++;
         }
         p = e2;
@@ -328,16 +348,15 @@ h2mg_status build_h2(const double* points_dev, int64_t n, int dim, const h2mg_ke
       for (int p = 0; p < nf.npairs; ++p)
         if (pcol[p] != prow[p]) cptr[pcol[p] + 1]++;
       for (int i = 0; i < h.nleaf; ++i) cptr[i + 1] += cptr[i];
-      cpair.resize(cptr[h.nleaf]);
       std::vector<int> fill(cptr.begin(), cptr.end() - 1);
       for (int p = 0; p < nf.npairs; ++p)
-        if (pcol[p] != prow[p]) cpair[fill[pcol[p]]++] = p;
+        if (pcol[p] != prow[p]) slot[p] = fill[pcol[p]]++;
       nf.ntasks = int(task.size() / 3);
       nf.task = upload(h, task);
       nf.pair_col = upload(h, pcol);
+      nf.pair_slot = upload(h, slot);
       nf.row_task_ptr = upload(h, rtp);
       nf.col_ptr = upload(h, cptr);
-      nf.col_pair = upload(h, cpair);
       nf.ld = (h.leaf_max + 7) / 8 * 8;
       for (int p = 0; p < nf.npairs; ++p)
         h.near_evals += int64_t(loff[prow[p] + 1] - loff[prow[p]]) * (loff[pcol[p] + 1] - loff[pcol[p]]);
@@ -350,7 +369,7 @@ h2mg_status build_h2(const double* points_dev, int64_t n, int dim, const h2mg_ke
     h.partial = h.arena.make<double>(size_t(std::max(h.max_tasks, 1)) * rr);
     h.colpart = h.arena.make<double>(size_t(std::max(h.nslot, 1)) * rr);
     h.near_partial = h.arena.make<double>(size_t(std::max(h.near.ntasks, 1)) * h.near.ld);
-    h.near_colpart = h.arena.make<double>(size_t(std::max(h.near.npairs, 1)) * h.near.ld);
+    h.near_colpart = h.arena.make<double>(size_t(std::max(h.near.npairs, 1)) * h.near.nsplit * h.near.ld);
     h.vtree = h.arena.make<double>(h.n);
     h.vtree2 = h.arena.make<double>(h.n);
     h.flags = h.arena.make<int>(4);

@@ -79,9 +79,11 @@ struct NearField {
   int* task = nullptr;                 // device: (row leaf, p0, p1)
   int* pair_col = nullptr;             // device: column leaf of each pair
   int* row_task_ptr = nullptr;         // device: nleaf + 1
-  int* col_ptr = nullptr;              // device: nleaf + 1
-  int* col_pair = nullptr;             // device: off-diagonal pairs by column leaf
+  int* col_ptr = nullptr;              // device: nleaf + 1, offsets into the slots
+  int* pair_slot = nullptr;            // device: place of each pair's column sums, by column leaf (-1: diagonal)
   int ld = 0;                          // padded leaf length of partial buffers
+  int chunk = 64, nchunk = 1;          // rows of a leaf taken at once, chunks of the largest leaf
+  int nsplit = 1;                      // waves per task, each with its own share of the chunks
 };
 
 // Stored near field (optional, FP64).  Every leaf is cut into chunks of at

@@ -31,66 +31,6 @@ void check_launch(const char* what) {
 template <typename Tv> __device__ inline Tv zero() { return Tv(0); }
 
 // ------------------------------------------------------------ symmetric block GEMV
-// Sum over the 8 lanes that share b (lane bits 3..5 = a) of T values each,
-// as a butterfly transpose-reduce: afterwards lane (a, b) holds the full sum
-// of value index a (T = 8), or of index a >> (3 - log2 T) for smaller T.
-template <int T, typename Tv>
-__device__ inline Tv transpose_reduce_a(Tv (&z)[T], int a) {
-  if constexpr (T == 1) {
-    Tv s = z[0];
-    s += shfl_xor(s, 8);
-    s += shfl_xor(s, 16);
-    s += shfl_xor(s, 32);
-    return s;
-  } else {
-    // halve the value set at each step, masks 32, 16, 8 (a bits 2, 1, 0)
-    constexpr int H = T / 2;
-    const bool hi = (a >> 2) & 1;
-    Tv v1[H];
-#pragma unroll
-    for (int k = 0; k < H; ++k) {
-      const Tv keep = hi ? z[k + H] : z[k];
-      const Tv send = hi ? z[k] : z[k + H];
-      v1[k] = keep + shfl_xor(send, 32);
-    }
-    if constexpr (H == 1) {
-      Tv s = v1[0];
-      s += shfl_xor(s, 16);
-      s += shfl_xor(s, 8);
-      return s;
-    } else {
-      constexpr int Q = H / 2;
-      const bool mid = (a >> 1) & 1;
-      Tv v2[Q];
-#pragma unroll
-      for (int k = 0; k < Q; ++k) {
-        const Tv keep = mid ? v1[k + Q] : v1[k];
-        const Tv send = mid ? v1[k] : v1[k + Q];
-        v2[k] = keep + shfl_xor(send, 16);
-      }
-      if constexpr (Q == 1) {
-        Tv s = v2[0];
-        s += shfl_xor(s, 8);
-        return s;
-      } else {
-        const bool lo = a & 1;
-        const Tv keep = lo ? v2[1] : v2[0];
-        const Tv send = lo ? v2[0] : v2[1];
-        return keep + shfl_xor(send, 8);
-      }
-    }
-  }
-}
-
-// Value index held by lane a after transpose_reduce_a.
-template <int T>
-__device__ inline int reduced_index(int a) {
-  if constexpr (T == 1) return 0;
-  else if constexpr (T == 2) return (a >> 2) & 1;
-  else if constexpr (T == 4) return ((a >> 2) & 1) * 2 + ((a >> 1) & 1);
-  else return ((a >> 2) & 1) * 4 + ((a >> 1) & 1) * 2 + (a & 1);
-}
-
 // One wave per task (row gid s, blocks [b0, b1)).  partial[task] = sum_b B_b x_{col b};
 // colpart[slot of b] = B_b^T x_s for every off-diagonal block (slots are
 // ordered by column, so the reduce reads each column's run contiguously).
@@ -372,148 +312,64 @@ __global__ __launch_bounds__(256) void k_leaf_up(const int* __restrict__ leaf_of
   if (w == 0 && j < r) xhat[int64_t(leaf) * r + j] = (red[0][j] + red[1][j]) + (red[2][j] + red[3][j]);
 }
 
-// ------------------------------------------------------------ near field
-// Close leaf pairs (s <= t) evaluated on the fly from the points: one
-// workgroup per task (row leaf s, pairs [p0, p1)), 16 x 16 threads, each
-// thread an 8 x 8 sub-tile of a 128 x 128 tile.  Row sums go to
-// partial[task], column sums of off-diagonal pairs to colpart[pair].
-template <typename Tv, typename Te, int KIND, int DERIV>
-__global__ __launch_bounds__(256) void k_near(const int* __restrict__ tasks,
-                                              const int* __restrict__ pair_col,
-                                              const int* __restrict__ leaf_off,
-                                              const double* __restrict__ pts, int dim,
-                                              const Tv* __restrict__ x, Tv* __restrict__ partial,
-                                              Tv* __restrict__ colpart, int ld, KernelParams kp,
-                                              const double* __restrict__ scale) {
-  constexpr int TILE = 128;
-  __shared__ double ps[TILE * 3];
-  __shared__ double pt[TILE * 3];
-  __shared__ Tv xsl[TILE];
-  __shared__ Tv xtl[TILE];
-  __shared__ Tv red[16][TILE + 1];
-  const int task = blockIdx.x, tid = threadIdx.x;
-  const int ti = tid >> 4, tj = tid & 15;
-  const int sl = tasks[3 * task], p0 = tasks[3 * task + 1], p1 = tasks[3 * task + 2];
-  const int s0 = leaf_off[sl], ns = leaf_off[sl + 1] - s0;
-  for (int rt = 0; rt < ns; rt += TILE) {
-    const int nrow = min(TILE, ns - rt);
-    __syncthreads();
-    for (int idx = tid; idx < TILE * dim; idx += 256) {
-      const int i = idx / dim;
-      ps[idx] = pts[int64_t(s0 + rt + min(i, nrow - 1)) * dim + idx % dim];
-    }
-    for (int i = tid; i < TILE; i += 256)
-      xsl[i] = i < nrow ? (scale ? Tv(scale[s0 + rt + i]) * x[s0 + rt + i] : x[s0 + rt + i]) : zero<Tv>();
-    __syncthreads();
-    double pi[8][3];
-    Tv xi[8], racc[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int i = ti + 16 * u;
-      for (int a = 0; a < 3; ++a) pi[u][a] = a < dim ? ps[i * dim + a] : 0.0;
-      xi[u] = xsl[i];
-      racc[u] = zero<Tv>();
-    }
-    for (int p = p0; p < p1; ++p) {
-      const int tl = pair_col[p];
-      const bool diag = tl == sl;
-      const int t0 = leaf_off[tl], nt = leaf_off[tl + 1] - t0;
-      for (int ct = 0; ct < nt; ct += TILE) {
-        const int ncol = min(TILE, nt - ct);
-        __syncthreads();
-        for (int idx = tid; idx < TILE * dim; idx += 256) {
-          const int j = idx / dim;
-          pt[idx] = pts[int64_t(t0 + ct + min(j, ncol - 1)) * dim + idx % dim];
-        }
-        for (int j = tid; j < TILE; j += 256)
-          xtl[j] = j < ncol ? (scale ? Tv(scale[t0 + ct + j]) * x[t0 + ct + j] : x[t0 + ct + j])
-                            : zero<Tv>();
-        __syncthreads();
-#pragma unroll 2
-        for (int v = 0; v < 8; ++v) {
-          const int j = tj + 16 * v;
-          double pj[3];
-          for (int a = 0; a < 3; ++a) pj[a] = a < dim ? pt[j * dim + a] : 0.0;
-          const Tv xj = xtl[j];
-          Tv cacc = zero<Tv>();
-#pragma unroll
-          for (int u = 0; u < 8; ++u) {
-            double r2 = 0.0;
-            for (int a = 0; a < 3; ++a) {
-              const double dx = pi[u][a] - pj[a];
-              r2 += dx * dx;
-            }
-            Tv k = Tv(kernel_fixed<KIND, DERIV, Te>(Te(kp.inv_l), Te(kp.inv_2l2), Te(r2)));
-            if (diag && rt + ti + 16 * u == ct + j) k += Tv(kp.shift);
-            racc[u] += k * xj;
-            cacc += k * xi[u];
-          }
-          red[ti][j] = cacc;
-        }
-        if (!diag) {
-          __syncthreads();
-          if (tid < TILE) {
-            Tv s = zero<Tv>();
-#pragma unroll
-            for (int q = 0; q < 16; ++q) s += red[q][tid];
-            if (tid < ncol) {
-              if (scale) s *= Tv(scale[t0 + ct + tid]);
-              Tv* dst = colpart + int64_t(p) * ld + ct + tid;
-              *dst = rt == 0 ? s : *dst + s;
-            }
-          }
-        }
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      Tv s = racc[u];
-      s += shfl_xor(s, 1);
-      s += shfl_xor(s, 2);
-      s += shfl_xor(s, 4);
-      s += shfl_xor(s, 8);
-      racc[u] = s;
-    }
-    if (tj == 0) {
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int i = ti + 16 * u;
-        if (i < nrow)
-          partial[int64_t(task) * ld + rt + i] = scale ? Tv(scale[s0 + rt + i]) * racc[u] : racc[u];
-      }
-    }
+// ------------------------------------------------------------ fine output
+// v += p[t * stride] for t in [a, b), four loads in flight, in a fixed order.
+template <typename Tv>
+__device__ __forceinline__ void sum_run(Tv& v, const Tv* __restrict__ p, int64_t stride, int64_t a, int64_t b) {
+  Tv v0 = zero<Tv>(), v1 = zero<Tv>(), v2 = zero<Tv>(), v3 = zero<Tv>();
+  int64_t t = a;
+  for (; t + 4 <= b; t += 4) {
+    v0 += p[t * stride];
+    v1 += p[(t + 1) * stride];
+    v2 += p[(t + 2) * stride];
+    v3 += p[(t + 3) * stride];
   }
+  for (; t < b; ++t) v0 += p[t * stride];
+  v += (v0 + v1) + (v2 + v3);
 }
 
 // out[idx(i)] = alpha * (Q_leaf yhat_leaf + near sums)_i + beta * add[idx(i)]
-// for the rows i of one leaf per workgroup; idx = i or perm[i].
+// for 64 rows i of one leaf per workgroup; idx = i or perm[i].  The near sums
+// are the row partials of the leaf's tasks and its column sums (nsplit per
+// pair, ordered by column leaf), up to some hundred runs of one leaf's
+// length.  Bound by latency, not bytes: the four waves take a quarter of the
+// basis columns and of both lists each, with four loads in flight.  One
+// thread per row summing all of them, each through an index, took 274 us on
+// 50000 points of a Gaussian mixture; 28 us now.
 template <typename Tq, typename Tv>
 __global__ __launch_bounds__(256) void k_fine_reduce(
     const int* __restrict__ leaf_off, const Tq* __restrict__ Qc, const Tv* __restrict__ yhat, int r,
-    const int* __restrict__ row_task_ptr, const int* __restrict__ col_ptr,
-    const int* __restrict__ col_pair, const Tv* __restrict__ partial,
-    const Tv* __restrict__ colpart, int ld, const Tv* __restrict__ near_y,
+    const int* __restrict__ row_task_ptr, const int* __restrict__ col_ptr, int nsplit,
+    const Tv* __restrict__ partial, const Tv* __restrict__ colpart, int ld, const Tv* __restrict__ near_y,
     const int* __restrict__ chunk_base, const double* __restrict__ dg, const Tv* __restrict__ xin,
     const int64_t* __restrict__ perm, Tv* __restrict__ out, double alpha, const Tv* __restrict__ add,
     double beta) {
-  __shared__ Tv yh[64];
+  __shared__ Tv red[4][64];
   const int leaf = blockIdx.x;
   const int s0 = leaf_off[leaf], n = leaf_off[leaf + 1] - s0;
-  if (threadIdx.x < r) yh[threadIdx.x] = yhat[int64_t(leaf) * r + threadIdx.x];
-  __syncthreads();
-  const int t0 = row_task_ptr[leaf], t1 = row_task_ptr[leaf + 1];
-  const int c0 = col_ptr[leaf], c1 = col_ptr[leaf + 1];
-  const Tq* Q = Qc + int64_t(s0) * r;
-  for (int i = threadIdx.x; i < n; i += 256) {
-    Tv v = zero<Tv>();
-    for (int j = 0; j < r; ++j) v += ld_as<Tv, Tq>(Q[int64_t(j) * n + i]) * yh[j];
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int i = 64 * int(blockIdx.y) + lane;
+  if (64 * int(blockIdx.y) >= n) return;
+  Tv v = zero<Tv>();
+  if (i < n) {
+    const Tq* Q = Qc + int64_t(s0) * r + i;
+    const Tv* yh = yhat + int64_t(leaf) * r;
+#pragma unroll 4
+    for (int j = w * r / 4; j < (w + 1) * r / 4; ++j) v += ld_as<Tv, Tq>(Q[int64_t(j) * n]) * yh[j];
     if (near_y) {
-      v += near_y[int64_t(chunk_base[leaf]) * 64 + i];
+      if (w == 0) v += near_y[int64_t(chunk_base[leaf]) * 64 + i];
     } else {
-      for (int t = t0; t < t1; ++t) v += partial[int64_t(t) * ld + i];
-      for (int c = c0; c < c1; ++c) v += colpart[int64_t(col_pair[c]) * ld + i];
-      if (dg) v += Tv(dg[s0 + i]) * xin[s0 + i];
+      const int64_t t0 = row_task_ptr[leaf], nt = row_task_ptr[leaf + 1] - t0;
+      const int64_t c0 = int64_t(col_ptr[leaf]) * nsplit, nc = int64_t(col_ptr[leaf + 1]) * nsplit - c0;
+      sum_run(v, partial + i, ld, t0 + w * nt / 4, t0 + (w + 1) * nt / 4);
+      sum_run(v, colpart + i, ld, c0 + w * nc / 4, c0 + (w + 1) * nc / 4);
+      if (dg && w == 0) v += Tv(dg[s0 + i]) * xin[s0 + i];
     }
+  }
+  red[w][lane] = v;
+  __syncthreads();
+  if (w == 0 && i < n) {
+    v = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
     const int64_t idx = perm ? perm[s0 + i] : int64_t(s0 + i);
     Tv o = Tv(alpha) * v;
     if (add) o += Tv(beta) * add[idx];
@@ -703,30 +559,6 @@ void launch_leaf_up(H2& h, int p, const void* xtree, void* xhat) {
   check_launch("leaf_up");
 }
 
-void launch_near(H2& h, int p, const void* xtree) {
-  if (h.nq > 0) throw std::runtime_error("close entries by quadrature are applied from the stored tiles only");
-  if (h.near.ntasks == 0) return;
-  int ev;
-  h.time_begin(ev);
-  const dim3 g(h.near.ntasks), b(256);
-  KernelParams kp = h.kp;
-  if (h.diag) kp.shift = 0.0;          // the per-point diagonal is added by k_fine_reduce
-  dispatch_kernel(h.kp.kind, h.kp.deriv, [&](auto kc, auto dc) {
-    constexpr int K = decltype(kc)::value, D = decltype(dc)::value;
-    if (p == P64)
-      hipLaunchKernelGGL((k_near<double, double, K, D>), g, b, 0, h.stream, h.near.task,
-                         h.near.pair_col, h.leaf_off, h.pts, h.dim, static_cast<const double*>(xtree),
-                         h.near_partial, h.near_colpart, h.near.ld, kp, h.scale);
-    else
-      hipLaunchKernelGGL((k_near<float, float, K, D>), g, b, 0, h.stream, h.near.task,
-                         h.near.pair_col, h.leaf_off, h.pts, h.dim, static_cast<const float*>(xtree),
-                         reinterpret_cast<float*>(h.near_partial),
-                         reinterpret_cast<float*>(h.near_colpart), h.near.ld, kp, h.scale);
-  });
-  check_launch("near");
-  h.time_end(p == P64 ? KS_NEAR64 : KS_NEAR32, ev, double(h.near_evals));
-}
-
 void launch_near_stored(H2& h, int p, const void* xtree) {
   StoredNear& sn = h.snear;
   if (sn.nblocks == 0) return;
@@ -782,21 +614,21 @@ void launch_near_stored(H2& h, int p, const void* xtree) {
 
 void launch_fine_reduce(H2& h, int p, const void* yhat, void* out, bool to_user, double alpha,
                         const void* add, double beta, const void* xin) {
-  const dim3 g(h.nleaf), b(256);
+  const dim3 g(h.nleaf, (h.leaf_max + 63) / 64), b(256);
   const int64_t* perm = to_user ? h.perm : nullptr;
   const bool stored = near_stored_for(h, p);
   const double* dg = stored ? nullptr : h.diag;     // stored tiles hold the diagonal
   if (p == P64)
     hipLaunchKernelGGL((k_fine_reduce<double, double>), g, b, 0, h.stream, h.leaf_off,
                        static_cast<const double*>(h.prec[P64].Qc), static_cast<const double*>(yhat),
-                       h.r, h.near.row_task_ptr, h.near.col_ptr, h.near.col_pair, h.near_partial,
+                       h.r, h.near.row_task_ptr, h.near.col_ptr, h.near.nsplit, h.near_partial,
                        h.near_colpart, h.near.ld, stored ? h.snear.yc : nullptr, h.snear.chunk_base, dg,
                        static_cast<const double*>(xin), perm, static_cast<double*>(out), alpha,
                        static_cast<const double*>(add), beta);
   else if (p == P32)
     hipLaunchKernelGGL((k_fine_reduce<float, float>), g, b, 0, h.stream, h.leaf_off,
                        static_cast<const float*>(h.prec[P32].Qc), static_cast<const float*>(yhat),
-                       h.r, h.near.row_task_ptr, h.near.col_ptr, h.near.col_pair,
+                       h.r, h.near.row_task_ptr, h.near.col_ptr, h.near.nsplit,
                        reinterpret_cast<const float*>(h.near_partial),
                        reinterpret_cast<const float*>(h.near_colpart), h.near.ld,
                        stored ? reinterpret_cast<const float*>(h.snear.yc) : nullptr, h.snear.chunk_base, dg,
@@ -805,7 +637,7 @@ void launch_fine_reduce(H2& h, int p, const void* yhat, void* out, bool to_user,
   else
     hipLaunchKernelGGL((k_fine_reduce<bf16, float>), g, b, 0, h.stream, h.leaf_off,
                        static_cast<const bf16*>(h.prec[P16].Qc), static_cast<const float*>(yhat),
-                       h.r, h.near.row_task_ptr, h.near.col_ptr, h.near.col_pair,
+                       h.r, h.near.row_task_ptr, h.near.col_ptr, h.near.nsplit,
                        reinterpret_cast<const float*>(h.near_partial),
                        reinterpret_cast<const float*>(h.near_colpart), h.near.ld,
                        stored ? reinterpret_cast<const float*>(h.snear.yc) : nullptr, h.snear.chunk_base, dg,
