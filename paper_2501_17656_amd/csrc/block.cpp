@@ -429,10 +429,13 @@ void cg16(H2& h, Work16& w, int k, const void* rhs, void* e, bool e0_zero, int n
   }
 }
 
-// Direct solve on the coarsest level with the FP64 Cholesky factor.
+// Direct solve on the coarsest level with the FP64 Cholesky factor, or its
+// inverse (w.tmp holds n x 16 doubles and is free here).
 void coarse_solve16(H2& h, Work16& w, const void* r, void* e) {
   const int64_t nf = h.Nl * NR;
-  if (w.p == P64) {
+  if (h.cinv) {
+    launch_inverse_solve16(h, vprec(w.p), r, e, static_cast<double*>(w.tmp));
+  } else if (w.p == P64) {
     launch_copy(h, P64, r, e, nf);
     launch_chol_solve16(h, h.chol, h.Nl, static_cast<double*>(e));
   } else {

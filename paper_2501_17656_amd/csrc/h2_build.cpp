@@ -745,6 +745,13 @@ h2mg_status setup_mg(H2& h, int precision_mask) {
         return fail(H2MG_ERR_NOT_SPD, "the coarsest operator (order %lld) is not positive definite",
                     (long long)h.Nl);
       }
+      if (h.Nl <= INVERSE_MAX) {
+        h.cinv = h.arena.make<double>(size_t(h.Nl) * h.Nl);
+        launch_tri_inverse(h, h.chol, h.Nl, h.cinv);
+        hip_check(hipStreamSynchronize(h.stream), "inverse factor");
+        h.arena.release(h.chol);
+        h.chol = nullptr;
+      }
       h.mg_built = true;
     }
     for (int p = P32; p <= P16; ++p) {

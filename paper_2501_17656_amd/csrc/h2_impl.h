@@ -24,6 +24,11 @@ const char* last_error_cstr();
 void clear_error();
 
 enum Prec { P64 = 0, P32 = 1, P16 = 2 };   // FP64, FP32, BF16 operator storage
+// Coarsest operators of up to this order are solved with the inverse of their
+// Cholesky factor, larger ones (dense problems without far blocks) by
+// substitution: the inverse costs twice the factorisation again and a second
+// square array, and pays from the first few cycles on.
+constexpr int64_t INVERSE_MAX = 8192;
 constexpr int MULTI_NR = 16;               // columns of a multi-vector block
 inline size_t elem_bytes(int p) { return p == P64 ? 8 : p == P32 ? 4 : 2; }
 
@@ -245,7 +250,10 @@ struct H2 {
   bool mg_built = false;
   int levels = 1;
   int64_t Nl = 0;                      // coarsest size
+  // the coarsest operator, up to INVERSE_MAX rows: X = L^{-1} in the lower and
+  // X^T in the upper triangle (cinv); larger ones: the factor L itself (chol)
   double* chol = nullptr;              // Nl x Nl column-major, lower factor
+  double* cinv = nullptr;              // Nl x Nl row-major
   int* flags = nullptr;                // device flags (0: not SPD, 1: non-finite)
   double* dot_part = nullptr;          // reduction partials (several slots)
   std::vector<double> history;
@@ -302,6 +310,7 @@ void launch_pi_upper(H2& h, int d, const int* child_map);   // Pi tiles of depth
 void launch_assemble_dense(H2& h, double* A, int64_t lda);  // depth d_top blocks
 void launch_assemble_kernel_dense(H2& h, double* A, int64_t lda);  // no far blocks
 void launch_potrf(H2& h, double* A, int64_t N);   // blocked Cholesky, sets flags[0]
+void launch_tri_inverse(H2& h, const double* L, int64_t N, double* S);   // S: X = L^{-1} below, X^T above the diagonal
 void launch_cast_precision(H2& h, int p);         // FP64 -> FP32 / BF16 copies
 void launch_near_tiles(H2& h);                    // stored near-field tiles (FP64)
 // Inverses of the block-Jacobi blocks: leaf blocks K_ss + shift (FP64) and the
@@ -436,6 +445,8 @@ void launch_cg_pupdate16(H2& h, int p, int64_t nrows, void* pv, const void* s, c
                          const double* gnew);
 void launch_bj_apply16(H2& h, int p, int k, const void* s, void* z);
 void launch_chol_solve16(H2& h, const double* L, int64_t N, double* x);   // in place, FP64
+// e = X^T (X r), tmp: Nl x 16 doubles.
+void launch_inverse_solve16(H2& h, int p, const void* r, void* e, double* tmp);
 
 // ------------------------------------------------------------ boundary elements
 // Per triangle (vertex rows V, index triples T): centroid y (nt x 3), scale
@@ -474,6 +485,9 @@ void launch_cg_update(H2& h, int p, int64_t n, void* e, const void* pv, void* s,
 void launch_cg_pupdate(H2& h, int p, int64_t n, void* pv, const void* s,
                        const double* gamma_old_part, const double* gamma_new_part);
 void launch_chol_solve(H2& h, const double* L, int64_t N, double* x);   // in place
+// e = X^T (X r) with the inverse factor h.cinv; r, e in the vector type of p
+// (FP64 arithmetic; uses vtree2).
+void launch_inverse_solve(H2& h, int p, const void* r, void* e);
 void launch_check_finite(H2& h, int p, int64_t n, const void* x);      // sets flags[1]
 // Gradient helpers (tree-ordered points h.pts, n x dim).
 void launch_scatter_rows(H2& h, const double* tree, double* user);     // user[perm[i], :] = tree[i, :]

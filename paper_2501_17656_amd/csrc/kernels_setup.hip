@@ -519,6 +519,9 @@ __global__ __launch_bounds__(NT) void k_assemble_dense(
   const double* tl = blk + int64_t(b) * tile_elems(T);
   for (int idx = threadIdx.x; idx < r * r; idx += NT) {
     const int i = idx / r, j = idx % r;
+    // a diagonal block is symmetric up to rounding: its entries below the
+    // diagonal are taken for both triangles (each place is written once)
+    if (s == t && i < j) continue;
     const double v = tl[tile_offset<double>(i, j, T)];
     const int64_t gi = int64_t(s) * r + i, gj = int64_t(t) * r + j;
     A[gi + gj * lda] = v;
@@ -626,6 +629,106 @@ __global__ __launch_bounds__(NT) void k_syrk_update(double* A, int64_t N, int64_
     double s = 0.0;
     for (int q = 0; q < nbk; ++q) s += Li[i][q] * Lj[j][q];
     A[(r0 + i) + (c0 + j) * N] -= s;
+  }
+}
+
+// ------------------------------------------------------------ inverse of the Cholesky factor
+// X = L^{-1} by doubling: X of every 64 x 64 diagonal block, then for s = 64,
+// 128, ... the pairs of neighbouring diagonal blocks A, C of order s (C may be
+// shorter), with B the block of L below A: X_B = -X_C (L_B X_A).  All pairs of
+// a step go together, so the chain is 2 log2(N / 64) products long instead of
+// N / 64 substitutions.  S (N x N, row-major) holds X in its lower triangle;
+// the upper one holds the transposes of the products L_B X_A meanwhile and
+// X^T in the end, so that rows of X and of X^T are both contiguous.
+__global__ __launch_bounds__(NB) void k_tri_inv_diag(const double* __restrict__ L, int64_t N,
+                                                     double* __restrict__ S) {
+  __shared__ double D[NB][NB + 1], X[NB][NB + 1];
+  const int64_t k0 = int64_t(blockIdx.x) * NB;
+  const int nb = int(min<int64_t>(NB, N - k0));
+  const int c = threadIdx.x;
+  for (int idx = c; idx < nb * nb; idx += NB) D[idx % nb][idx / nb] = L[(k0 + idx % nb) + (k0 + idx / nb) * N];
+  __syncthreads();
+  // thread c: column c of the inverse
+  if (c < nb) {
+    for (int i = 0; i < c; ++i) X[i][c] = 0.0;
+    X[c][c] = 1.0 / D[c][c];
+    for (int i = c + 1; i < nb; ++i) {
+      double v = 0.0;
+      for (int q = c; q < i; ++q) v += D[i][q] * X[q][c];
+      X[i][c] = -v / D[i][i];
+    }
+  }
+  __syncthreads();
+  for (int idx = c; idx < nb * nb; idx += NB) {
+    const int i = idx / nb, j = idx % nb;
+    if (j <= i) S[(k0 + i) * N + k0 + j] = X[i][j];
+  }
+}
+
+// One 64 x 64 tile of a doubling product per workgroup, on the FP64 matrix
+// cores; step 0: T = L_B X_A, stored transposed in the upper triangle of S;
+// step 1: X_B = -X_C T.  Tile (ti, tj) of pair z: rows of C, columns of A.
+// The inner range is cut to where the triangular operand is not zero.
+template <int STEP>
+__global__ __launch_bounds__(NT) void k_tri_inv_step(const double* __restrict__ L, int64_t N, int64_t s,
+                                                     double* __restrict__ S) {
+  constexpr int KB = 16;
+  __shared__ double P[KB][NB + 2], Q[KB][NB + 2];
+  const int64_t a0 = 2 * s * blockIdx.z, c0 = a0 + s, c1 = min(N, c0 + s);
+  const int64_t i0 = c0 + int64_t(blockIdx.x) * NB, j0 = a0 + int64_t(blockIdx.y) * NB;
+  if (i0 >= c1) return;
+  const int64_t k0 = STEP == 0 ? j0 : c0, k1 = STEP == 0 ? c0 : min<int64_t>(c1, i0 + NB);
+  const int tid = threadIdx.x, w = tid >> 6, li = tid & 15, lk = (tid >> 4) & 3;
+  d4 acc[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) acc[c] = d4{0.0, 0.0, 0.0, 0.0};
+  for (int64_t k = k0; k < k1; k += KB) {
+    __syncthreads();
+    for (int e = tid; e < KB * NB; e += NT) {
+      // P[q][i] = L or X_C at (i0 + i, k + q), Q[q][j] = X_A or T at (k + q, j0 + j)
+      if (STEP == 0) {
+        const int i = e % NB, q = e / NB;
+        P[q][i] = i0 + i < c1 && k + q < k1 ? L[(i0 + i) + (k + q) * N] : 0.0;
+        Q[q][i] = k + q < k1 && j0 + i <= k + q ? S[(k + q) * N + j0 + i] : 0.0;
+      } else {
+        const int q = e % KB, i = e / KB;
+        P[q][i] = i0 + i < c1 && k + q <= i0 + i ? S[(i0 + i) * N + k + q] : 0.0;
+        Q[q][i] = k + q < k1 ? S[(j0 + i) * N + k + q] : 0.0;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < KB; q += 4) {
+      const double a = P[q + lk][16 * w + li];
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, Q[q + lk][16 * c + li], acc[c], 0, 0, 0);
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < 4; ++c)
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const int64_t i = i0 + 16 * w + 4 * t + lk, j = j0 + 16 * c + li;
+      if (i >= c1) continue;
+      if (STEP == 0) S[j * N + i] = acc[c][t];
+      else S[i * N + j] = -acc[c][t];
+    }
+}
+
+// Upper triangle = transpose of the lower one, 64 x 64 tiles (bi >= bj).
+__global__ __launch_bounds__(NT) void k_tri_mirror(double* __restrict__ S, int64_t N) {
+  __shared__ double X[NB][NB + 1];
+  const int64_t i0 = int64_t(blockIdx.x) * NB, j0 = int64_t(blockIdx.y) * NB;
+  if (j0 > i0) return;
+  for (int e = threadIdx.x; e < NB * NB; e += NT) {
+    const int i = e / NB, j = e % NB;
+    X[i][j] = i0 + i < N && j0 + j < N ? S[(i0 + i) * N + j0 + j] : 0.0;
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < NB * NB; e += NT) {
+    const int j = e / NB, i = e % NB;
+    if (i0 + i < N && j0 + j < i0 + i) S[(j0 + j) * N + i0 + i] = X[i][j];
   }
 }
 
@@ -926,6 +1029,18 @@ void launch_potrf(H2& h, double* A, int64_t N) {
     }
   }
   check_launch("potrf");
+}
+
+void launch_tri_inverse(H2& h, const double* L, int64_t N, double* S) {
+  const unsigned nb = unsigned((N + NB - 1) / NB);
+  hipLaunchKernelGGL(k_tri_inv_diag, dim3(nb), dim3(NB), 0, h.stream, L, N, S);
+  for (int64_t s = NB; s < N; s *= 2) {
+    const dim3 grid(unsigned(s / NB), unsigned(s / NB), unsigned((N - s + 2 * s - 1) / (2 * s)));
+    hipLaunchKernelGGL(k_tri_inv_step<0>, grid, dim3(NT), 0, h.stream, L, N, s, S);
+    hipLaunchKernelGGL(k_tri_inv_step<1>, grid, dim3(NT), 0, h.stream, L, N, s, S);
+  }
+  hipLaunchKernelGGL(k_tri_mirror, dim3(nb, nb), dim3(NT), 0, h.stream, S, N);
+  check_launch("tri_inverse");
 }
 
 void launch_bj_inverse_fine(H2& h, double* out, int ld) {

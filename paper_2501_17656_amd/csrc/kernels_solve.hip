@@ -272,6 +272,45 @@ __global__ __launch_bounds__(NT) void k_gemv_bwd(const double* __restrict__ L, i
   x[j] -= s;
 }
 
+// ------------------------------------------------------------ products with the inverse factor
+// y = X x (UP = false) or X^T x (UP = true) with X the inverse of the Cholesky
+// factor; S holds X below and X^T above its diagonal (row-major), so both are
+// dot products with contiguous parts of its rows: columns 0 .. i of row i, or
+// i .. N - 1.  One wave per row, eight loads of 64 entries in flight; the
+// factor of a 4096-row operator (134 MB for both triangles) stays in the
+// 256 MB last-level cache between cycles.
+// One solve with 4096 rows took 128 + 128 launches of substitution steps,
+// 5.2 ms; a cycle on 100003 points went from 62.1 to 49.4 ms with this and
+// the near field, a training step on 12000 points from 245 to 176 ms.
+template <bool UP, typename Tin, typename Tout>
+__global__ __launch_bounds__(NT) void k_tri_gemv(const double* __restrict__ S, int64_t N,
+                                                 const Tin* __restrict__ x, Tout* __restrict__ y) {
+  const int64_t i = __builtin_amdgcn_readfirstlane(int((blockIdx.x * NT + threadIdx.x) >> 6));
+  if (i >= N) return;
+  const int lane = threadIdx.x & 63;
+  const double* row = S + i * N;
+  const int64_t j1 = UP ? N : i + 1;
+  int64_t j = (UP ? i : 0) + lane;
+  double v0 = 0.0, v1 = 0.0;
+  for (; j + 7 * 64 < j1; j += 8 * 64) {
+    double a[8], b[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      a[q] = row[j + q * 64];
+      b[q] = double(x[j + q * 64]);
+    }
+#pragma unroll
+    for (int q = 0; q < 8; q += 2) {
+      v0 += a[q] * b[q];
+      v1 += a[q + 1] * b[q + 1];
+    }
+  }
+  for (; j < j1; j += 64) v0 += row[j] * double(x[j]);
+  v0 += v1;
+  for (int o = 32; o > 0; o >>= 1) v0 += __shfl_xor(v0, o, 64);
+  if (lane == 0) y[i] = Tout(v0);
+}
+
 inline unsigned blocks(int64_t n) { return unsigned((n + NT - 1) / NT); }
 
 }  // namespace
@@ -387,6 +426,23 @@ void launch_chol_solve(H2& h, const double* L, int64_t N, double* x) {
       hipLaunchKernelGGL(k_gemv_bwd, dim3(blocks(k0)), dim3(NT), 0, h.stream, L, N, k0, x);
   }
   check_launch("chol_solve");
+}
+
+void launch_inverse_solve(H2& h, int p, const void* r, void* e) {
+  const dim3 g(unsigned((h.Nl + NT / 64 - 1) / (NT / 64))), b(NT);
+  double* y = h.vtree2;
+  if (p == P64) {
+    hipLaunchKernelGGL((k_tri_gemv<false, double, double>), g, b, 0, h.stream, h.cinv, h.Nl,
+                       static_cast<const double*>(r), y);
+    hipLaunchKernelGGL((k_tri_gemv<true, double, double>), g, b, 0, h.stream, h.cinv, h.Nl, y,
+                       static_cast<double*>(e));
+  } else {
+    hipLaunchKernelGGL((k_tri_gemv<false, float, double>), g, b, 0, h.stream, h.cinv, h.Nl,
+                       static_cast<const float*>(r), y);
+    hipLaunchKernelGGL((k_tri_gemv<true, double, float>), g, b, 0, h.stream, h.cinv, h.Nl, y,
+                       static_cast<float*>(e));
+  }
+  check_launch("inverse_solve");
 }
 
 void launch_bj_apply(H2& h, int p, int k, const void* s, void* z) {

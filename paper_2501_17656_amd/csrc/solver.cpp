@@ -159,10 +159,13 @@ void cg(H2& h, int p, int k, Work& w, const void* rhs, void* e, bool e0_zero, in
   }
 }
 
-// Direct solve on the coarsest level (FP64 Cholesky factor): e = A_l^{-1} r.
+// Direct solve on the coarsest level (FP64 Cholesky factor, or its inverse):
+// e = A_l^{-1} r.
 void coarse_solve(H2& h, int p, const void* r, void* e) {
   const int vp = vprec(p);
-  if (vp == P64) {
+  if (h.cinv) {
+    launch_inverse_solve(h, vp, r, e);
+  } else if (vp == P64) {
     launch_copy(h, P64, r, e, h.Nl);
     launch_chol_solve(h, h.chol, h.Nl, static_cast<double*>(e));
   } else {
