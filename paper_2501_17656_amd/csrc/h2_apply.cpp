@@ -31,8 +31,7 @@ void apply_fine(H2& h, int p, const void* xt, void* out, double alpha, const voi
   if (h.d_top >= 0) {
     // upsweep: x_L = Q^T x, then x_d = E^T x_{d+1}
     launch_leaf_up(h, p, xt, at_depth(xall, p, h.L, r));
-    for (int d = h.L - 1; d >= h.d_top; --d)
-      launch_transfer_up(h, p, d, at_depth(xall, p, d + 1, r), at_depth(xall, p, d, r));
+    launch_sweep_up(h, p, h.L, xall, nullptr, nullptr, nullptr, nullptr, 0);
     // couplings of every depth in one launch, then one reduce for all depths
     launch_gemv(h, p, h.fine_launch, xall);
     std::vector<const View*> vs;
@@ -43,9 +42,7 @@ void apply_fine(H2& h, int p, const void* xt, void* out, double alpha, const voi
     }
     launch_reduce(h, p, h.d_top, h.L, vs.data(), bs.data(), nullptr, nullptr, yall, nullptr);
     // downsweep: y_d += E y_{d-1}
-    for (int d = h.d_top + 1; d <= h.L; ++d)
-      launch_transfer_down(h, p, d - 1, at_depth(yall, p, d - 1, r), at_depth(yall, p, d, r),
-                           at_depth(yall, p, d, r));
+    launch_sweep_down(h, p, h.L, yall, at_depth(yall, p, h.L, r), nullptr, nullptr, nullptr);
   }
   // near field and leaf downsweep: y = D x + Q y_L
   if (near_stored_for(h, p)) launch_near_stored(h, p, xt);
@@ -53,14 +50,14 @@ void apply_fine(H2& h, int p, const void* xt, void* out, double alpha, const voi
   launch_fine_reduce(h, p, at_depth(yall, p, h.L, r), out, false, alpha, add, beta, xt);
 }
 
-void apply_coarse(H2& h, int p, int k, const void* x, void* y) {
+void* level_input(H2& h, int p, int k) { return at_depth(h.xall, p, h.level_depth(k), h.r); }
+
+int apply_coarse(H2& h, int p, int k, const CoarseInput& in, void* y, const void* add, double* dpart) {
   const int d = h.level_depth(k);
   const int r = h.r;
   void* xall = h.xall;
   void* yall = h.yall;
-  launch_copy(h, p, x, at_depth(xall, p, d, r), int64_t(1 << d) * r);
-  for (int q = d - 1; q >= h.d_top; --q)
-    launch_transfer_up(h, p, q, at_depth(xall, p, q + 1, r), at_depth(xall, p, q, r));
+  launch_sweep_up(h, p, d, xall, in.src, in.prev, in.gold, in.gnew, in.np);
   const Launch& l = h.coarse_launch[d];
   launch_gemv(h, p, l, xall);
   // partial sums of every depth: S_q for q < d, Pi_d and S_d at depth d
@@ -80,14 +77,22 @@ void apply_coarse(H2& h, int p, int k, const void* x, void* y) {
   launch_reduce(h, p, h.d_top, d, v0.data(), b0.data(), v1.data(), b1.data(), yall,
                 d == h.d_top ? y : nullptr);
   // downsweep, the last step writing the output
-  for (int q = h.d_top + 1; q <= d; ++q)
-    launch_transfer_down(h, p, q - 1, at_depth(yall, p, q - 1, r), q == d ? y : at_depth(yall, p, q, r),
-                         at_depth(yall, p, q, r));
+  if (d > h.d_top) return launch_sweep_down(h, p, d, yall, y, add, at_depth(xall, p, d, r), dpart);
+  const int64_t n = int64_t(1 << d) * r;
+  const int vp = p == P64 ? P64 : P32;
+  if (add) launch_axpby(h, vp, n, 1.0, add, -1.0, y);
+  if (!dpart) return 0;
+  launch_dot(h, vp, n, at_depth(xall, p, d, r), y, dpart);
+  return dot_parts(n);
 }
 
-void apply_level(H2& h, int p, int k, const void* x, void* y) {
-  if (k == 1) apply_fine(h, p, x, y, 1.0, nullptr, 0.0);
-  else apply_coarse(h, p, k, x, y);
+void apply_coarse(H2& h, int p, int k, const void* x, void* y) {
+  apply_coarse(h, p, k, CoarseInput{x}, y, nullptr, nullptr);
+}
+
+void residual_level(H2& h, int p, int k, const void* x, void* out, const void* b) {
+  if (k == 1) apply_fine(h, p, x, out, -1.0, b, 1.0);
+  else apply_coarse(h, p, k, CoarseInput{x}, out, b, nullptr);
 }
 
 void restrict_level(H2& h, int p, int k, const void* r, void* r_next) {

@@ -373,7 +373,8 @@ h2mg_status build_h2(const double* points_dev, int64_t n, int dim, const h2mg_ke
     h.vtree = h.arena.make<double>(h.n);
     h.vtree2 = h.arena.make<double>(h.n);
     h.flags = h.arena.make<int>(4);
-    h.dot_part = h.arena.make<double>(8 * 512);
+    h.dot_part = h.arena.make<double>(8 * DOT_PARTS);
+    h.sweep_part = h.arena.make<double>(std::max(h.nleaf, DOT_PARTS));
     hip_check(hipMemsetAsync(h.flags, 0, 4 * sizeof(int), h.stream), "memset");
     hip_check(hipMemsetAsync(h.yall, 0, size_t(h.ngid) * rr * sizeof(double), h.stream), "memset");
 

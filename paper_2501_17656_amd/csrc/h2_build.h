@@ -44,7 +44,23 @@ void apply_fine(H2& h, int p, const void* xt, void* out, double alpha, const voi
                 double beta);
 // Level k >= 2 (depth L - k + 2), coefficient order: y = A_k x.
 void apply_coarse(H2& h, int p, int k, const void* x, void* y);
-void apply_level(H2& h, int p, int k, const void* x, void* y);
+// The input of a level's product as its upsweep forms it: src, or src + beta
+// prev with beta = sum(gnew) / sum(gold) over np partial sums (the next CG
+// direction; prev may be level_input, where the input is left).
+struct CoarseInput {
+  const void* src = nullptr;
+  const void* prev = nullptr;
+  const double* gold = nullptr;
+  const double* gnew = nullptr;
+  int np = 0;
+};
+// y = A_k x, or add - A_k x; with dpart the partial sums of x . y (returns
+// their number).
+int apply_coarse(H2& h, int p, int k, const CoarseInput& in, void* y, const void* add, double* dpart);
+// Where a product of level k >= 2 keeps its input until the next one.
+void* level_input(H2& h, int p, int k);
+// out = b - A_k x.
+void residual_level(H2& h, int p, int k, const void* x, void* out, const void* b);
 // r_next = U_k^T r (level k to k+1); level-1 vectors in tree order.
 void restrict_level(H2& h, int p, int k, const void* r, void* r_next);
 // e = alpha * U_k e_next + beta * add.

@@ -29,6 +29,7 @@ enum Prec { P64 = 0, P32 = 1, P16 = 2 };   // FP64, FP32, BF16 operator storage
 // substitution: the inverse costs twice the factorisation again and a second
 // square array, and pays from the first few cycles on.
 constexpr int64_t INVERSE_MAX = 8192;
+constexpr int DOT_PARTS = 512;             // most partial sums of a dot product of one kernel
 constexpr int MULTI_NR = 16;               // columns of a multi-vector block
 inline size_t elem_bytes(int p) { return p == P64 ? 8 : p == P32 ? 4 : 2; }
 
@@ -256,6 +257,7 @@ struct H2 {
   double* cinv = nullptr;              // Nl x Nl row-major
   int* flags = nullptr;                // device flags (0: not SPD, 1: non-finite)
   double* dot_part = nullptr;          // reduction partials (several slots)
+  double* sweep_part = nullptr;        // those of the downsweeps (at most one per cluster of depth L - 1)
   std::vector<double> history;
 
   // block-Jacobi smoother: inverse diagonal blocks per level and precision
@@ -332,6 +334,16 @@ void launch_reduce(H2& h, int p, int d0, int d1, const View* const* v0, const in
 void launch_transfer_up(H2& h, int p, int d, const void* xchild, void* xpar);
 void launch_transfer_down(H2& h, int p, int d, const void* ypar, void* ychild,
                           const void* addend);
+// Sweeps over all levels between depth d and d_top (kernels_sweep.hip).
+// Upwards: xall's coefficients of depths < d from those of depth d, which are
+// those in xall (src null), src, or src + beta prev with beta = sum(gnew) /
+// sum(gold) over np partial sums; they are left in xall.
+void launch_sweep_up(H2& h, int p, int d, void* xall, const void* src, const void* prev, const double* gold,
+                     const double* gnew, int np);
+// Downwards (d > d_top): out = y_d or add - y_d with y_c = yall[c] + E_c
+// y_parent; with dpart the partial sums of out . xd, at most 2^(d-1) (returns
+// their number).  yall's depths above d are used up.
+int launch_sweep_down(H2& h, int p, int d, void* yall, void* out, const void* add, const void* xd, double* dpart);
 void launch_leaf_up(H2& h, int p, const void* xtree, void* xhat);
 void launch_near(H2& h, int p, const void* xtree);
 // Stored near field: snear.yc = D x over the chunk-padded layout, FP64
@@ -479,11 +491,21 @@ void launch_axpby(H2& h, int p, int64_t n, double a, const void* x, double b, vo
 int dot_parts(int64_t n);
 void launch_dot(H2& h, int p, int64_t n, const void* x, const void* y, double* part);
 // CG step halves; scalars are read from partial-sum arrays on the device.
-void launch_cg_update(H2& h, int p, int64_t n, void* e, const void* pv, void* s,
-                      const void* q, const double* gamma_part, const double* delta_part,
+// (pv may be s; e_zero: e = alpha pv.)  Partial sums: ngp of gamma, ndp of
+// delta; the new ones are dot_parts(n).
+void launch_cg_update(H2& h, int p, int64_t n, void* e, bool e_zero, const void* pv, void* s, const void* q,
+                      const double* gamma_part, int ngp, const double* delta_part, int ndp,
                       double* gamma_new_part);
 void launch_cg_pupdate(H2& h, int p, int64_t n, void* pv, const void* s,
-                       const double* gamma_old_part, const double* gamma_new_part);
+                       const double* gamma_old_part, const double* gamma_new_part, int np);
+// s = src and the partial sums of s . s.
+void launch_copy_dot(H2& h, int p, int64_t n, const void* src, void* s, double* part);
+// A step of the block-Jacobi preconditioned CG on level k (kernels_sweep.hip):
+// the update of e and s, z = M^{-1} s and the partial sums of s . z (returns
+// their number).  Without pv: s = src, z and the sums only.
+int launch_cg_step_bj(H2& h, int p, int k, const void* src, void* e, bool e_zero, const void* pv, void* s,
+                      const void* q, void* z, const double* gamma_part, int ngp, const double* delta_part,
+                      int ndp, double* gamma_new_part);
 void launch_chol_solve(H2& h, const double* L, int64_t N, double* x);   // in place
 // e = X^T (X r) with the inverse factor h.cinv; r, e in the vector type of p
 // (FP64 arithmetic; uses vtree2).
@@ -495,8 +517,4 @@ void launch_coord_mul(H2& h, int a, const double* x, double* w);       // w = x 
 // grad[perm[i], a] = -2 scale x_i (p[i, a] v_i - u_i)
 void launch_coord_grad(H2& h, int a, double scale, const double* x, const double* v, const double* u,
                        double* grad);
-// z = M^{-1} s on one level (block-Jacobi): level 1 uses the leaf blocks,
-// level k >= 2 the r x r blocks of its depth.
-void launch_bj_apply(H2& h, int p, int k, const void* s, void* z);
-
 }  // namespace h2mg

@@ -164,43 +164,52 @@ struct RedArgs {
   int nrows;
 };
 
-// One wave per row of any depth: out = sum of its partials, in a fixed order.
+// v += p[t * stride] for t in [a, b), four loads in flight, in a fixed order.
+template <typename Tv>
+__device__ __forceinline__ void sum_run(Tv& v, const Tv* __restrict__ p, int64_t stride, int64_t a, int64_t b) {
+  Tv v0 = zero<Tv>(), v1 = zero<Tv>(), v2 = zero<Tv>(), v3 = zero<Tv>();
+  int64_t t = a;
+  for (; t + 4 <= b; t += 4) {
+    v0 += p[t * stride];
+    v1 += p[(t + 1) * stride];
+    v2 += p[(t + 2) * stride];
+    v3 += p[(t + 3) * stride];
+  }
+  for (; t < b; ++t) v0 += p[t * stride];
+  v += (v0 + v1) + (v2 + v3);
+}
+
+// One workgroup per row of any depth: out = sum of its partials, in a fixed
+// order.  A row has up to some hundred contributions and moves little, so the
+// length of the chain of loads is what counts: the 256 threads are 256 / rp
+// groups (rp: the power of two that holds r), each sums its share of every
+// list with four loads in flight, and the groups' sums meet in LDS.  With one
+// wave per row the reduces were a tenth of a solve on 65536 points (23 us
+// each; 10 us now).
 template <typename Tv>
 __global__ __launch_bounds__(256) void k_reduce(RedArgs A, const Tv* __restrict__ partial,
                                                 const Tv* __restrict__ colpart, Tv* __restrict__ out,
-                                                Tv* __restrict__ out_last, int r) {
-  const int grow = int((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
-  const int i = threadIdx.x & 63;
-  if (grow >= A.nrows) return;
+                                                Tv* __restrict__ out_last, int r, int rp) {
+  __shared__ Tv red[256];
+  const int grow = blockIdx.x;
   int q = 0;
   while (q + 1 < A.ndep && A.dep[q + 1].row0 <= grow) ++q;
   const RedDepth& D = A.dep[q];
   const int row = grow - D.row0;
-  if (i >= r) return;
-  Tv v0 = zero<Tv>(), v1 = zero<Tv>(), v2 = zero<Tv>(), v3 = zero<Tv>();
-  for (int sidx = 0; sidx < D.nsrc; ++sidx) {
-    const Tv* pp = partial + int64_t(D.base[sidx]) * r + i;
-    int t = D.rtp[sidx][row];
-    const int t1 = D.rtp[sidx][row + 1];
-    for (; t + 4 <= t1; t += 4) {
-      v0 += pp[int64_t(t) * r];
-      v1 += pp[int64_t(t + 1) * r];
-      v2 += pp[int64_t(t + 2) * r];
-      v3 += pp[int64_t(t + 3) * r];
+  const int i = threadIdx.x & (rp - 1), g = threadIdx.x / rp, ng = 256 / rp;
+  Tv v = zero<Tv>();
+  if (i < r) {
+    for (int sidx = 0; sidx < D.nsrc; ++sidx) {
+      const int64_t t0 = D.rtp[sidx][row], nt = D.rtp[sidx][row + 1] - t0;
+      sum_run(v, partial + int64_t(D.base[sidx]) * r + i, r, t0 + g * nt / ng, t0 + (g + 1) * nt / ng);
+      const int64_t c0 = D.cptr[sidx][row], nc = D.cptr[sidx][row + 1] - c0;
+      sum_run(v, colpart + int64_t(D.slot[sidx]) * r + i, r, c0 + g * nc / ng, c0 + (g + 1) * nc / ng);
     }
-    for (; t < t1; ++t) v0 += pp[int64_t(t) * r];
-    const Tv* cp = colpart + int64_t(D.slot[sidx]) * r + i;
-    int c = D.cptr[sidx][row];
-    const int c1 = D.cptr[sidx][row + 1];
-    for (; c + 4 <= c1; c += 4) {
-      v0 += cp[int64_t(c) * r];
-      v1 += cp[int64_t(c + 1) * r];
-      v2 += cp[int64_t(c + 2) * r];
-      v3 += cp[int64_t(c + 3) * r];
-    }
-    for (; c < c1; ++c) v0 += cp[int64_t(c) * r];
   }
-  const Tv v = (v0 + v1) + (v2 + v3);
+  red[threadIdx.x] = v;
+  __syncthreads();
+  if (threadIdx.x >= r) return;
+  for (int k = 1; k < ng; ++k) v += red[k * rp + threadIdx.x];
   if (out_last && q == A.ndep - 1) out_last[int64_t(row) * r + i] = v;
   else out[D.out_off + int64_t(row) * r + i] = v;
 }
@@ -313,21 +322,6 @@ __global__ __launch_bounds__(256) void k_leaf_up(const int* __restrict__ leaf_of
 }
 
 // ------------------------------------------------------------ fine output
-// v += p[t * stride] for t in [a, b), four loads in flight, in a fixed order.
-template <typename Tv>
-__device__ __forceinline__ void sum_run(Tv& v, const Tv* __restrict__ p, int64_t stride, int64_t a, int64_t b) {
-  Tv v0 = zero<Tv>(), v1 = zero<Tv>(), v2 = zero<Tv>(), v3 = zero<Tv>();
-  int64_t t = a;
-  for (; t + 4 <= b; t += 4) {
-    v0 += p[t * stride];
-    v1 += p[(t + 1) * stride];
-    v2 += p[(t + 2) * stride];
-    v3 += p[(t + 3) * stride];
-  }
-  for (; t < b; ++t) v0 += p[t * stride];
-  v += (v0 + v1) + (v2 + v3);
-}
-
 // out[idx(i)] = alpha * (Q_leaf yhat_leaf + near sums)_i + beta * add[idx(i)]
 // for 64 rows i of one leaf per workgroup; idx = i or perm[i].  The near sums
 // are the row partials of the leaf's tasks and its column sums (nsplit per
@@ -487,14 +481,14 @@ void launch_reduce(H2& h, int p, int d0, int d1, const View* const* v0, const in
     rows += 1 << d;
   }
   A.nrows = rows;
-  const dim3 g(grid_waves(rows)), b(256);
+  const dim3 g(rows), b(256);
   if (p == P64)
     hipLaunchKernelGGL(k_reduce<double>, g, b, 0, h.stream, A, h.partial, h.colpart,
-                       static_cast<double*>(out), static_cast<double*>(out_last), h.r);
+                       static_cast<double*>(out), static_cast<double*>(out_last), h.r, 8 * h.T);
   else
     hipLaunchKernelGGL(k_reduce<float>, g, b, 0, h.stream, A, reinterpret_cast<const float*>(h.partial),
                        reinterpret_cast<const float*>(h.colpart), static_cast<float*>(out),
-                       static_cast<float*>(out_last), h.r);
+                       static_cast<float*>(out_last), h.r, 8 * h.T);
   check_launch("reduce");
 }
 
@@ -588,8 +582,8 @@ void launch_near_stored(H2& h, int p, const void* xtree) {
                        sn.ntasks, sn.tiles, sn.blk_col, sn.blk_slot, xc, sn.partial, sn.colpart);
     check_launch("near_gemv");
     h.time_end(KS_NEARST64, ev, double(sn.nblocks) * 64.0 * 64.0 * sizeof(double));
-    hipLaunchKernelGGL(k_reduce<double>, dim3(grid_waves(sn.nchunk)), dim3(256), 0, h.stream, A,
-                       sn.partial, sn.colpart, sn.yc, static_cast<double*>(nullptr), 64);
+    hipLaunchKernelGGL(k_reduce<double>, dim3(sn.nchunk), dim3(256), 0, h.stream, A,
+                       sn.partial, sn.colpart, sn.yc, static_cast<double*>(nullptr), 64, 64);
   } else {
     // FP32 partials and output in the first half of the FP64 buffers; the
     // padded input has a zero-padded FP32 buffer of its own
@@ -605,9 +599,9 @@ void launch_near_stored(H2& h, int p, const void* xtree) {
     hipLaunchKernelGGL(k_near_gemv32, dim3(grid_waves(sn.ntasks)), dim3(256), 0, h.stream, sn.task,
                        sn.ntasks, sn.tiles32, sn.blk_col, sn.blk_slot, xc, part, cpart);
     check_launch("near_gemv32");
-    hipLaunchKernelGGL(k_reduce<float>, dim3(grid_waves(sn.nchunk)), dim3(256), 0, h.stream, A,
+    hipLaunchKernelGGL(k_reduce<float>, dim3(sn.nchunk), dim3(256), 0, h.stream, A,
                        static_cast<const float*>(part), static_cast<const float*>(cpart),
-                       reinterpret_cast<float*>(sn.yc), static_cast<float*>(nullptr), 64);
+                       reinterpret_cast<float*>(sn.yc), static_cast<float*>(nullptr), 64, 64);
   }
   check_launch("near_reduce");
 }

@@ -20,7 +20,7 @@ namespace h2mg {
 namespace {
 
 constexpr int NT = 256;
-constexpr int MAX_PARTS = 512;
+constexpr int MAX_PARTS = DOT_PARTS;
 
 void check_launch(const char* what) {
   hipError_t e = hipGetLastError();
@@ -38,18 +38,12 @@ __device__ double block_sum(double v) {
   return s;
 }
 
-// Sum of np partials in a fixed order, computed by wave 0 and broadcast.
+// Sum of np partials in a fixed order, by the whole workgroup.
 __device__ double sum_parts(const double* part, int np) {
-  __shared__ double bc;
+  double s = 0.0;
+  for (int i = threadIdx.x; i < np; i += NT) s += part[i];
   __syncthreads();
-  if (threadIdx.x < 64) {
-    double s = 0.0;
-    for (int i = threadIdx.x; i < np; i += 64) s += part[i];
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-    if (threadIdx.x == 0) bc = s;
-  }
-  __syncthreads();
-  return bc;
+  return block_sum(s);
 }
 
 __global__ __launch_bounds__(NT) void k_gather(int64_t n, const int64_t* __restrict__ perm,
@@ -132,18 +126,18 @@ __global__ __launch_bounds__(NT) void k_dot(int64_t n, const Tv* __restrict__ x,
   if (threadIdx.x == 0) part[blockIdx.x] = s;
 }
 
-// alpha = gamma / delta; e += alpha p; s -= alpha q; partials of s.s.
-// gamma == 0 (exact convergence) gives alpha = 0; delta <= 0 with gamma > 0
-// flags a non-SPD operator and freezes the iterate.
+// alpha = gamma / delta; e += alpha p (e = alpha p when e_zero); s -= alpha q;
+// partials of s.s.  p may be s.  gamma == 0 (exact convergence) gives alpha =
+// 0; delta <= 0 with gamma > 0 flags a non-SPD operator and freezes the
+// iterate.
 template <typename Tv>
-__global__ __launch_bounds__(NT) void k_cg_update(int64_t n, Tv* __restrict__ e,
-                                                  const Tv* __restrict__ p, Tv* __restrict__ s,
+__global__ __launch_bounds__(NT) void k_cg_update(int64_t n, Tv* __restrict__ e, bool e_zero, const Tv* p, Tv* s,
                                                   const Tv* __restrict__ q,
-                                                  const double* __restrict__ gpart,
-                                                  const double* __restrict__ dpart, int np,
+                                                  const double* __restrict__ gpart, int ngp,
+                                                  const double* __restrict__ dpart, int ndp,
                                                   double* __restrict__ gnew, int* __restrict__ flag) {
-  const double gamma = sum_parts(gpart, np);
-  const double delta = sum_parts(dpart, np);
+  const double gamma = sum_parts(gpart, ngp);
+  const double delta = sum_parts(dpart, ndp);
   double alpha = 0.0;
   if (gamma != 0.0) {
     if (delta > 0.0) {
@@ -155,13 +149,28 @@ __global__ __launch_bounds__(NT) void k_cg_update(int64_t n, Tv* __restrict__ e,
   double acc = 0.0;
   const Tv al = Tv(alpha);
   for (int64_t i = int64_t(blockIdx.x) * NT + threadIdx.x; i < n; i += int64_t(gridDim.x) * NT) {
-    e[i] += al * p[i];
+    const Tv pi = p[i];
+    e[i] = e_zero ? al * pi : e[i] + al * pi;
     const Tv sn = s[i] - al * q[i];
     s[i] = sn;
     acc += double(sn) * double(sn);
   }
+  __syncthreads();
   const double t = block_sum(acc);
   if (threadIdx.x == 0) gnew[blockIdx.x] = t;
+}
+
+template <typename Tv>
+__global__ __launch_bounds__(NT) void k_copy_dot(int64_t n, const Tv* __restrict__ src, Tv* __restrict__ s,
+                                                 double* __restrict__ part) {
+  double acc = 0.0;
+  for (int64_t i = int64_t(blockIdx.x) * NT + threadIdx.x; i < n; i += int64_t(gridDim.x) * NT) {
+    const Tv v = src[i];
+    s[i] = v;
+    acc += double(v) * double(v);
+  }
+  const double t = block_sum(acc);
+  if (threadIdx.x == 0) part[blockIdx.x] = t;
 }
 
 // beta = gamma_new / gamma_old; p = s + beta p.
@@ -182,28 +191,6 @@ __global__ __launch_bounds__(NT) void k_check_finite(int64_t n, const Tv* __rest
                                                      int* __restrict__ flag) {
   const int64_t i = int64_t(blockIdx.x) * NT + threadIdx.x;
   if (i < n && !isfinite(double(x[i]))) atomicOr(flag, 1);
-}
-
-// z_b = M_b^{-1} s_b for every diagonal block b (one workgroup per block):
-// rows [off[b], off[b+1]) when off is given, else [b*stride, (b+1)*stride).
-// The stored inverses are symmetric, so thread i reads column i of block b,
-// coalesced across threads.
-template <typename Tm, typename Tv>
-__global__ __launch_bounds__(NT) void k_bj_apply(const int* __restrict__ off, int stride,
-                                                 const Tm* __restrict__ Minv, int ld,
-                                                 const Tv* __restrict__ s, Tv* __restrict__ z) {
-  __shared__ Tv sl[256];
-  const int b = blockIdx.x;
-  const int s0 = off ? off[b] : b * stride;
-  const int n = off ? off[b + 1] - s0 : stride;
-  for (int i = threadIdx.x; i < n; i += NT) sl[i] = s[s0 + i];
-  __syncthreads();
-  const Tm* M = Minv + int64_t(b) * ld * ld;
-  for (int i = threadIdx.x; i < n; i += NT) {
-    Tv acc = Tv(0);
-    for (int j = 0; j < n; ++j) acc += Tv(M[int64_t(j) * ld + i]) * sl[j];
-    z[s0 + i] = acc;
-  }
 }
 
 // ------------------------------------------------------------ triangular solves
@@ -382,34 +369,46 @@ void launch_dot(H2& h, int p, int64_t n, const void* x, const void* y, double* p
   check_launch("dot");
 }
 
-void launch_cg_update(H2& h, int p, int64_t n, void* e, const void* pv, void* s, const void* q,
-                      const double* gamma_part, const double* delta_part, double* gamma_new_part) {
+void launch_cg_update(H2& h, int p, int64_t n, void* e, bool e_zero, const void* pv, void* s, const void* q,
+                      const double* gamma_part, int ngp, const double* delta_part, int ndp,
+                      double* gamma_new_part) {
   const int np = dot_parts(n);
   if (p == P64)
     hipLaunchKernelGGL(k_cg_update<double>, dim3(np), dim3(NT), 0, h.stream, n,
-                       static_cast<double*>(e), static_cast<const double*>(pv),
-                       static_cast<double*>(s), static_cast<const double*>(q), gamma_part,
-                       delta_part, np, gamma_new_part, h.flags);
+                       static_cast<double*>(e), e_zero, static_cast<const double*>(pv),
+                       static_cast<double*>(s), static_cast<const double*>(q), gamma_part, ngp,
+                       delta_part, ndp, gamma_new_part, h.flags);
   else
     hipLaunchKernelGGL(k_cg_update<float>, dim3(np), dim3(NT), 0, h.stream, n,
-                       static_cast<float*>(e), static_cast<const float*>(pv),
-                       static_cast<float*>(s), static_cast<const float*>(q), gamma_part,
-                       delta_part, np, gamma_new_part, h.flags);
+                       static_cast<float*>(e), e_zero, static_cast<const float*>(pv),
+                       static_cast<float*>(s), static_cast<const float*>(q), gamma_part, ngp,
+                       delta_part, ndp, gamma_new_part, h.flags);
   check_launch("cg_update");
 }
 
 void launch_cg_pupdate(H2& h, int p, int64_t n, void* pv, const void* s,
-                       const double* gamma_old_part, const double* gamma_new_part) {
-  const int np = dot_parts(n);
+                       const double* gamma_old_part, const double* gamma_new_part, int np) {
+  const dim3 g(dot_parts(n)), b(NT);
   if (p == P64)
-    hipLaunchKernelGGL(k_cg_pupdate<double>, dim3(np), dim3(NT), 0, h.stream, n,
+    hipLaunchKernelGGL(k_cg_pupdate<double>, g, b, 0, h.stream, n,
                        static_cast<double*>(pv), static_cast<const double*>(s), gamma_old_part,
                        gamma_new_part, np);
   else
-    hipLaunchKernelGGL(k_cg_pupdate<float>, dim3(np), dim3(NT), 0, h.stream, n,
+    hipLaunchKernelGGL(k_cg_pupdate<float>, g, b, 0, h.stream, n,
                        static_cast<float*>(pv), static_cast<const float*>(s), gamma_old_part,
                        gamma_new_part, np);
   check_launch("cg_pupdate");
+}
+
+void launch_copy_dot(H2& h, int p, int64_t n, const void* src, void* s, double* part) {
+  const dim3 g(dot_parts(n)), b(NT);
+  if (p == P64)
+    hipLaunchKernelGGL(k_copy_dot<double>, g, b, 0, h.stream, n, static_cast<const double*>(src),
+                       static_cast<double*>(s), part);
+  else
+    hipLaunchKernelGGL(k_copy_dot<float>, g, b, 0, h.stream, n, static_cast<const float*>(src),
+                       static_cast<float*>(s), part);
+  check_launch("copy_dot");
 }
 
 void launch_chol_solve(H2& h, const double* L, int64_t N, double* x) {
@@ -443,28 +442,6 @@ void launch_inverse_solve(H2& h, int p, const void* r, void* e) {
                        static_cast<float*>(e));
   }
   check_launch("inverse_solve");
-}
-
-void launch_bj_apply(H2& h, int p, int k, const void* s, void* z) {
-  const bool fine = k == 1;
-  const int d = h.level_depth(k);
-  const int nb = fine ? h.nleaf : (1 << d);
-  const int* off = fine ? h.leaf_off : nullptr;
-  const int ld = fine ? h.bj_ld : h.r;
-  const int stride = h.r;
-  const size_t eb = p == P64 ? 8 : 4;
-  const char* base = static_cast<const char*>(fine ? h.bj_fine[p == P64 ? P64 : P32]
-                                                   : h.bj_coarse[p == P64 ? P64 : P32]);
-  if (!fine) base += size_t((1 << d) - 1) * h.r * h.r * eb;
-  if (p == P64)
-    hipLaunchKernelGGL((k_bj_apply<double, double>), dim3(nb), dim3(NT), 0, h.stream, off, stride,
-                       reinterpret_cast<const double*>(base), ld, static_cast<const double*>(s),
-                       static_cast<double*>(z));
-  else
-    hipLaunchKernelGGL((k_bj_apply<float, float>), dim3(nb), dim3(NT), 0, h.stream, off, stride,
-                       reinterpret_cast<const float*>(base), ld, static_cast<const float*>(s),
-                       static_cast<float*>(z));
-  check_launch("bj_apply");
 }
 
 void launch_scatter_rows(H2& h, const double* tree, double* user) {

@@ -79,9 +79,9 @@ Work make_work(H2& h, int p, bool second_corrections, VecSource& src) {
   w.q = src.get(size_t(h.n) * vb);
   w.tmp = src.get(size_t(h.n) * vb);
   w.z = src.get(size_t(h.n) * vb);
-  w.gpart[0] = h.dot_part + 512;
-  w.gpart[1] = h.dot_part + 1024;
-  w.dpart = h.dot_part + 1536;
+  w.gpart[0] = h.dot_part + DOT_PARTS;
+  w.gpart[1] = h.dot_part + 2 * DOT_PARTS;
+  w.dpart = h.sweep_part;
   return w;
 }
 
@@ -119,42 +119,53 @@ void read_flags(H2& h, int* f) {
 
 // e = Iter(A_k, rhs, e0): n CG steps (plain, or preconditioned by the
 // block-Jacobi inverses when w.smoother == 1); e holds e0 on entry unless
-// e0_zero.
+// e0_zero.  On the coarse levels a step is five launches: the upsweep forms
+// the direction, the block products and their reduce, the downsweep with
+// p . A p, and the update with the preconditioner and the new residual's
+// product.
 void cg(H2& h, int p, int k, Work& w, const void* rhs, void* e, bool e0_zero, int nsteps) {
   const int vp = vprec(p);
   const int64_t N = h.level_size(k);
   const bool pre = w.smoother == 1;
-  if (e0_zero) zero(h, e, N, vp);
-  if (nsteps <= 0) return;
-  if (e0_zero) {
-    launch_copy(h, vp, rhs, w.s, N);
-  } else {
-    apply_level(h, p, k, e, w.q);
-    launch_copy(h, vp, rhs, w.s, N);
-    launch_axpby(h, vp, N, -1.0, w.q, 1.0, w.s);
+  if (nsteps <= 0) {
+    if (e0_zero) zero(h, e, N, vp);
+    return;
   }
-  int cur = 0;
+  if (!e0_zero) residual_level(h, p, k, e, w.s, rhs);
+  const void* s0 = e0_zero ? rhs : w.s;
+  const void* z = pre ? w.z : w.s;     // the residual a direction starts from
+  int cur = 0, ngp;
   if (pre) {
-    launch_bj_apply(h, p, k, w.s, w.z);
-    launch_copy(h, vp, w.z, w.pv, N);
-    launch_dot(h, vp, N, w.s, w.z, w.gpart[cur]);
+    ngp = launch_cg_step_bj(h, p, k, s0, nullptr, false, nullptr, w.s, nullptr, w.z, nullptr, 0, nullptr, 0,
+                            w.gpart[cur]);
   } else {
-    launch_copy(h, vp, w.s, w.pv, N);
-    launch_dot(h, vp, N, w.s, w.s, w.gpart[cur]);
+    if (e0_zero) launch_copy_dot(h, vp, N, rhs, w.s, w.gpart[cur]);
+    else launch_dot(h, vp, N, w.s, w.s, w.gpart[cur]);
+    ngp = dot_parts(N);
   }
-  double* scratch = h.dot_part + 2048;
+  // the direction: where the upsweep leaves it, on level 1 a vector of its
+  // own (for a single step z itself)
+  void* pv = k >= 2 ? level_input(h, p, k) : w.pv;
+  const void* dir = pv;
+  if (k == 1 && nsteps == 1) dir = z;
+  else if (k == 1) launch_copy(h, vp, z, pv, N);
   for (int it = 0; it < nsteps; ++it) {
-    apply_level(h, p, k, w.pv, w.q);
-    launch_dot(h, vp, N, w.pv, w.q, w.dpart);
-    if (pre) {
-      launch_cg_update(h, vp, N, e, w.pv, w.s, w.q, w.gpart[cur], w.dpart, scratch);
-      launch_bj_apply(h, p, k, w.s, w.z);
-      launch_dot(h, vp, N, w.s, w.z, w.gpart[1 - cur]);
-      if (it + 1 < nsteps) launch_cg_pupdate(h, vp, N, w.pv, w.z, w.gpart[cur], w.gpart[1 - cur]);
+    int ndp;
+    if (k >= 2) {
+      ndp = apply_coarse(h, p, k, it == 0 ? CoarseInput{z} : CoarseInput{z, pv, w.gpart[1 - cur], w.gpart[cur], ngp},
+                         w.q, nullptr, w.dpart);
     } else {
-      launch_cg_update(h, vp, N, e, w.pv, w.s, w.q, w.gpart[cur], w.dpart, w.gpart[1 - cur]);
-      if (it + 1 < nsteps) launch_cg_pupdate(h, vp, N, w.pv, w.s, w.gpart[cur], w.gpart[1 - cur]);
+      if (it > 0) launch_cg_pupdate(h, vp, N, pv, z, w.gpart[1 - cur], w.gpart[cur], ngp);
+      apply_fine(h, p, dir, w.q, 1.0, nullptr, 0.0);
+      launch_dot(h, vp, N, dir, w.q, w.dpart);
+      ndp = dot_parts(N);
     }
+    const bool e_zero = e0_zero && it == 0;
+    if (pre)
+      launch_cg_step_bj(h, p, k, nullptr, e, e_zero, dir, w.s, w.q, w.z, w.gpart[cur], ngp, w.dpart, ndp,
+                        w.gpart[1 - cur]);
+    else
+      launch_cg_update(h, vp, N, e, e_zero, dir, w.s, w.q, w.gpart[cur], ngp, w.dpart, ndp, w.gpart[1 - cur]);
     cur = 1 - cur;
   }
 }
@@ -187,19 +198,17 @@ void mg(H2& h, int p, Work& w, int k, int kind, int n_f, int n_c) {
     return;
   }
   const int nk = k == 1 ? n_f : n_c;
-  const int64_t N = h.level_size(k);
   cg(h, p, k, w, w.r[k], w.et[k], true, nk);
   // restriction of the residual: r_{k+1} = U_k^T (r_k - A_k e~_k)
-  apply_level(h, p, k, w.et[k], w.tmp);
-  launch_axpby(h, vp, N, 1.0, w.r[k], -1.0, w.tmp);
+  residual_level(h, p, k, w.et[k], w.tmp, w.r[k]);
   restrict_level(h, p, k, w.tmp, w.r[k + 1]);
   mg(h, p, w, k + 1, kind, n_f, n_c);
   if (kind != CYCLE_V && k + 1 < l) {
     // second coarse correction on r_{k+1} - A_{k+1} e_{k+1}
     const int64_t N1 = h.level_size(k + 1);
     launch_copy(h, vp, w.et[k + 1], w.ec[k + 1], N1);
-    apply_level(h, p, k + 1, w.et[k + 1], w.tmp);
-    launch_axpby(h, vp, N1, -1.0, w.tmp, 1.0, w.r[k + 1]);
+    residual_level(h, p, k + 1, w.et[k + 1], w.tmp, w.r[k + 1]);
+    launch_copy(h, vp, w.tmp, w.r[k + 1], N1);
     mg(h, p, w, k + 1, kind == CYCLE_F ? CYCLE_V : CYCLE_W, n_f, n_c);
     launch_axpby(h, vp, N1, 1.0, w.ec[k + 1], 1.0, w.et[k + 1]);
   }
@@ -247,14 +256,15 @@ h2mg_status plain_cg(H2& h, Work& w, const double* bt, double* xt, double nb, co
   double* z = static_cast<double*>(w.z);
   double* pv = static_cast<double*>(w.pv);
   double* q = static_cast<double*>(w.q);
-  double* ss = h.dot_part + 2048;
+  double* ss = h.dot_part + 3 * DOT_PARTS;
   // s = b - A x
   apply_fine(h, P64, xt, s, -1.0, bt, 1.0);
   int cur = 0;
+  int ngp = np;                        // partial sums of gamma
   if (pre) {
-    launch_bj_apply(h, P64, 1, s, z);
+    ngp = launch_cg_step_bj(h, P64, 1, s, nullptr, false, nullptr, s, nullptr, z, nullptr, 0, nullptr, 0,
+                            w.gpart[cur]);
     launch_copy(h, P64, z, pv, n);
-    launch_dot(h, P64, n, s, z, w.gpart[cur]);
     launch_dot(h, P64, n, s, s, ss);
   } else {
     launch_copy(h, P64, s, pv, n);
@@ -279,13 +289,12 @@ h2mg_status plain_cg(H2& h, Work& w, const double* bt, double* xt, double nb, co
     apply_fine(h, P64, pv, q, 1.0, nullptr, 0.0);
     launch_dot(h, P64, n, pv, q, w.dpart);
     if (pre) {
-      launch_cg_update(h, P64, n, xt, pv, s, q, w.gpart[cur], w.dpart, ss);
-      launch_bj_apply(h, P64, 1, s, z);
-      launch_dot(h, P64, n, s, z, w.gpart[1 - cur]);
-      launch_cg_pupdate(h, P64, n, pv, z, w.gpart[cur], w.gpart[1 - cur]);
+      launch_cg_step_bj(h, P64, 1, nullptr, xt, false, pv, s, q, z, w.gpart[cur], ngp, w.dpart, np, w.gpart[1 - cur]);
+      launch_dot(h, P64, n, s, s, ss);
+      launch_cg_pupdate(h, P64, n, pv, z, w.gpart[cur], w.gpart[1 - cur], ngp);
     } else {
-      launch_cg_update(h, P64, n, xt, pv, s, q, w.gpart[cur], w.dpart, w.gpart[1 - cur]);
-      launch_cg_pupdate(h, P64, n, pv, s, w.gpart[cur], w.gpart[1 - cur]);
+      launch_cg_update(h, P64, n, xt, false, pv, s, q, w.gpart[cur], ngp, w.dpart, np, w.gpart[1 - cur]);
+      launch_cg_pupdate(h, P64, n, pv, s, w.gpart[cur], w.gpart[1 - cur], ngp);
     }
     cur = 1 - cur;
   }

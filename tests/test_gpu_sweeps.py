@@ -1,0 +1,30 @@
+"""Tree sweeps with several levels per launch, on trees deep enough that a sweep takes one launch, two
+and three, for every tile width: A_{k+1} = U_k^T A_k U_k, applied level by level.  The shallowest level
+has no sweep at all, so the chain is anchored there."""
+import pytest
+import torch
+
+from paper_2501_17656_amd import H2Matrix
+
+pytestmark = pytest.mark.gpu
+
+
+# Chebyshev nodes (= rank, in one dimension), leaf size, leaves
+@pytest.mark.parametrize("m,leaf,leaves", [(2, 4, 4096), (8, 9, 1024), (9, 16, 512), (16, 20, 2048), (25, 32, 512),
+                                           (33, 40, 512), (64, 70, 512), (64, 70, 64), (16, 20, 8)])
+def test_levels_agree(m, leaf, leaves):
+    n = leaf * leaves - leaves // 3
+    gen = torch.Generator(device="cuda").manual_seed(m + leaves)
+    pts = torch.rand((n, 1), dtype=torch.float64, device="cuda", generator=gen)
+    g = H2Matrix(pts, "exp", 0.05, 1.0, leaf, 0.7, m)
+    g.setup(["fp64", "fp32"])
+    assert g.levels >= 2
+    for k in range(1, g.levels):
+        x = torch.randn(g.level_size(k + 1), dtype=torch.float64, device="cuda", generator=gen)
+        want = g.restrict(k, g.level_apply(k, g.prolong(k, x)))
+        y = g.level_apply(k + 1, x)
+        # sums of at most n products in a basis with orthonormal columns
+        assert float((y - want).norm()) <= 1e-13 * float(want.norm()), k
+        low = g.level_apply(k + 1, x, precision="fp32")
+        assert float((y - low).norm()) <= 1e-5 * float(y.norm()), k
+    g.close()
