@@ -18,7 +18,7 @@ INCLUDE = os.path.join(ROOT, "include")
 BUILD_DIR = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libh2mg.so")
 
-HIP_SOURCES = ["kernels_setup.hip", "kernels_apply.hip", "kernels_near.hip", "kernels_sweep.hip",
+HIP_SOURCES = ["kernels_setup.hip", "kernels_apply.hip", "kernels_near.hip", "kernels_sweep.hip", "kernels_sweep16.hip",
                "kernels_solve.hip", "kernels_bem.hip",
                "kernels_block.hip", "noalloc.hip"]
 CPP_SOURCES = ["plan.cpp", "h2_build.cpp", "h2_apply.cpp", "block.cpp", "solver.cpp", "abi.cpp"]

@@ -295,13 +295,10 @@ void apply_fine16(H2& h, int p, const void* X, void* out, double alpha, const vo
   const void* yhat = nullptr;
   if (h.d_top >= 0) {
     launch_leaf_up16(h, p, X, at_depth(w.xall, p, h.L, r));
-    for (int d = h.L - 1; d >= h.d_top; --d)
-      launch_transfer_up16(h, p, d, at_depth(w.xall, p, d + 1, r), at_depth(w.xall, p, d, r));
+    launch_sweep_up16(h, p, h.L, w.xall, nullptr, nullptr, nullptr, nullptr, 0);
     launch_tgemm(h, p, h.T, w.fine, h.prec[p].blk, r, w.xall, w.partial);
     launch_reduce16(h, p, w.fine, r, w.partial, w.yall);
-    for (int d = h.d_top + 1; d <= h.L; ++d)
-      launch_transfer_down16(h, p, d - 1, at_depth(w.yall, p, d - 1, r), at_depth(w.yall, p, d, r),
-                             at_depth(w.yall, p, d, r));
+    launch_sweep_down16(h, p, h.L, w.yall, at_depth(w.yall, p, h.L, r), nullptr, nullptr, nullptr);
     yhat = at_depth(w.yall, p, h.L, r);
   }
   const StoredNear& sn = h.snear;
@@ -325,24 +322,39 @@ void apply_fine16(H2& h, int p, const void* X, void* out, double alpha, const vo
   launch_leaf_down16(h, p, yhat, w.yc, out, alpha, add, beta);
 }
 
-// Level k >= 2 (depth d = L - k + 2), coefficient order: Y = A_k X.
-void apply_coarse16(H2& h, int p, int k, const void* X, void* Y) {
+// Where a product of level k >= 2 keeps its input until the next one.
+inline void* level_input16(H2& h, int p, int k) { return at_depth(h.blk16.xall, p, h.level_depth(k), h.r); }
+
+// Level k >= 2 (depth d = L - k + 2), coefficient order: Y = A_k X, or add -
+// A_k X, with X formed by the upsweep (see CoarseInput); with dpart the
+// per-column partial sums of X . Y (returns their number).  The part behind
+// the tile products:
+int coarse_output16(H2& h, int p, int k, void* Y, const void* add, double* dpart) {
   BlockWork& w = h.blk16;
   const int r = h.r, d = h.level_depth(k);
-  launch_copy(h, vprec(p), X, at_depth(w.xall, p, d, r), int64_t(1 << d) * r * NR);
-  for (int q = d - 1; q >= h.d_top; --q)
-    launch_transfer_up16(h, p, q, at_depth(w.xall, p, q + 1, r), at_depth(w.xall, p, q, r));
-  launch_tgemm(h, p, h.T, w.coarse[d], h.prec[p].blk, r, w.xall, w.partial);
   launch_reduce16(h, p, w.coarse[d], r, w.partial, w.yall);
-  for (int q = h.d_top + 1; q <= d; ++q)
-    launch_transfer_down16(h, p, q - 1, at_depth(w.yall, p, q - 1, r), q == d ? Y : at_depth(w.yall, p, q, r),
-                           at_depth(w.yall, p, q, r));
-  if (d == h.d_top) launch_copy(h, vprec(p), at_depth(w.yall, p, d, r), Y, int64_t(1 << d) * r * NR);
+  const void* X = at_depth(w.xall, p, d, r);
+  if (d > h.d_top) return launch_sweep_down16(h, p, d, w.yall, Y, add, X, dpart);
+  const int64_t rows = int64_t(1 << d) * r;
+  launch_copy(h, vprec(p), at_depth(w.yall, p, d, r), Y, rows * NR);
+  if (add) launch_axpby(h, vprec(p), rows * NR, 1.0, add, -1.0, Y);
+  if (!dpart) return 0;
+  launch_dot16(h, vprec(p), rows, X, Y, dpart);
+  return parts16(rows);
 }
 
-void apply16(H2& h, int p, int k, const void* X, void* Y) {
-  if (k == 1) apply_fine16(h, p, X, Y, 1.0, nullptr, 0.0);
-  else apply_coarse16(h, p, k, X, Y);
+int apply_coarse16(H2& h, int p, int k, const CoarseInput& in, void* Y, const void* add, double* dpart) {
+  BlockWork& w = h.blk16;
+  const int d = h.level_depth(k);
+  launch_sweep_up16(h, p, d, w.xall, in.src, in.prev, in.gold, in.gnew, in.np);
+  launch_tgemm(h, p, h.T, w.coarse[d], h.prec[p].blk, h.r, w.xall, w.partial);
+  return coarse_output16(h, p, k, Y, add, dpart);
+}
+
+// out = b - A_k X.
+void residual16(H2& h, int p, int k, const void* X, void* out, const void* b) {
+  if (k == 1) apply_fine16(h, p, X, out, -1.0, b, 1.0);
+  else apply_coarse16(h, p, k, CoarseInput{X}, out, b, nullptr);
 }
 
 // ------------------------------------------------------------ cycle
@@ -351,12 +363,11 @@ struct Work16 {
   int smoother = 0;
   std::vector<void*> r, et, ec;
   void *s = nullptr, *pv = nullptr, *q = nullptr, *tmp = nullptr, *z = nullptr;
-  double* part = nullptr;              // 4 slots of 256 x NR partial sums
+  double* part = nullptr;              // partial sums: two slots of DOT_PARTS x NR, one of max(DOT_PARTS, leaves)
   double* coarse64 = nullptr;          // Nl x NR, FP64 coarse solve of a low-precision cycle
   std::vector<void*> owned;
-  double* gpart(int i) const { return part + size_t(i) * 256 * NR; }
-  double* dpart() const { return part + size_t(2) * 256 * NR; }
-  double* scratch() const { return part + size_t(3) * 256 * NR; }
+  double* gpart(int i) const { return part + size_t(i) * DOT_PARTS * NR; }
+  double* dpart() const { return part + size_t(2) * DOT_PARTS * NR; }
 };
 
 void make_work16(H2& h, Work16& w, int p, bool second) {
@@ -380,7 +391,7 @@ void make_work16(H2& h, Work16& w, int p, bool second) {
   w.q = take(size_t(h.n) * vb);
   w.tmp = take(size_t(h.n) * NR * sizeof(double));
   w.z = take(size_t(h.n) * vb);
-  w.part = static_cast<double*>(take(size_t(4) * 256 * NR * sizeof(double)));
+  w.part = static_cast<double*>(take((size_t(2) * DOT_PARTS + std::max(h.nleaf, DOT_PARTS)) * NR * sizeof(double)));
   if (p != P64) w.coarse64 = static_cast<double*>(take(size_t(h.Nl) * NR * sizeof(double)));
 }
 
@@ -389,42 +400,67 @@ void release_work16(H2& h, Work16& w) {
   w.owned.clear();
 }
 
+// The parts of a CG smoothing on every column, for one problem: the residual
+// s0 (rhs, or w.s) in place with its preconditioned form and products; the
+// direction's starting point; one update.  cur: the slot of the current
+// products; returned: their number.
+int cg16_begin(H2& h, Work16& w, int k, const void* s0, int cur) {
+  const int vp = vprec(w.p);
+  const int64_t N = h.level_size(k);
+  if (w.smoother == 1)
+    return launch_cg_step16_bj(h, w.p, k, s0, nullptr, false, nullptr, w.s, nullptr, w.z, nullptr, 0, nullptr, 0,
+                               w.gpart(cur));
+  if (s0 != w.s) launch_copy_dot16(h, vp, N, s0, w.s, w.gpart(cur));
+  else launch_dot16(h, vp, N, w.s, w.s, w.gpart(cur));
+  return parts16(N);
+}
+const void* cg16_z(const Work16& w) { return w.smoother == 1 ? w.z : w.s; }
+// The direction: where the upsweep leaves it; on level 1 a vector of its own,
+// or for a single step z itself.
+const void* cg16_direction(H2& h, Work16& w, int k, int nsteps) {
+  if (k >= 2) return level_input16(h, w.p, k);
+  if (nsteps == 1) return cg16_z(w);
+  launch_copy(h, vprec(w.p), cg16_z(w), w.pv, h.level_size(k) * NR);
+  return w.pv;
+}
+CoarseInput cg16_input(H2& h, Work16& w, int k, int it, int cur, int ngp) {
+  if (it == 0) return CoarseInput{cg16_z(w)};
+  return CoarseInput{cg16_z(w), level_input16(h, w.p, k), w.gpart(1 - cur), w.gpart(cur), ngp};
+}
+void cg16_update(H2& h, Work16& w, int k, void* e, bool e_zero, const void* dir, int cur, int ngp, int ndp) {
+  if (w.smoother == 1)
+    launch_cg_step16_bj(h, w.p, k, nullptr, e, e_zero, dir, w.s, w.q, w.z, w.gpart(cur), ngp, w.dpart(), ndp,
+                        w.gpart(1 - cur));
+  else
+    launch_cg_update16(h, vprec(w.p), h.level_size(k), e, e_zero, dir, w.s, w.q, w.gpart(cur), ngp, w.dpart(), ndp,
+                       w.gpart(1 - cur));
+}
+
 // e = Iter(A_k, rhs, e0) on every column: nsteps of CG, or of block-Jacobi
 // PCG when w.smoother == 1; e holds e0 on entry unless e0_zero.
 void cg16(H2& h, Work16& w, int k, const void* rhs, void* e, bool e0_zero, int nsteps) {
   const int p = w.p, vp = vprec(p);
-  const int64_t N = h.level_size(k), nf = N * NR;
-  const bool pre = w.smoother == 1;
-  if (e0_zero) launch_zero(h, vp, e, nf);
-  if (nsteps <= 0) return;
-  if (e0_zero) {
-    launch_copy(h, vp, rhs, w.s, nf);
-  } else {
-    apply16(h, p, k, e, w.q);
-    launch_copy(h, vp, rhs, w.s, nf);
-    launch_axpby(h, vp, nf, -1.0, w.q, 1.0, w.s);
+  const int64_t N = h.level_size(k);
+  if (nsteps <= 0) {
+    if (e0_zero) launch_zero(h, vp, e, N * NR);
+    return;
   }
+  if (!e0_zero) residual16(h, p, k, e, w.s, rhs);
   int cur = 0;
-  if (pre) {
-    launch_bj_apply16(h, p, k, w.s, w.z);
-    launch_copy(h, vp, w.z, w.pv, nf);
-    launch_dot16(h, vp, N, w.s, w.z, w.gpart(cur));
-  } else {
-    launch_copy(h, vp, w.s, w.pv, nf);
-    launch_dot16(h, vp, N, w.s, w.s, w.gpart(cur));
-  }
+  int ngp = cg16_begin(h, w, k, e0_zero ? rhs : w.s, cur);
+  const void* dir = cg16_direction(h, w, k, nsteps);
   for (int it = 0; it < nsteps; ++it) {
-    apply16(h, p, k, w.pv, w.q);
-    launch_dot16(h, vp, N, w.pv, w.q, w.dpart());
-    if (pre) {
-      launch_cg_update16(h, vp, N, e, w.pv, w.s, w.q, w.gpart(cur), w.dpart(), w.scratch());
-      launch_bj_apply16(h, p, k, w.s, w.z);
-      launch_dot16(h, vp, N, w.s, w.z, w.gpart(1 - cur));
-      if (it + 1 < nsteps) launch_cg_pupdate16(h, vp, N, w.pv, w.z, w.gpart(cur), w.gpart(1 - cur));
+    int ndp;
+    if (k >= 2) {
+      ndp = apply_coarse16(h, p, k, cg16_input(h, w, k, it, cur, ngp), w.q, nullptr, w.dpart());
     } else {
-      launch_cg_update16(h, vp, N, e, w.pv, w.s, w.q, w.gpart(cur), w.dpart(), w.gpart(1 - cur));
-      if (it + 1 < nsteps) launch_cg_pupdate16(h, vp, N, w.pv, w.s, w.gpart(cur), w.gpart(1 - cur));
+      if (it > 0) launch_cg_pupdate16(h, vp, N, w.pv, cg16_z(w), w.gpart(1 - cur), w.gpart(cur), ngp);
+      apply_fine16(h, p, dir, w.q, 1.0, nullptr, 0.0);
+      launch_dot16(h, vp, N, dir, w.q, w.dpart());
+      ndp = parts16(N);
     }
+    cg16_update(h, w, k, e, e0_zero && it == 0, dir, cur, ngp, ndp);
+    if (w.smoother != 1) ngp = parts16(N);
     cur = 1 - cur;
   }
 }
@@ -455,25 +491,20 @@ void mg16(H2& h, Work16& w, int k, int kind, int n_f, int n_c) {
     return;
   }
   const int nk = k == 1 ? n_f : n_c;
-  const int64_t nf = h.level_size(k) * NR;
   cg16(h, w, k, w.r[k], w.et[k], true, nk);
   // R_{k+1} = U_k^T (R_k - A_k E~_k)
-  apply16(h, p, k, w.et[k], w.tmp);
-  launch_axpby(h, vp, nf, 1.0, w.r[k], -1.0, w.tmp);
-  if (k == 1) launch_leaf_up16(h, p, w.tmp, w.r[k + 1]);
-  else launch_transfer_up16(h, p, h.level_depth(k) - 1, w.tmp, w.r[k + 1]);
+  residual16(h, p, k, w.et[k], w.tmp, w.r[k]);
+  launch_restrict16(h, p, k, w.tmp, w.r[k + 1]);
   mg16(h, w, k + 1, kind, n_f, n_c);
   if (kind != CYCLE_V && k + 1 < l) {
     const int64_t nf1 = h.level_size(k + 1) * NR;
     launch_copy(h, vp, w.et[k + 1], w.ec[k + 1], nf1);
-    apply16(h, p, k + 1, w.et[k + 1], w.tmp);
-    launch_axpby(h, vp, nf1, -1.0, w.tmp, 1.0, w.r[k + 1]);
+    residual16(h, p, k + 1, w.et[k + 1], w.tmp, w.r[k + 1]);
+    launch_copy(h, vp, w.tmp, w.r[k + 1], nf1);
     mg16(h, w, k + 1, kind == CYCLE_F ? CYCLE_V : CYCLE_W, n_f, n_c);
     launch_axpby(h, vp, nf1, 1.0, w.ec[k + 1], 1.0, w.et[k + 1]);
   }
-  // E~_k += U_k E_{k+1}
-  if (k == 1) launch_leaf_down16(h, p, w.et[k + 1], nullptr, w.et[k], 1.0, w.et[k], 1.0);
-  else launch_transfer_down16(h, p, h.level_depth(k) - 1, w.et[k + 1], w.et[k], w.et[k]);
+  launch_prolong16(h, p, k, w.et[k + 1], w.et[k]);
   cg16(h, w, k, w.r[k], w.et[k], false, nk);
 }
 
@@ -565,10 +596,13 @@ class MemberSection {
   bool on_ = false;
 };
 
-// Y_m = A_k X_m for every member (each at its own level k).
-void apply16_group(const std::vector<GM>& G, int p, int k, const std::vector<const void*>& X,
+// Y_m = A_k X_m, or alpha A_k X_m + beta add_m on level 1 and add_m - A_k X_m
+// on the others, for every member (each at its own level k; on level 1 the
+// input is in.src).  dpart (levels k >= 2): the per-column partial sums of X . Y
+// as well, their numbers in *ndp.
+void apply16_group(const std::vector<GM>& G, int p, int k, const std::vector<CoarseInput>& X,
                    const std::vector<void*>& Y, double alpha = 1.0, const std::vector<const void*>* add = nullptr,
-                   double beta = 0.0) {
+                   double beta = 0.0, std::vector<int>* ndp = nullptr) {
   if (G.empty()) return;
   const hipStream_t st = G[0].h->stream;
   const int vp = vprec(p);
@@ -580,9 +614,8 @@ void apply16_group(const std::vector<GM>& G, int p, int k, const std::vector<con
       H2& h = *G[i].h;
       BlockWork& w = h.blk16;
       if (h.d_top < 0) continue;
-      launch_leaf_up16(h, p, X[i], at_depth(w.xall, p, h.L, h.r));
-      for (int d = h.L - 1; d >= h.d_top; --d)
-        launch_transfer_up16(h, p, d, at_depth(w.xall, p, d + 1, h.r), at_depth(w.xall, p, d, h.r));
+      launch_leaf_up16(h, p, X[i].src, at_depth(w.xall, p, h.L, h.r));
+      launch_sweep_up16(h, p, h.L, w.xall, nullptr, nullptr, nullptr, nullptr, 0);
       tiles.push_back(GroupTiles{h.T, &w.fine, h.prec[p].blk, h.r, w.xall, w.partial});
     }
     up.end();
@@ -594,15 +627,13 @@ void apply16_group(const std::vector<GM>& G, int p, int k, const std::vector<con
       BlockWork& w = h.blk16;
       if (h.d_top >= 0) {
         launch_reduce16(h, p, w.fine, h.r, w.partial, w.yall);
-        for (int d = h.d_top + 1; d <= h.L; ++d)
-          launch_transfer_down16(h, p, d - 1, at_depth(w.yall, p, d - 1, h.r), at_depth(w.yall, p, d, h.r),
-                                 at_depth(w.yall, p, d, h.r));
         yhat[i] = at_depth(w.yall, p, h.L, h.r);
+        launch_sweep_down16(h, p, h.L, w.yall, at_depth(w.yall, p, h.L, h.r), nullptr, nullptr, nullptr);
       }
-      xc[i] = X[i];
+      xc[i] = X[i].src;
       if (!h.snear.identity) {
         void* buf = p == P64 ? static_cast<void*>(w.xc64) : static_cast<void*>(w.xc32);
-        launch_near_pad16(h, p, X[i], buf);
+        launch_near_pad16(h, p, X[i].src, buf);
         xc[i] = buf;
       }
     }
@@ -634,26 +665,27 @@ void apply16_group(const std::vector<GM>& G, int p, int k, const std::vector<con
   for (size_t i = 0; i < G.size(); ++i) {
     H2& h = *G[i].h;
     BlockWork& w = h.blk16;
-    const int r = h.r, d = h.level_depth(k);
-    launch_copy(h, vp, X[i], at_depth(w.xall, p, d, r), int64_t(1 << d) * r * NR);
-    for (int q = d - 1; q >= h.d_top; --q)
-      launch_transfer_up16(h, p, q, at_depth(w.xall, p, q + 1, r), at_depth(w.xall, p, q, r));
-    tiles.push_back(GroupTiles{h.T, &w.coarse[d], h.prec[p].blk, r, w.xall, w.partial});
+    const int d = h.level_depth(k);
+    launch_sweep_up16(h, p, d, w.xall, X[i].src, X[i].prev, X[i].gold, X[i].gnew, X[i].np);
+    tiles.push_back(GroupTiles{h.T, &w.coarse[d], h.prec[p].blk, h.r, w.xall, w.partial});
   }
   up.end();
   launch_tgemm_group(st, p, tiles);
+  if (ndp) ndp->assign(G.size(), 0);
   MemberSection down(G);
   for (size_t i = 0; i < G.size(); ++i) {
-    H2& h = *G[i].h;
-    BlockWork& w = h.blk16;
-    const int r = h.r, d = h.level_depth(k);
-    launch_reduce16(h, p, w.coarse[d], r, w.partial, w.yall);
-    for (int q = h.d_top + 1; q <= d; ++q)
-      launch_transfer_down16(h, p, q - 1, at_depth(w.yall, p, q - 1, r), q == d ? Y[i] : at_depth(w.yall, p, q, r),
-                             at_depth(w.yall, p, q, r));
-    if (d == h.d_top) launch_copy(h, vp, at_depth(w.yall, p, d, r), Y[i], int64_t(1 << d) * r * NR);
+    const int nd = coarse_output16(*G[i].h, p, k, Y[i], add ? (*add)[i] : nullptr, ndp ? G[i].w->dpart() : nullptr);
+    if (ndp) (*ndp)[i] = nd;
   }
   down.end();
+}
+
+// out_m = b_m - A_k X_m for every member.
+void residual16_group(const std::vector<GM>& G, int p, int k, const std::vector<const void*>& X,
+                      const std::vector<void*>& out, const std::vector<const void*>& b) {
+  std::vector<CoarseInput> in;
+  for (const void* x : X) in.push_back(CoarseInput{x});
+  apply16_group(G, p, k, in, out, -1.0, &b, 1.0);
 }
 
 // cg16 for every member: e = Iter(A_k, rhs, e0) on level k.
@@ -661,61 +693,57 @@ void cg16_group(const std::vector<GM>& G, int k, bool e0_zero, int nsteps) {
   if (G.empty()) return;
   const int p = G[0].w->p, vp = vprec(p);
   auto N = [&](const GM& m) { return m.h->level_size(k); };
-  std::vector<const void*> X(G.size());
-  std::vector<void*> Y(G.size());
-  if (e0_zero) {
+  if (nsteps <= 0) {
+    if (!e0_zero) return;
     MemberSection zero(G);
     for (const GM& m : G) launch_zero(*m.h, vp, m.w->et[k], N(m) * NR);
     zero.end();
+    return;
   }
-  if (nsteps <= 0) return;
+  std::vector<void*> Y(G.size());
   if (!e0_zero) {
+    std::vector<const void*> X, b;
     for (size_t i = 0; i < G.size(); ++i) {
-      X[i] = G[i].w->et[k];
-      Y[i] = G[i].w->q;
+      X.push_back(G[i].w->et[k]);
+      b.push_back(G[i].w->r[k]);
+      Y[i] = G[i].w->s;
     }
-    apply16_group(G, p, k, X, Y);
+    residual16_group(G, p, k, X, Y, b);
   }
+  std::vector<int> ngp(G.size()), ndp(G.size());
+  std::vector<const void*> dir(G.size());
+  std::vector<CoarseInput> X(G.size());
+  int cur = 0;
   MemberSection init(G);
-  for (const GM& m : G) {
-    H2& h = *m.h;
-    Work16& w = *m.w;
-    const int64_t nf = N(m) * NR;
-    launch_copy(h, vp, w.r[k], w.s, nf);
-    if (!e0_zero) launch_axpby(h, vp, nf, -1.0, w.q, 1.0, w.s);
-    if (w.smoother == 1) {
-      launch_bj_apply16(h, p, k, w.s, w.z);
-      launch_copy(h, vp, w.z, w.pv, nf);
-      launch_dot16(h, vp, N(m), w.s, w.z, w.gpart(0));
-    } else {
-      launch_copy(h, vp, w.s, w.pv, nf);
-      launch_dot16(h, vp, N(m), w.s, w.s, w.gpart(0));
-    }
+  for (size_t i = 0; i < G.size(); ++i) {
+    Work16& w = *G[i].w;
+    ngp[i] = cg16_begin(*G[i].h, w, k, e0_zero ? w.r[k] : w.s, cur);
+    dir[i] = cg16_direction(*G[i].h, w, k, nsteps);
+    Y[i] = w.q;
   }
   init.end();
-  int cur = 0;
   for (int it = 0; it < nsteps; ++it) {
-    for (size_t i = 0; i < G.size(); ++i) {
-      X[i] = G[i].w->pv;
-      Y[i] = G[i].w->q;
-    }
-    apply16_group(G, p, k, X, Y);
-    MemberSection step(G);
-    for (const GM& m : G) {
-      H2& h = *m.h;
-      Work16& w = *m.w;
-      const int64_t n = N(m);
-      void* e = w.et[k];
-      launch_dot16(h, vp, n, w.pv, w.q, w.dpart());
-      if (w.smoother == 1) {
-        launch_cg_update16(h, vp, n, e, w.pv, w.s, w.q, w.gpart(cur), w.dpart(), w.scratch());
-        launch_bj_apply16(h, p, k, w.s, w.z);
-        launch_dot16(h, vp, n, w.s, w.z, w.gpart(1 - cur));
-        if (it + 1 < nsteps) launch_cg_pupdate16(h, vp, n, w.pv, w.z, w.gpart(cur), w.gpart(1 - cur));
-      } else {
-        launch_cg_update16(h, vp, n, e, w.pv, w.s, w.q, w.gpart(cur), w.dpart(), w.gpart(1 - cur));
-        if (it + 1 < nsteps) launch_cg_pupdate16(h, vp, n, w.pv, w.s, w.gpart(cur), w.gpart(1 - cur));
+    if (k == 1 && it > 0) {
+      MemberSection pup(G);
+      for (size_t i = 0; i < G.size(); ++i) {
+        Work16& w = *G[i].w;
+        launch_cg_pupdate16(*G[i].h, vp, N(G[i]), w.pv, cg16_z(w), w.gpart(1 - cur), w.gpart(cur), ngp[i]);
       }
+      pup.end();
+    }
+    for (size_t i = 0; i < G.size(); ++i)
+      X[i] = k >= 2 ? cg16_input(*G[i].h, *G[i].w, k, it, cur, ngp[i]) : CoarseInput{dir[i]};
+    apply16_group(G, p, k, X, Y, 1.0, nullptr, 0.0, k >= 2 ? &ndp : nullptr);
+    MemberSection step(G);
+    for (size_t i = 0; i < G.size(); ++i) {
+      H2& h = *G[i].h;
+      Work16& w = *G[i].w;
+      if (k == 1) {
+        launch_dot16(h, vp, N(G[i]), dir[i], w.q, w.dpart());
+        ndp[i] = parts16(N(G[i]));
+      }
+      cg16_update(h, w, k, w.et[k], e0_zero && it == 0, dir[i], cur, ngp[i], ndp[i]);
+      if (w.smoother != 1) ngp[i] = parts16(N(G[i]));
     }
     step.end();
     cur = 1 - cur;
@@ -738,21 +766,16 @@ void mg16_group(const std::vector<GM>& all, int k, int kind, int n_f, int n_c) {
   const int p = G[0].w->p, vp = vprec(p);
   const int nk = k == 1 ? n_f : n_c;
   cg16_group(G, k, true, nk);
-  std::vector<const void*> X(G.size());
-  std::vector<void*> Y(G.size());
-  for (size_t i = 0; i < G.size(); ++i) {
-    X[i] = G[i].w->et[k];
-    Y[i] = G[i].w->tmp;
-  }
-  apply16_group(G, p, k, X, Y);
-  MemberSection restrict_(G);
+  std::vector<const void*> X, b;
+  std::vector<void*> Y;
   for (const GM& m : G) {
-    H2& h = *m.h;
-    Work16& w = *m.w;
-    launch_axpby(h, vp, h.level_size(k) * NR, 1.0, w.r[k], -1.0, w.tmp);
-    if (k == 1) launch_leaf_up16(h, p, w.tmp, w.r[k + 1]);
-    else launch_transfer_up16(h, p, h.level_depth(k) - 1, w.tmp, w.r[k + 1]);
+    X.push_back(m.w->et[k]);
+    Y.push_back(m.w->tmp);
+    b.push_back(m.w->r[k]);
   }
+  residual16_group(G, p, k, X, Y, b);
+  MemberSection restrict_(G);
+  for (const GM& m : G) launch_restrict16(*m.h, p, k, m.w->tmp, m.w->r[k + 1]);
   restrict_.end();
   mg16_group(G, k + 1, kind, n_f, n_c);
   if (kind != CYCLE_V) {
@@ -760,7 +783,7 @@ void mg16_group(const std::vector<GM>& all, int k, int kind, int n_f, int n_c) {
     for (const GM& m : G)
       if (k + 1 < m.h->levels) sub.push_back(m);
     if (!sub.empty()) {
-      std::vector<const void*> X1(sub.size());
+      std::vector<const void*> X1(sub.size()), b1(sub.size());
       std::vector<void*> Y1(sub.size());
       MemberSection save(sub);
       for (size_t i = 0; i < sub.size(); ++i) {
@@ -768,13 +791,14 @@ void mg16_group(const std::vector<GM>& all, int k, int kind, int n_f, int n_c) {
         Work16& w = *sub[i].w;
         launch_copy(h, vp, w.et[k + 1], w.ec[k + 1], h.level_size(k + 1) * NR);
         X1[i] = w.et[k + 1];
+        b1[i] = w.r[k + 1];
         Y1[i] = w.tmp;
       }
       save.end();
-      apply16_group(sub, p, k + 1, X1, Y1);
+      residual16_group(sub, p, k + 1, X1, Y1, b1);
       MemberSection res(sub);
       for (const GM& m : sub)
-        launch_axpby(*m.h, vp, m.h->level_size(k + 1) * NR, -1.0, m.w->tmp, 1.0, m.w->r[k + 1]);
+        launch_copy(*m.h, vp, m.w->tmp, m.w->r[k + 1], m.h->level_size(k + 1) * NR);
       res.end();
       mg16_group(sub, k + 1, kind == CYCLE_F ? CYCLE_V : CYCLE_W, n_f, n_c);
       MemberSection add(sub);
@@ -784,12 +808,7 @@ void mg16_group(const std::vector<GM>& all, int k, int kind, int n_f, int n_c) {
     }
   }
   MemberSection prolong(G);
-  for (const GM& m : G) {
-    H2& h = *m.h;
-    Work16& w = *m.w;
-    if (k == 1) launch_leaf_down16(h, p, w.et[k + 1], nullptr, w.et[k], 1.0, w.et[k], 1.0);
-    else launch_transfer_down16(h, p, h.level_depth(k) - 1, w.et[k + 1], w.et[k], w.et[k]);
-  }
+  for (const GM& m : G) launch_prolong16(*m.h, p, k, m.w->et[k + 1], m.w->et[k]);
   prolong.end();
   cg16_group(G, k, false, nk);
 }
@@ -1182,11 +1201,12 @@ h2mg_status solve_group(int nprob, H2* const* hs, const int* nrhs, const double*
       if (act.empty()) break;
       // residuals R = B - A_H2 X of every active problem (FP64), one group product
       std::vector<GM> G64;
-      std::vector<const void*> X, add;
+      std::vector<const void*> add;
+      std::vector<CoarseInput> X;
       std::vector<void*> Y;
       for (int i : act) {
         G64.push_back(GM{hs[i], &bs[i]->w64});
-        X.push_back(bs[i]->xt);
+        X.push_back(CoarseInput{bs[i]->xt});
         Y.push_back(bs[i]->w64.r[1]);
         add.push_back(bs[i]->bt);
       }

@@ -105,6 +105,28 @@ __device__ inline void load_subtile(const Tb* __restrict__ tile, int lane, Tacc 
   }
 }
 
+// ---------------------------------------------------------------- matrix cores
+// 16 x 16 x 4 products: lane l supplies A[l % 16][l / 16] and
+// B[l / 16][l % 16]; accumulator element t of lane l is row row(t, l / 16),
+// column l % 16 (measured on gfx950).
+typedef double d4 __attribute__((ext_vector_type(4)));
+typedef float f4 __attribute__((ext_vector_type(4)));
+template <typename Tc> struct Mfma;
+template <> struct Mfma<double> {
+  typedef d4 acc_t;
+  __device__ static d4 mma(double a, double b, d4 c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+  }
+  __device__ static int row(int t, int q) { return 4 * t + q; }
+};
+template <> struct Mfma<float> {
+  typedef f4 acc_t;
+  __device__ static f4 mma(float a, float b, f4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+  }
+  __device__ static int row(int t, int q) { return 4 * q + t; }
+};
+
 // ---------------------------------------------------------------- kernels
 enum { KER_EXP = 0, KER_GAUSS = 1, KER_MATERN32 = 2, KER_LAPLACE = 3 };
 // deriv: the kernel itself, its derivative in the length scale at fixed r,

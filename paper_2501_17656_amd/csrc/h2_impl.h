@@ -447,15 +447,24 @@ void launch_leaf_up16(H2& h, int p, const void* x, void* xhat);
 // out = alpha * (Q yhat + near) + beta * add (tree order; yhat, near may be null)
 void launch_leaf_down16(H2& h, int p, const void* yhat, const void* near_y, void* out, double alpha,
                         const void* add, double beta);
-void launch_transfer_up16(H2& h, int p, int d, const void* xchild, void* xpar);
-void launch_transfer_down16(H2& h, int p, int d, const void* ypar, void* ychild, const void* addend);
+// Sweeps, as launch_sweep_up / launch_sweep_down (kernels_sweep16.hip); partial
+// sums are per column.
+void launch_sweep_up16(H2& h, int p, int d, void* xall, const void* src, const void* prev, const double* gold,
+                       const double* gnew, int np);
+int launch_sweep_down16(H2& h, int p, int d, void* yall, void* out, const void* add, const void* xd, double* dpart);
+// Level k to k + 1: xnext = U_k^T x; and back: e += U_k enext.
+void launch_restrict16(H2& h, int p, int k, const void* x, void* xnext);
+void launch_prolong16(H2& h, int p, int k, const void* enext, void* e);
 void launch_near_pad16(H2& h, int p, const void* x, void* xc);
 void launch_dot16(H2& h, int p, int64_t nrows, const void* x, const void* y, double* part);
-void launch_cg_update16(H2& h, int p, int64_t nrows, void* e, const void* pv, void* s, const void* q,
-                        const double* gpart, const double* dpart, double* gnew);
+void launch_cg_update16(H2& h, int p, int64_t nrows, void* e, bool e_zero, const void* pv, void* s, const void* q,
+                        const double* gpart, int ngp, const double* dpart, int ndp, double* gnew);
+void launch_copy_dot16(H2& h, int p, int64_t nrows, const void* src, void* s, double* part);
 void launch_cg_pupdate16(H2& h, int p, int64_t nrows, void* pv, const void* s, const double* gold,
-                         const double* gnew);
-void launch_bj_apply16(H2& h, int p, int k, const void* s, void* z);
+                         const double* gnew, int np);
+int launch_cg_step16_bj(H2& h, int p, int k, const void* src, void* e, bool e_zero, const void* pv, void* s,
+                        const void* q, void* z, const double* gpart, int ngp, const double* dpart, int ndp,
+                        double* gnew);
 void launch_chol_solve16(H2& h, const double* L, int64_t N, double* x);   // in place, FP64
 // e = X^T (X r), tmp: Nl x 16 doubles.
 void launch_inverse_solve16(H2& h, int p, const void* r, void* e, double* tmp);

@@ -36,8 +36,6 @@ namespace h2mg {
 
 namespace {
 
-typedef double d4 __attribute__((ext_vector_type(4)));
-typedef float f4 __attribute__((ext_vector_type(4)));
 constexpr int NR = MULTI_NR;           // columns of a block
 constexpr int NT = 256;
 
@@ -68,33 +66,12 @@ __device__ __forceinline__ int swz(int i) {
          ((__popc(i & m3) & 1) << 3) | ((__popc(i & m4) & 1) << 4) | ((__popc(i & m5) & 1) << 5);
 }
 
-template <typename Tc> struct Mfma;
-template <> struct Mfma<double> {
-  typedef d4 acc_t;
-  __device__ static d4 mma(double a, double b, d4 c) {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-  }
-  __device__ static int row(int t, int q) { return 4 * t + q; }
-};
-template <> struct Mfma<float> {
-  typedef f4 acc_t;
-  __device__ static f4 mma(float a, float b, f4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-  }
-  __device__ static int row(int t, int q) { return 4 * q + t; }
-};
-
-// Tile products of one launch.  MODE_LIST: blocks [0, nrt) run the
-// row-pass tasks (index, i0, i1) over rorder, blocks [nrt, nrt + nct) the
+// Tile products of one launch.  Blocks [0, nrt) run the row-pass tasks (index, i0, i1) over rorder, blocks [nrt, nrt + nct) the
 // column-pass tasks over corder.  Tile b joins block row brow[b] and block
 // column bcol[b]; the operand of a row task is the block of bcol[b], of a
 // column task that of brow[b], at x + index * rr * 16 (rr rows: the rank for
 // coupling tiles, 64 for near-field tiles; rows >= rr of the RP = 8T padded
 // tile are zero).  out[block] = the rr x 16 result.
-// MODE_UP (transfer to the parents): block s sums E_c^T x[c] over its two
-// children c = 2s, 2s+1 (tiles base + c).  MODE_DOWN (transfer to the
-// children): block c computes E_c x[c / 2] (tile base + c), plus addend[c]
-// when addend is not null.
 // A block has one wave per 16-row slab of the result (RP / 16 = T / 2
 // waves); all of them stage the tile into LDS together, then wave w runs the
 // matrix-core products of slab w.  The stage object fills LDS: load(b, regs)
@@ -102,57 +79,30 @@ template <> struct Mfma<float> {
 // writes entry (i, j) through put(i, j, value).  When Stage::PREFETCH, the
 // loads of the next tile are issued as soon as the current one is in LDS, so
 // they overlap its products; the operand rows are loaded before staging.
-// DUAL (MODE_LIST, no column-pass tasks): each staged off-diagonal tile also
+// DUAL (no column-pass tasks): each staged off-diagonal tile also
 // gives its transposed product B^T X_s, with X_s the task's block-row
 // operand, written as the rr x 16 column contribution of slot rslot[it]
 // (the tile's place among the off-diagonal tiles ordered by column) after
 // the nrt row partials: every tile is read once instead of twice.
-enum { MODE_LIST = 0, MODE_UP = 1, MODE_DOWN = 2 };
 
-template <int T, int MODE, typename Tv, typename Stage, bool DUAL = false>
+template <int T, typename Tv, typename Stage, bool DUAL = false>
 __device__ __forceinline__ void tgemm_body(int blk, const int* __restrict__ rtask, int nrt,
                                            const int* __restrict__ rorder,
                                            const int* __restrict__ ctask,
                                            const int* __restrict__ corder,
                                            const int* __restrict__ brow,
-                                           const int* __restrict__ bcol, int base, int rr,
-                                           const Tv* __restrict__ x, Tv* out_base, const Tv* addend,
+                                           const int* __restrict__ bcol, int rr,
+                                           const Tv* __restrict__ x, Tv* out_base,
                                            Tv* lds, const Stage& stage,
                                            const int* __restrict__ rslot = nullptr) {
   constexpr int RP = 8 * T, NKB = RP / 4;
   constexpr int EB = int(sizeof(Tv));
   using M = Mfma<Tv>;
-  bool tr;
-  int i0, i1;
-  const int* order = nullptr;
-  const int* other = nullptr;
-  int task_row = 0;
-  if constexpr (MODE == MODE_LIST) {
-    tr = blk >= nrt;
-    const int* task = tr ? ctask + 3 * (blk - nrt) : rtask + 3 * blk;
-    task_row = task[0];
-    order = tr ? corder : rorder;
-    other = tr ? brow : bcol;
-    i0 = task[1];
-    i1 = task[2];
-  } else if constexpr (MODE == MODE_UP) {
-    tr = true;
-    i0 = 2 * blk;
-    i1 = 2 * blk + 2;
-  } else {
-    tr = false;
-    i0 = blk;
-    i1 = blk + 1;
-  }
-  auto tile_of = [&](int it) {
-    if constexpr (MODE == MODE_LIST) return order[it];
-    else return base + it;
-  };
-  auto other_of = [&](int it, int b) {
-    if constexpr (MODE == MODE_LIST) return other[b];
-    else if constexpr (MODE == MODE_UP) return it;
-    else return it >> 1;
-  };
+  const bool tr = blk >= nrt;
+  const int* task = tr ? ctask + 3 * (blk - nrt) : rtask + 3 * blk;
+  const int task_row = task[0], i0 = task[1], i1 = task[2];
+  const int* order = tr ? corder : rorder;
+  const int* other = tr ? brow : bcol;
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63, p = l & 15, q = l >> 4;
   const int nkb = (rr + 3) >> 2;
   auto put = [&](int i, int j, Tv v) { lds[i * RP + (j ^ swz<RP, EB>(i))] = v; };
@@ -169,7 +119,7 @@ __device__ __forceinline__ void tgemm_body(int blk, const int* __restrict__ rtas
       else acc = M::mma(lds[slab * RP + (kr ^ slabsw)], xb, acc);
     };
     typename Stage::Regs regs;
-    int b = tile_of(i0);
+    int b = order[i0];
     if constexpr (Stage::PREFETCH) stage.load(b, regs);
     // DUAL: operand of the transposed products (the task's own block row)
     Tv xs[DUAL ? NKB : 1];
@@ -182,7 +132,7 @@ __device__ __forceinline__ void tgemm_body(int blk, const int* __restrict__ rtas
       }
     }
     for (int it = i0; it < i1; ++it) {
-      const int o = other_of(it, b);
+      const int o = other[b];
       const Tv* xo = x + int64_t(o) * rr * NR;
       Tv xr[NKB];
 #pragma unroll
@@ -194,7 +144,7 @@ __device__ __forceinline__ void tgemm_body(int blk, const int* __restrict__ rtas
       if constexpr (!Stage::PREFETCH) stage.load(b, regs);
       stage.store(b, regs, put);
       if (it + 1 < i1) {
-        b = tile_of(it + 1);
+        b = order[it + 1];
         if constexpr (Stage::PREFETCH) stage.load(b, regs);
       }
       __syncthreads();
@@ -223,11 +173,10 @@ __device__ __forceinline__ void tgemm_body(int blk, const int* __restrict__ rtas
   if (tr) run(std::integral_constant<bool, true>{});
   else run(std::integral_constant<bool, false>{});
   Tv* out = out_base + int64_t(blk) * rr * NR;
-  const Tv* add = addend ? addend + int64_t(blk) * rr * NR : nullptr;
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
     const int row = 16 * w + M::row(t, q);
-    if (row < rr) out[row * NR + p] = add ? acc[t] + add[row * NR + p] : acc[t];
+    if (row < rr) out[row * NR + p] = acc[t];
   }
 }
 
@@ -287,18 +236,8 @@ __global__ __launch_bounds__(32 * T) void k_tgemm(const int* __restrict__ rtask,
                                                   const Tv* __restrict__ x, Tv* __restrict__ partial,
                                                   const int* __restrict__ rslot) {
   __shared__ Tv lds[64 * T * T];
-  tgemm_body<T, MODE_LIST, Tv, StageStored<T, Te, Tv>, DUAL>(
-      blockIdx.x, rtask, nrt, rorder, ctask, corder, brow, bcol, 0, rr, x, partial,
-      static_cast<const Tv*>(nullptr), lds, StageStored<T, Te, Tv>{tiles}, rslot);
-}
-
-// Transfers between depth d + 1 (children, gids base + c) and depth d.
-template <int T, int MODE, typename Te, typename Tv>
-__global__ __launch_bounds__(32 * T) void k_transfer16(const Te* __restrict__ E, int base, int r,
-                                                       const Tv* __restrict__ x, Tv* out, const Tv* addend) {
-  __shared__ Tv lds[64 * T * T];
-  tgemm_body<T, MODE>(blockIdx.x, nullptr, 0, nullptr, nullptr, nullptr, nullptr, nullptr, base, r, x, out,
-                      addend, lds, StageStored<T, Te, Tv>{E});
+  tgemm_body<T, Tv, StageStored<T, Te, Tv>, DUAL>(
+      blockIdx.x, rtask, nrt, rorder, ctask, corder, brow, bcol, rr, x, partial, lds, StageStored<T, Te, Tv>{tiles}, rslot);
 }
 
 // Near-field tiles evaluated from the points: lane (a, b) of wave w
@@ -382,9 +321,8 @@ __global__ __launch_bounds__(256) void k_tgemm_eval(const int* __restrict__ rtas
                                                     const Tv* __restrict__ x, Tv* __restrict__ partial,
                                                     const int* __restrict__ rslot) {
   __shared__ Tv lds[64 * 64];
-  tgemm_body<8, MODE_LIST, Tv, StageEval<Tv, KIND, DERIV>, DUAL>(
-      blockIdx.x, rtask, nrt, rorder, ctask, corder, brow, bcol, 0, 64, x, partial,
-      static_cast<const Tv*>(nullptr), lds,
+  tgemm_body<8, Tv, StageEval<Tv, KIND, DERIV>, DUAL>(
+      blockIdx.x, rtask, nrt, rorder, ctask, corder, brow, bcol, 64, x, partial, lds,
       StageEval<Tv, KIND, DERIV>{brow, bcol, chunk_start, chunk_n, pts, dim, kp, ps}, rslot);
 }
 
@@ -399,9 +337,9 @@ __global__ __launch_bounds__(32 * T) void k_tgemm_group(TgemmGroup G) {
   int m = 0;
   while (m + 1 < G.n && G.start[m + 1] <= int(blockIdx.x)) ++m;
   const TgemmMember& M = G.m[m];
-  tgemm_body<T, MODE_LIST, Tv, StageStored<T, Te, Tv>, DUAL>(
-      int(blockIdx.x) - G.start[m], M.rtask, M.nrt, M.rorder, M.ctask, M.corder, M.brow, M.bcol, 0, M.rr,
-      static_cast<const Tv*>(M.x), static_cast<Tv*>(M.partial), static_cast<const Tv*>(nullptr), lds,
+  tgemm_body<T, Tv, StageStored<T, Te, Tv>, DUAL>(
+      int(blockIdx.x) - G.start[m], M.rtask, M.nrt, M.rorder, M.ctask, M.corder, M.brow, M.bcol, M.rr,
+      static_cast<const Tv*>(M.x), static_cast<Tv*>(M.partial), lds,
       StageStored<T, Te, Tv>{static_cast<const Te*>(M.tiles)}, M.rslot);
 }
 
@@ -411,9 +349,9 @@ __global__ __launch_bounds__(256) void k_tgemm_eval_group(TevalGroup G) {
   int m = 0;
   while (m + 1 < G.n && G.start[m + 1] <= int(blockIdx.x)) ++m;
   const TevalMember& M = G.m[m];
-  tgemm_body<8, MODE_LIST, Tv, StageEval<Tv, KIND, DERIV>, DUAL>(
-      int(blockIdx.x) - G.start[m], M.rtask, M.nrt, M.rorder, M.ctask, M.corder, M.brow, M.bcol, 0, 64,
-      static_cast<const Tv*>(M.x), static_cast<Tv*>(M.partial), static_cast<const Tv*>(nullptr), lds,
+  tgemm_body<8, Tv, StageEval<Tv, KIND, DERIV>, DUAL>(
+      int(blockIdx.x) - G.start[m], M.rtask, M.nrt, M.rorder, M.ctask, M.corder, M.brow, M.bcol, 64,
+      static_cast<const Tv*>(M.x), static_cast<Tv*>(M.partial), lds,
       StageEval<Tv, KIND, DERIV>{M.brow, M.bcol, M.chunk_start, M.chunk_n, M.pts, M.dim, M.kp, M.ps}, M.rslot);
 }
 
@@ -471,48 +409,6 @@ __global__ __launch_bounds__(NT) void k_scatter16(int64_t n, int nrhs, const int
   if (k < nrhs) user[perm[i] * ldu + k] = tree[idx];
 }
 
-// xhat[leaf] (r x 16) = Q_leaf^T x_leaf.
-template <typename Tq, typename Tv>
-__global__ __launch_bounds__(NT) void k_leaf_up16(const int* __restrict__ leaf_off,
-                                                  const Tq* __restrict__ Qr, int r,
-                                                  const Tv* __restrict__ x, Tv* __restrict__ xhat) {
-  const int leaf = blockIdx.x;
-  const int s0 = leaf_off[leaf], n = leaf_off[leaf + 1] - s0;
-  for (int e = threadIdx.x; e < r * NR; e += NT) {
-    const int j = e / NR, k = e % NR;
-    Tv v = Tv(0);
-    for (int i = 0; i < n; ++i)
-      v += ld_as<Tv, Tq>(Qr[int64_t(s0 + i) * r + j]) * x[int64_t(s0 + i) * NR + k];
-    xhat[(int64_t(leaf) * r + j) * NR + k] = v;
-  }
-}
-
-// out = alpha * (Q_leaf yhat_leaf + near) + beta * add over the rows of one
-// leaf per workgroup (tree order); yhat or near may be null, add is read
-// only when beta != 0 (it may alias out).
-template <typename Tq, typename Tv>
-__global__ __launch_bounds__(NT) void k_leaf_down16(const int* __restrict__ leaf_off,
-                                                    const Tq* __restrict__ Qr, int r,
-                                                    const Tv* __restrict__ yhat,
-                                                    const Tv* __restrict__ near_y,
-                                                    const int* __restrict__ chunk_base, Tv* out,
-                                                    double alpha, const Tv* add, double beta) {
-  const int leaf = blockIdx.x;
-  const int s0 = leaf_off[leaf], n = leaf_off[leaf + 1] - s0;
-  for (int e = threadIdx.x; e < n * NR; e += NT) {
-    const int i = e / NR, k = e % NR;
-    Tv v = Tv(0);
-    if (yhat)
-      for (int j = 0; j < r; ++j)
-        v += ld_as<Tv, Tq>(Qr[int64_t(s0 + i) * r + j]) * yhat[(int64_t(leaf) * r + j) * NR + k];
-    if (near_y) v += near_y[(int64_t(chunk_base[leaf]) * 64 + i) * NR + k];
-    const int64_t idx = int64_t(s0 + i) * NR + k;
-    Tv o = Tv(alpha) * v;
-    if (beta != 0.0) o += Tv(beta) * add[idx];
-    out[idx] = o;
-  }
-}
-
 // Chunk-padded block from the tree-order block (padding rows stay zero).
 template <typename Tv>
 __global__ __launch_bounds__(NT) void k_near_pad16(const int* __restrict__ leaf_off,
@@ -566,19 +462,18 @@ __global__ __launch_bounds__(NT) void k_dot16(int64_t nrows, const Tv* __restric
 }
 
 // Per column: alpha = gamma / delta (0 when gamma == 0; delta <= 0 with
-// gamma > 0 flags a non-SPD operator); e += alpha p; s -= alpha q; partials
-// of s.s.
+// gamma > 0 flags a non-SPD operator); e += alpha p (e = alpha p when e_zero);
+// s -= alpha q; partials of s.s.  p may be s.
 template <typename Tv>
-__global__ __launch_bounds__(NT) void k_cg_update16(int64_t nrows, Tv* __restrict__ e,
-                                                    const Tv* __restrict__ p, Tv* __restrict__ s,
-                                                    const Tv* __restrict__ q,
-                                                    const double* __restrict__ gpart,
-                                                    const double* __restrict__ dpart, int np,
+__global__ __launch_bounds__(NT) void k_cg_update16(int64_t nrows, Tv* __restrict__ e, bool e_zero, const Tv* p,
+                                                    Tv* s, const Tv* __restrict__ q,
+                                                    const double* __restrict__ gpart, int ngp,
+                                                    const double* __restrict__ dpart, int ndp,
                                                     double* __restrict__ gnew, int* __restrict__ flag) {
   __shared__ double red[NT];
   __shared__ double gam[NR], del[NR], alp[NR];
-  colsum16(gpart, np, gam, red);
-  colsum16(dpart, np, del, red);
+  colsum16(gpart, ngp, gam, red);
+  colsum16(dpart, ndp, del, red);
   if (threadIdx.x < NR) {
     double al = 0.0;
     if (gam[threadIdx.x] != 0.0) {
@@ -593,12 +488,28 @@ __global__ __launch_bounds__(NT) void k_cg_update16(int64_t nrows, Tv* __restric
   double acc = 0.0;
   for (int64_t i = int64_t(blockIdx.x) * 16 + g; i < nrows; i += int64_t(gridDim.x) * 16) {
     const int64_t idx = i * NR + k;
-    e[idx] += al * p[idx];
+    const Tv pi = p[idx];
+    e[idx] = e_zero ? al * pi : e[idx] + al * pi;
     const Tv sn = s[idx] - al * q[idx];
     s[idx] = sn;
     acc += double(sn) * double(sn);
   }
   colpart16(acc, red, gnew);
+}
+
+// s = src and the per-column partials of s.s.
+template <typename Tv>
+__global__ __launch_bounds__(NT) void k_copy_dot16(int64_t nrows, const Tv* __restrict__ src, Tv* __restrict__ s,
+                                                   double* __restrict__ part) {
+  __shared__ double red[NT];
+  const int k = threadIdx.x & 15, g = threadIdx.x >> 4;
+  double acc = 0.0;
+  for (int64_t i = int64_t(blockIdx.x) * 16 + g; i < nrows; i += int64_t(gridDim.x) * 16) {
+    const Tv v = src[i * NR + k];
+    s[i * NR + k] = v;
+    acc += double(v) * double(v);
+  }
+  colpart16(acc, red, part);
 }
 
 // Per column: beta = gamma_new / gamma_old (0 when gamma_old == 0); p = s + beta p.
@@ -616,28 +527,6 @@ __global__ __launch_bounds__(NT) void k_cg_pupdate16(int64_t nrows, Tv* __restri
   for (int64_t i = int64_t(blockIdx.x) * 16 + g; i < nrows; i += int64_t(gridDim.x) * 16) {
     const int64_t idx = i * NR + k;
     p[idx] = s[idx] + beta * p[idx];
-  }
-}
-
-// z_b = M_b^{-1} s_b for every diagonal block b (one workgroup per block,
-// at most 128 rows): rows [off[b], off[b+1]) when off is given, else
-// [b*stride, (b+1)*stride).  The stored inverses are symmetric.
-template <typename Tm, typename Tv>
-__global__ __launch_bounds__(NT) void k_bj_apply16(const int* __restrict__ off, int stride,
-                                                   const Tm* __restrict__ Minv, int ld,
-                                                   const Tv* __restrict__ s, Tv* __restrict__ z) {
-  __shared__ Tv sl[128 * NR];
-  const int b = blockIdx.x;
-  const int s0 = off ? off[b] : b * stride;
-  const int n = off ? off[b + 1] - s0 : stride;
-  for (int e = threadIdx.x; e < n * NR; e += NT) sl[e] = s[int64_t(s0) * NR + e];
-  __syncthreads();
-  const Tm* M = Minv + int64_t(b) * ld * ld;
-  for (int e = threadIdx.x; e < n * NR; e += NT) {
-    const int i = e / NR, k = e % NR;
-    Tv acc = Tv(0);
-    for (int j = 0; j < n; ++j) acc += Tv(M[int64_t(j) * ld + i]) * sl[j * NR + k];
-    z[int64_t(s0 + i) * NR + k] = acc;
   }
 }
 
@@ -934,58 +823,6 @@ void launch_scatter16(H2& h, int nrhs, const double* tree, double* user, int ldu
   check_launch("scatter16");
 }
 
-void launch_leaf_up16(H2& h, int p, const void* x, void* xhat) {
-  dispatch_prec(p, [&](auto tv, auto te) {
-    using Tv = decltype(tv);
-    using Te = decltype(te);
-    hipLaunchKernelGGL((k_leaf_up16<Te, Tv>), dim3(h.nleaf), dim3(NT), 0, h.stream, h.leaf_off,
-                       static_cast<const Te*>(h.prec[p].Qr), h.r, static_cast<const Tv*>(x),
-                       static_cast<Tv*>(xhat));
-  });
-  check_launch("leaf_up16");
-}
-
-void launch_leaf_down16(H2& h, int p, const void* yhat, const void* near_y, void* out, double alpha,
-                        const void* add, double beta) {
-  dispatch_prec(p, [&](auto tv, auto te) {
-    using Tv = decltype(tv);
-    using Te = decltype(te);
-    hipLaunchKernelGGL((k_leaf_down16<Te, Tv>), dim3(h.nleaf), dim3(NT), 0, h.stream, h.leaf_off,
-                       static_cast<const Te*>(h.prec[p].Qr), h.r, static_cast<const Tv*>(yhat),
-                       static_cast<const Tv*>(near_y), h.snear.chunk_base, static_cast<Tv*>(out), alpha,
-                       static_cast<const Tv*>(add), beta);
-  });
-  check_launch("leaf_down16");
-}
-
-void launch_transfer_up16(H2& h, int p, int d, const void* xchild, void* xpar) {
-  dispatch_T16(h.T, [&](auto Tc) {
-    constexpr int TT = decltype(Tc)::value;
-    dispatch_prec(p, [&](auto tv, auto te) {
-      using Tv = decltype(tv);
-      using Te = decltype(te);
-      hipLaunchKernelGGL((k_transfer16<TT, MODE_UP, Te, Tv>), dim3(1 << d), dim3(32 * TT), 0, h.stream,
-                         static_cast<const Te*>(h.prec[p].E), (1 << (d + 1)) - 1, h.r,
-                         static_cast<const Tv*>(xchild), static_cast<Tv*>(xpar), static_cast<const Tv*>(nullptr));
-    });
-  });
-  check_launch("transfer_up16");
-}
-
-void launch_transfer_down16(H2& h, int p, int d, const void* ypar, void* ychild, const void* addend) {
-  dispatch_T16(h.T, [&](auto Tc) {
-    constexpr int TT = decltype(Tc)::value;
-    dispatch_prec(p, [&](auto tv, auto te) {
-      using Tv = decltype(tv);
-      using Te = decltype(te);
-      hipLaunchKernelGGL((k_transfer16<TT, MODE_DOWN, Te, Tv>), dim3(2 << d), dim3(32 * TT), 0, h.stream,
-                         static_cast<const Te*>(h.prec[p].E), (1 << (d + 1)) - 1, h.r,
-                         static_cast<const Tv*>(ypar), static_cast<Tv*>(ychild), static_cast<const Tv*>(addend));
-    });
-  });
-  check_launch("transfer_down16");
-}
-
 void launch_near_pad16(H2& h, int p, const void* x, void* xc) {
   if (p == P64)
     hipLaunchKernelGGL(k_near_pad16<double>, dim3(h.nleaf), dim3(NT), 0, h.stream, h.leaf_off,
@@ -1007,51 +844,41 @@ void launch_dot16(H2& h, int p, int64_t nrows, const void* x, const void* y, dou
   check_launch("dot16");
 }
 
-void launch_cg_update16(H2& h, int p, int64_t nrows, void* e, const void* pv, void* s, const void* q,
-                        const double* gpart, const double* dpart, double* gnew) {
+void launch_cg_update16(H2& h, int p, int64_t nrows, void* e, bool e_zero, const void* pv, void* s, const void* q,
+                        const double* gpart, int ngp, const double* dpart, int ndp, double* gnew) {
   const int np = parts16(nrows);
   if (p == P64)
     hipLaunchKernelGGL(k_cg_update16<double>, dim3(np), dim3(NT), 0, h.stream, nrows, static_cast<double*>(e),
-                       static_cast<const double*>(pv), static_cast<double*>(s), static_cast<const double*>(q),
-                       gpart, dpart, np, gnew, h.flags);
+                       e_zero, static_cast<const double*>(pv), static_cast<double*>(s),
+                       static_cast<const double*>(q), gpart, ngp, dpart, ndp, gnew, h.flags);
   else
     hipLaunchKernelGGL(k_cg_update16<float>, dim3(np), dim3(NT), 0, h.stream, nrows, static_cast<float*>(e),
-                       static_cast<const float*>(pv), static_cast<float*>(s), static_cast<const float*>(q),
-                       gpart, dpart, np, gnew, h.flags);
+                       e_zero, static_cast<const float*>(pv), static_cast<float*>(s),
+                       static_cast<const float*>(q), gpart, ngp, dpart, ndp, gnew, h.flags);
   check_launch("cg_update16");
 }
 
-void launch_cg_pupdate16(H2& h, int p, int64_t nrows, void* pv, const void* s, const double* gold,
-                         const double* gnew) {
-  const int np = parts16(nrows);
+void launch_copy_dot16(H2& h, int p, int64_t nrows, const void* src, void* s, double* part) {
+  const dim3 g(parts16(nrows)), b(NT);
   if (p == P64)
-    hipLaunchKernelGGL(k_cg_pupdate16<double>, dim3(np), dim3(NT), 0, h.stream, nrows, static_cast<double*>(pv),
-                       static_cast<const double*>(s), gold, gnew, np);
+    hipLaunchKernelGGL(k_copy_dot16<double>, g, b, 0, h.stream, nrows, static_cast<const double*>(src),
+                       static_cast<double*>(s), part);
   else
-    hipLaunchKernelGGL(k_cg_pupdate16<float>, dim3(np), dim3(NT), 0, h.stream, nrows, static_cast<float*>(pv),
-                       static_cast<const float*>(s), gold, gnew, np);
-  check_launch("cg_pupdate16");
+    hipLaunchKernelGGL(k_copy_dot16<float>, g, b, 0, h.stream, nrows, static_cast<const float*>(src),
+                       static_cast<float*>(s), part);
+  check_launch("copy_dot16");
 }
 
-void launch_bj_apply16(H2& h, int p, int k, const void* s, void* z) {
-  const bool fine = k == 1;
-  const int d = h.level_depth(k);
-  const int nb = fine ? h.nleaf : (1 << d);
-  const int* off = fine ? h.leaf_off : nullptr;
-  const int ld = fine ? h.bj_ld : h.r;
-  const size_t eb = p == P64 ? 8 : 4;
-  const char* base = static_cast<const char*>(fine ? h.bj_fine[p == P64 ? P64 : P32]
-                                                   : h.bj_coarse[p == P64 ? P64 : P32]);
-  if (!fine) base += size_t((1 << d) - 1) * h.r * h.r * eb;
+void launch_cg_pupdate16(H2& h, int p, int64_t nrows, void* pv, const void* s, const double* gold,
+                         const double* gnew, int np) {
+  const dim3 g(parts16(nrows)), b(NT);
   if (p == P64)
-    hipLaunchKernelGGL((k_bj_apply16<double, double>), dim3(nb), dim3(NT), 0, h.stream, off, h.r,
-                       reinterpret_cast<const double*>(base), ld, static_cast<const double*>(s),
-                       static_cast<double*>(z));
+    hipLaunchKernelGGL(k_cg_pupdate16<double>, g, b, 0, h.stream, nrows, static_cast<double*>(pv),
+                       static_cast<const double*>(s), gold, gnew, np);
   else
-    hipLaunchKernelGGL((k_bj_apply16<float, float>), dim3(nb), dim3(NT), 0, h.stream, off, h.r,
-                       reinterpret_cast<const float*>(base), ld, static_cast<const float*>(s),
-                       static_cast<float*>(z));
-  check_launch("bj_apply16");
+    hipLaunchKernelGGL(k_cg_pupdate16<float>, g, b, 0, h.stream, nrows, static_cast<float*>(pv),
+                       static_cast<const float*>(s), gold, gnew, np);
+  check_launch("cg_pupdate16");
 }
 
 void launch_inverse_solve16(H2& h, int p, const void* r, void* e, double* tmp) {

@@ -29,8 +29,6 @@ namespace {
 
 constexpr int NT = 256;   // threads per workgroup of the setup kernels
 
-typedef double d4 __attribute__((ext_vector_type(4)));
-
 __device__ double block_sum(double v, double* red) {
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
