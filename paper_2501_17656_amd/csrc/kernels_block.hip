@@ -73,17 +73,32 @@ __device__ __forceinline__ int swz(int i) {
 // coupling tiles, 64 for near-field tiles; rows >= rr of the RP = 8T padded
 // tile are zero).  out[block] = the rr x 16 result.
 // A block has one wave per 16-row slab of the result (RP / 16 = T / 2
-// waves); all of them stage the tile into LDS together, then wave w runs the
-// matrix-core products of slab w.  The stage object fills LDS: load(b, regs)
-// issues this thread's share of the tile's global loads, store(b, regs, put)
-// writes entry (i, j) through put(i, j, value).  When Stage::PREFETCH, the
-// loads of the next tile are issued as soon as the current one is in LDS, so
-// they overlap its products; the operand rows are loaded before staging.
+// waves); all of them stage the tile and its operand rows into LDS together,
+// then wave w runs the matrix-core products of slab w.  The stage object fills
+// LDS: load(b, regs) issues this thread's share of the tile's global loads,
+// store(b, regs, put) writes entry (i, j) through put(i, j, value); rows(b,
+// regs) and cols(b, regs) bound the entries that are not zero.  The loads of
+// the next tile and of its operand are issued as soon as the current ones are
+// in LDS, so they overlap its products.
 // DUAL (no column-pass tasks): each staged off-diagonal tile also
 // gives its transposed product B^T X_s, with X_s the task's block-row
 // operand, written as the rr x 16 column contribution of slot rslot[it]
 // (the tile's place among the off-diagonal tiles ordered by column) after
 // the nrt row partials: every tile is read once instead of twice.
+// The operands were held in registers before, a copy per wave (64 of them for
+// a 64 x 64 FP64 tile, the block-row operand another 64): in LDS a workgroup
+// reads them from the L2 once instead of four times, and three workgroups fit
+// on a compute unit instead of two.
+// 16 FP64 products of 66k points (rank 64, near field evaluated) went from 2114
+// to 2012 us, 5 of 20k points from 1321 to 803 us, a 16-column solve of 16k
+// points from 122 to 117 ms.
+template <int T, typename Tv>
+struct TgemmLds {
+  static constexpr int RP = 8 * T;
+  Tv tile[RP * RP];
+  Tv xo[RP * NR];                      // operand of the row (or column) pass
+  Tv xs[RP * NR];                      // DUAL: operand of the transposed products
+};
 
 template <int T, typename Tv, typename Stage, bool DUAL = false>
 __device__ __forceinline__ void tgemm_body(int blk, const int* __restrict__ rtask, int nrt,
@@ -93,9 +108,10 @@ __device__ __forceinline__ void tgemm_body(int blk, const int* __restrict__ rtas
                                            const int* __restrict__ brow,
                                            const int* __restrict__ bcol, int rr,
                                            const Tv* __restrict__ x, Tv* out_base,
-                                           Tv* lds, const Stage& stage,
+                                           TgemmLds<T, Tv>& lds, const Stage& stage,
                                            const int* __restrict__ rslot = nullptr) {
-  constexpr int RP = 8 * T, NKB = RP / 4;
+  constexpr int RP = 8 * T, NKB = RP / 4, NTH = 32 * T;
+  constexpr int NX = RP * NR / NTH;    // operand entries per thread
   constexpr int EB = int(sizeof(Tv));
   using M = Mfma<Tv>;
   const bool tr = blk >= nrt;
@@ -103,63 +119,76 @@ __device__ __forceinline__ void tgemm_body(int blk, const int* __restrict__ rtas
   const int task_row = task[0], i0 = task[1], i1 = task[2];
   const int* order = tr ? corder : rorder;
   const int* other = tr ? brow : bcol;
-  const int w = threadIdx.x >> 6, l = threadIdx.x & 63, p = l & 15, q = l >> 4;
-  const int nkb = (rr + 3) >> 2;
-  auto put = [&](int i, int j, Tv v) { lds[i * RP + (j ^ swz<RP, EB>(i))] = v; };
+  const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, p = l & 15, q = l >> 4;
+  auto put = [&](int i, int j, Tv v) { lds.tile[i * RP + (j ^ swz<RP, EB>(i))] = v; };
   typename M::acc_t acc = typename M::acc_t{Tv(0), Tv(0), Tv(0), Tv(0)};
   const int slab = 16 * w + p;          // this lane's result row (row pass) / column (transposed)
+  const int slabsw = swz<RP, EB>(slab);
+  auto load_x = [&](int block, Tv (&r)[NX]) {
+    const Tv* xo = x + int64_t(block) * rr * NR;
+#pragma unroll
+    for (int k = 0; k < NX; ++k) {
+      const int e = tid + NTH * k;
+      r[k] = e < rr * NR ? xo[e] : Tv(0);
+    }
+  };
+  auto store_x = [&](Tv* dst, const Tv (&r)[NX]) {
+#pragma unroll
+    for (int k = 0; k < NX; ++k) dst[tid + NTH * k] = r[k];
+  };
+  // c plus the products of nk k-steps of the tile (TR: of its transpose) with
+  // operand xl, four at a time (what lies beyond is zero): without a branch
+  // when that is all of them, so that LDS reads run ahead of the matrix cores
+  auto products = [&](auto trc, int nk, const Tv* xl, typename M::acc_t c) {
+    constexpr bool TR = decltype(trc)::value;
+    auto four = [&](int kb0) {
+#pragma unroll
+      for (int kb = kb0; kb < kb0 + 4; ++kb) {
+        const int kr = 4 * kb + q;
+        const Tv t = TR ? lds.tile[kr * RP + (slab ^ swz<RP, EB>(kr))] : lds.tile[slab * RP + (kr ^ slabsw)];
+        c = M::mma(t, xl[kr * NR + p], c);
+      }
+    };
+    if (nk > NKB - 4) {
+#pragma unroll
+      for (int g = 0; g < NKB; g += 4) four(g);
+    } else {
+#pragma unroll
+      for (int g = 0; g < NKB - 4; g += 4)
+        if (g < nk) four(g);
+    }
+    return c;
+  };
   // The pass (row or transposed) is uniform per block; each has its own loop
   // with the LDS addressing fixed at compile time.
   auto run = [&](auto trc) {
     constexpr bool TR = decltype(trc)::value;
-    const int slabsw = swz<RP, EB>(slab);
-    auto mma_step = [&](int kb, Tv xb) {
-      const int kr = 4 * kb + q;
-      if constexpr (TR) acc = M::mma(lds[kr * RP + (slab ^ swz<RP, EB>(kr))], xb, acc);
-      else acc = M::mma(lds[slab * RP + (kr ^ slabsw)], xb, acc);
-    };
     typename Stage::Regs regs;
-    int b = order[i0];
-    if constexpr (Stage::PREFETCH) stage.load(b, regs);
-    // DUAL: operand of the transposed products (the task's own block row)
-    Tv xs[DUAL ? NKB : 1];
+    Tv xr[NX];
     if constexpr (DUAL) {
-      const Tv* xso = x + int64_t(task_row) * rr * NR;
-#pragma unroll
-      for (int kb = 0; kb < NKB; ++kb) {
-        const int kr = 4 * kb + q;
-        xs[kb] = kr < rr ? xso[kr * NR + p] : Tv(0);
-      }
+      load_x(task_row, xr);
+      store_x(lds.xs, xr);
     }
+    int b = order[i0];
+    stage.load(b, regs);
+    load_x(other[b], xr);
     for (int it = i0; it < i1; ++it) {
-      const int o = other[b];
-      const Tv* xo = x + int64_t(o) * rr * NR;
-      Tv xr[NKB];
-#pragma unroll
-      for (int kb = 0; kb < NKB; ++kb) {
-        const int kr = 4 * kb + q;
-        xr[kb] = kr < rr ? xo[kr * NR + p] : Tv(0);
-      }
-      __syncthreads();                 // every wave's operand reads of the previous tile are done
-      if constexpr (!Stage::PREFETCH) stage.load(b, regs);
+      __syncthreads();                 // every wave's reads of the previous tile are done
+      const int nrow = stage.rows(b, regs, rr), ncol = stage.cols(b, regs, rr);
       stage.store(b, regs, put);
+      store_x(lds.xo, xr);
       if (it + 1 < i1) {
         b = order[it + 1];
-        if constexpr (Stage::PREFETCH) stage.load(b, regs);
+        stage.load(b, regs);
+        load_x(other[b], xr);
       }
       __syncthreads();
-#pragma unroll
-      for (int kb = 0; kb < NKB; ++kb)
-        if (kb < nkb) mma_step(kb, xr[kb]);
+      acc = products(trc, ((TR ? nrow : ncol) + 3) >> 2, lds.xo, acc);
       if constexpr (DUAL && !TR) {
         const int slot = rslot[it];
         if (slot >= 0) {
-          typename M::acc_t at = typename M::acc_t{Tv(0), Tv(0), Tv(0), Tv(0)};
-#pragma unroll
-          for (int kb = 0; kb < NKB; ++kb) {
-            const int kr = 4 * kb + q;
-            if (kb < nkb) at = M::mma(lds[kr * RP + (slab ^ swz<RP, EB>(kr))], xs[kb], at);
-          }
+          const typename M::acc_t at = products(std::integral_constant<bool, true>{}, (nrow + 3) >> 2, lds.xs,
+                                                typename M::acc_t{Tv(0), Tv(0), Tv(0), Tv(0)});
           Tv* oc = out_base + int64_t(nrt + slot) * rr * NR;
 #pragma unroll
           for (int t = 0; t < 4; ++t) {
@@ -188,7 +217,6 @@ template <int T, typename Te, typename Tv>
 struct StageStored {
   static constexpr int W = T / 2;
   static constexpr int K = tile_K<Te>(T), NCH = T * T / K, NPW = NCH / W;
-  static constexpr bool PREFETCH = true;
   static_assert(NCH % W == 0, "chunks must split evenly over the waves");
   union Chunk {
     u32x4 q4;
@@ -223,6 +251,8 @@ struct StageStored {
         put(T * a + el / T, T * bb + el % T, ld_as<Tv, Te>(R.c[cc].e[k]));
       }
   }
+  __device__ __forceinline__ int rows(int, const Regs&, int rr) const { return rr; }
+  __device__ __forceinline__ int cols(int, const Regs&, int rr) const { return rr; }
 };
 
 template <int T, typename Te, typename Tv, bool DUAL>
@@ -235,18 +265,24 @@ __global__ __launch_bounds__(32 * T) void k_tgemm(const int* __restrict__ rtask,
                                                   const int* __restrict__ bcol, int rr,
                                                   const Tv* __restrict__ x, Tv* __restrict__ partial,
                                                   const int* __restrict__ rslot) {
-  __shared__ Tv lds[64 * T * T];
+  __shared__ TgemmLds<T, Tv> lds;
   tgemm_body<T, Tv, StageStored<T, Te, Tv>, DUAL>(
       blockIdx.x, rtask, nrt, rorder, ctask, corder, brow, bcol, rr, x, partial, lds, StageStored<T, Te, Tv>{tiles}, rslot);
 }
 
-// Near-field tiles evaluated from the points: lane (a, b) of wave w
-// evaluates rows 8a + 2w, 8a + 2w + 1 and columns 8b .. 8b+7 of the 64 x 64
-// tile (4 waves).
+// Near-field tiles evaluated from the points, 4 waves: lane j holds the point
+// of column j, wave w takes rows w, w + 4, ... of the row chunk, whose points
+// are the same for the whole wave (scalar loads).  Rows beyond the chunk are
+// not evaluated; rows and columns beyond it are zero.  Each lane evaluating
+// 2 x 8 entries held eight column points and needed 264 registers with its
+// products, one wave per SIMD.
 template <typename Tv, int KIND, int DERIV>
 struct StageEval {
-  static constexpr bool PREFETCH = false;
-  struct Regs {};
+  struct Regs {
+    double pc[3];
+    double sc;
+    int rs, nr, cs, nc;
+  };
   const int* brow;
   const int* bcol;
   const int* chunk_start;
@@ -255,50 +291,42 @@ struct StageEval {
   int dim;
   KernelParams kp;
   PointScale ps;
-  __device__ __forceinline__ void load(int, Regs&) const {}
-  template <typename Put>
-  __device__ __forceinline__ void store(int b, const Regs&, Put& put) const {
-    const int w = threadIdx.x >> 6, l = threadIdx.x & 63, a = l >> 3, bb = l & 7;
-    const Tv inv_l = Tv(kp.inv_l), inv_2l2 = Tv(kp.inv_2l2);
-    const int rs = chunk_start[brow[b]], nr = chunk_n[brow[b]];
-    const int cs = chunk_start[bcol[b]], nc = chunk_n[bcol[b]];
-    double pc[8][3];
+  __device__ __forceinline__ void load(int b, Regs& R) const {
+    const int j = threadIdx.x & 63;
+    R.rs = chunk_start[brow[b]];
+    R.nr = chunk_n[brow[b]];
+    R.cs = chunk_start[bcol[b]];
+    R.nc = chunk_n[bcol[b]];
+    const int64_t g = R.cs + min(j, R.nc - 1);
 #pragma unroll
-    for (int v = 0; v < 8; ++v) {
-      const int j = 8 * bb + v;
-#pragma unroll
-      for (int d = 0; d < 3; ++d) pc[v][d] = (j < nc && d < dim) ? pts[int64_t(cs + j) * dim + d] : 0.0;
-    }
-#pragma unroll
-    for (int uu = 0; uu < 2; ++uu) {
-      const int i = 8 * a + 2 * w + uu;
-      const bool rowok = i < nr;
-      double pr[3];
-#pragma unroll
-      for (int d = 0; d < 3; ++d) pr[d] = (rowok && d < dim) ? pts[int64_t(rs + i) * dim + d] : 0.0;
-      const int64_t gi = int64_t(rs) + i;
-#pragma unroll
-      for (int v = 0; v < 8; ++v) {
-        const int j = 8 * bb + v;
-        Tv e = Tv(0);
-        if (rowok && j < nc) {
-          // coordinate differences in FP64 (no cancellation), their squares
-          // in the vector precision
-          Tv r2 = Tv(0);
-#pragma unroll
-          for (int d = 0; d < 3; ++d) {
-            const Tv dx = Tv(pr[d] - pc[v][d]);
-            r2 += dx * dx;
-          }
-          const int64_t gj = int64_t(cs) + j;
-          e = kernel_fixed<KIND, DERIV, Tv>(inv_l, inv_2l2, r2);
-          if (ps.s) e *= Tv(ps.s[gi] * ps.s[gj]);
-          if (gi == gj) e += Tv(ps.d ? ps.d[gi] : kp.shift);
-        }
-        put(i, j, e);
-      }
-    }
+    for (int d = 0; d < 3; ++d) R.pc[d] = d < dim ? pts[g * dim + d] : 0.0;
+    R.sc = ps.s ? ps.s[g] : 1.0;
   }
+  template <typename Put>
+  __device__ __forceinline__ void store(int, const Regs& R, Put& put) const {
+    const int w = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6)), j = threadIdx.x & 63;
+    const Tv inv_l = Tv(kp.inv_l), inv_2l2 = Tv(kp.inv_2l2);
+    const bool colok = j < R.nc;
+#pragma unroll 4
+    for (int i = w; i < R.nr; i += 4) {
+      const int64_t gi = int64_t(R.rs) + i;
+      // coordinate differences in FP64 (no cancellation), their squares in the
+      // vector precision
+      Tv r2 = Tv(0);
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        const Tv dx = Tv((d < dim ? pts[gi * dim + d] : 0.0) - R.pc[d]);
+        r2 += dx * dx;
+      }
+      Tv e = kernel_fixed<KIND, DERIV, Tv>(inv_l, inv_2l2, r2);
+      if (ps.s) e *= Tv(ps.s[gi] * R.sc);
+      if (R.rs == R.cs && i == j) e += Tv(ps.d ? ps.d[gi] : kp.shift);
+      put(i, j, colok ? e : Tv(0));
+    }
+    for (int i = R.nr + w; i < 64; i += 4) put(i, j, Tv(0));
+  }
+  __device__ __forceinline__ int rows(int, const Regs& R, int) const { return R.nr; }
+  __device__ __forceinline__ int cols(int, const Regs& R, int) const { return R.nc; }
 };
 
 // Near-field tiles evaluated from the points instead of read: tile b is the
@@ -320,7 +348,7 @@ __global__ __launch_bounds__(256) void k_tgemm_eval(const int* __restrict__ rtas
                                                     KernelParams kp, PointScale ps,
                                                     const Tv* __restrict__ x, Tv* __restrict__ partial,
                                                     const int* __restrict__ rslot) {
-  __shared__ Tv lds[64 * 64];
+  __shared__ TgemmLds<8, Tv> lds;
   tgemm_body<8, Tv, StageEval<Tv, KIND, DERIV>, DUAL>(
       blockIdx.x, rtask, nrt, rorder, ctask, corder, brow, bcol, 64, x, partial, lds,
       StageEval<Tv, KIND, DERIV>{brow, bcol, chunk_start, chunk_n, pts, dim, kp, ps}, rslot);
@@ -333,7 +361,7 @@ __global__ __launch_bounds__(256) void k_tgemm_eval(const int* __restrict__ rtas
 // problem's partial sums are bit for bit those of a launch of its own.
 template <int T, typename Te, typename Tv, bool DUAL>
 __global__ __launch_bounds__(32 * T) void k_tgemm_group(TgemmGroup G) {
-  __shared__ Tv lds[64 * T * T];
+  __shared__ TgemmLds<T, Tv> lds;
   int m = 0;
   while (m + 1 < G.n && G.start[m + 1] <= int(blockIdx.x)) ++m;
   const TgemmMember& M = G.m[m];
@@ -345,7 +373,7 @@ __global__ __launch_bounds__(32 * T) void k_tgemm_group(TgemmGroup G) {
 
 template <typename Tv, int KIND, int DERIV, bool DUAL>
 __global__ __launch_bounds__(256) void k_tgemm_eval_group(TevalGroup G) {
-  __shared__ Tv lds[64 * 64];
+  __shared__ TgemmLds<8, Tv> lds;
   int m = 0;
   while (m + 1 < G.n && G.start[m + 1] <= int(blockIdx.x)) ++m;
   const TevalMember& M = G.m[m];
