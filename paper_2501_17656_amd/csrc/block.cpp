@@ -148,8 +148,8 @@ void free_set(H2& h, TileSet& ts) {
 void run_set(H2& h, int p, const TileSet& ts, bool near, const void* x, void* out) {
   BlockWork& w = h.blk16;
   const int rr = near ? 64 : h.r;
-  if (!near) launch_tgemm(h, p, h.T, ts, h.prec[p].blk, rr, x, w.partial);
-  else if (p == P64 && h.snear.ready) launch_tgemm(h, P64, 8, ts, h.snear.tiles, 64, x, w.partial);
+  if (!near) launch_tgemm(h, p, h.T, ts, h.prec[p].blk, tile_A(h.r, h.T), rr, x, w.partial);
+  else if (p == P64 && h.snear.ready) launch_tgemm(h, P64, 8, ts, h.snear.tiles, h.snear.lanes, 64, x, w.partial);
   else launch_tgemm_eval(h, p == P64 ? P64 : P32, ts, x, w.partial);
   launch_reduce16(h, p, ts, rr, w.partial, out);
 }
@@ -296,7 +296,7 @@ void apply_fine16(H2& h, int p, const void* X, void* out, double alpha, const vo
   if (h.d_top >= 0) {
     launch_leaf_up16(h, p, X, at_depth(w.xall, p, h.L, r));
     launch_sweep_up16(h, p, h.L, w.xall, nullptr, nullptr, nullptr, nullptr, 0);
-    launch_tgemm(h, p, h.T, w.fine, h.prec[p].blk, r, w.xall, w.partial);
+    launch_tgemm(h, p, h.T, w.fine, h.prec[p].blk, tile_A(r, h.T), r, w.xall, w.partial);
     launch_reduce16(h, p, w.fine, r, w.partial, w.yall);
     launch_sweep_down16(h, p, h.L, w.yall, at_depth(w.yall, p, h.L, r), nullptr, nullptr, nullptr);
     yhat = at_depth(w.yall, p, h.L, r);
@@ -311,10 +311,10 @@ void apply_fine16(H2& h, int p, const void* X, void* out, double alpha, const vo
   if (p == P64 && sn.ready) {
     int ev;
     h.time_begin(ev);
-    launch_tgemm(h, P64, 8, w.near, sn.tiles, 64, xc, w.partial);
+    launch_tgemm(h, P64, 8, w.near, sn.tiles, sn.lanes, 64, xc, w.partial);
     h.time_end(KS_NEAR16, ev, double(w.near.ntiles) * 4096.0 * sizeof(double));   // each stored tile once
   } else if (near_stored_for(h, p)) {
-    launch_tgemm(h, P32, 8, w.near, sn.tiles32, 64, xc, w.partial);
+    launch_tgemm(h, P32, 8, w.near, sn.tiles32, sn.lanes, 64, xc, w.partial);
   } else {
     launch_tgemm_eval(h, vprec(p), w.near, xc, w.partial);
   }
@@ -347,7 +347,7 @@ int apply_coarse16(H2& h, int p, int k, const CoarseInput& in, void* Y, const vo
   BlockWork& w = h.blk16;
   const int d = h.level_depth(k);
   launch_sweep_up16(h, p, d, w.xall, in.src, in.prev, in.gold, in.gnew, in.np);
-  launch_tgemm(h, p, h.T, w.coarse[d], h.prec[p].blk, h.r, w.xall, w.partial);
+  launch_tgemm(h, p, h.T, w.coarse[d], h.prec[p].blk, tile_A(h.r, h.T), h.r, w.xall, w.partial);
   return coarse_output16(h, p, k, Y, add, dpart);
 }
 
@@ -616,7 +616,7 @@ void apply16_group(const std::vector<GM>& G, int p, int k, const std::vector<Coa
       if (h.d_top < 0) continue;
       launch_leaf_up16(h, p, X[i].src, at_depth(w.xall, p, h.L, h.r));
       launch_sweep_up16(h, p, h.L, w.xall, nullptr, nullptr, nullptr, nullptr, 0);
-      tiles.push_back(GroupTiles{h.T, &w.fine, h.prec[p].blk, h.r, w.xall, w.partial});
+      tiles.push_back(GroupTiles{h.T, &w.fine, h.prec[p].blk, tile_A(h.r, h.T), h.r, w.xall, w.partial});
     }
     up.end();
     launch_tgemm_group(st, p, tiles);
@@ -644,8 +644,8 @@ void apply16_group(const std::vector<GM>& G, int p, int k, const std::vector<Coa
     for (size_t i = 0; i < G.size(); ++i) {
       H2& h = *G[i].h;
       BlockWork& w = h.blk16;
-      if (p == P64 && h.snear.ready) tiles.push_back(GroupTiles{8, &w.near, h.snear.tiles, 64, xc[i], w.partial});
-      else if (near_stored_for(h, p)) tiles32.push_back(GroupTiles{8, &w.near, h.snear.tiles32, 64, xc[i], w.partial});
+      if (p == P64 && h.snear.ready) tiles.push_back(GroupTiles{8, &w.near, h.snear.tiles, h.snear.lanes, 64, xc[i], w.partial});
+      else if (near_stored_for(h, p)) tiles32.push_back(GroupTiles{8, &w.near, h.snear.tiles32, h.snear.lanes, 64, xc[i], w.partial});
       else evals.push_back(GroupEval{&h, &w.near, xc[i], w.partial});
     }
     launch_tgemm_group(st, P64, tiles);
@@ -667,7 +667,7 @@ void apply16_group(const std::vector<GM>& G, int p, int k, const std::vector<Coa
     BlockWork& w = h.blk16;
     const int d = h.level_depth(k);
     launch_sweep_up16(h, p, d, w.xall, X[i].src, X[i].prev, X[i].gold, X[i].gnew, X[i].np);
-    tiles.push_back(GroupTiles{h.T, &w.coarse[d], h.prec[p].blk, h.r, w.xall, w.partial});
+    tiles.push_back(GroupTiles{h.T, &w.coarse[d], h.prec[p].blk, tile_A(h.r, h.T), h.r, w.xall, w.partial});
   }
   up.end();
   launch_tgemm_group(st, p, tiles);

@@ -6,8 +6,13 @@
 // b*T .. b*T+T-1 of the block, where T is the smallest power of two with
 // 8T >= r (entries beyond r are zero).  The T*T elements of a lane are cut
 // into chunks of K consecutive elements (K = min(16 bytes / element size,
-// T*T)), and chunk c of lane l lives at element offset (c*64 + l)*K, so a
-// wave reads each chunk row as one contiguous 64*K-element segment.
+// T*T)).  Only the A x A lanes with rows and columns below r take part, A =
+// ceil(r / T): chunk c of lane (a, b) lives at element offset
+// (c*A*A + a*A + b)*K, so a wave reads each chunk row as one contiguous
+// segment of A*A*K elements and the used part of a tile is contiguous too.
+// A tile takes tile_elems(T) elements whatever A is.  With all 64 lanes'
+// places stored, a block of rank 27 streamed 1024 entries for 729 (now 784),
+// and a 49-point near-field tile 4096 for 2401 (now 3136).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -66,31 +71,37 @@ template <typename Tb>
 __host__ __device__ constexpr int tile_K(int T) {
   return (16 / int(sizeof(Tb))) < T * T ? (16 / int(sizeof(Tb))) : T * T;
 }
+// Lanes per side that hold entries of a block of r rows.
+__host__ __device__ constexpr int tile_A(int r, int T) { return (r + T - 1) / T; }
 // Elements per stored tile.
 __host__ __device__ constexpr int64_t tile_elems(int T) { return 64LL * T * T; }
 
-// Element offset of block entry (i, j) inside a tile.
+// Element offset of block entry (i, j) inside a tile (i, j < A * T).
 template <typename Tb>
-__host__ __device__ inline int tile_offset(int i, int j, int T) {
+__host__ __device__ inline int tile_offset(int i, int j, int T, int A) {
   const int K = tile_K<Tb>(T);
   const int a = i / T, u = i % T, b = j / T, v = j % T;
-  const int lane = 8 * a + b;
   const int e = u * T + v;
-  return ((e / K) * 64 + lane) * K + (e % K);
+  return ((e / K) * A * A + A * a + b) * K + (e % K);
 }
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 // Load the T*T elements of this lane's sub-tile (row-major u*T + v) from
-// the tile starting at `tile`.  NT: non-temporal (streaming) loads, for
+// the tile starting at `tile`.  Lanes that hold no entries get those of
+// another one: their rows and columns meet zero coefficients, and their own
+// results are not used.  NT: non-temporal (streaming) loads, for
 // blocks read once per product so they do not evict reused vectors.
 template <int T, typename Tb, typename Tacc, bool NT = false>
-__device__ inline void load_subtile(const Tb* __restrict__ tile, int lane, Tacc (&B)[T * T]) {
+__device__ inline void load_subtile(const Tb* __restrict__ tile, int lane, int A, Tacc (&B)[T * T]) {
   constexpr int K = tile_K<Tb>(T);
   constexpr int NC = T * T / K;
+  // a uniform base and one 32-bit lane offset for all chunks (an address per
+  // chunk would take 64 registers)
+  const uint32_t off = uint32_t(A * min(lane >> 3, A - 1) + min(lane & 7, A - 1)) * uint32_t(K * sizeof(Tb));
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
-    const Tb* p = tile + (c * 64 + lane) * K;
+    const Tb* p = reinterpret_cast<const Tb*>(reinterpret_cast<const char*>(tile + c * A * A * K) + off);
     if constexpr (K * sizeof(Tb) == 16) {
       // one 16-byte load per chunk
       union { u32x4 q; Tb e[K]; } u;
@@ -103,6 +114,19 @@ __device__ inline void load_subtile(const Tb* __restrict__ tile, int lane, Tacc 
       for (int k = 0; k < K; ++k) B[c * K + k] = ld_as<Tacc, Tb>(p[k]);
     }
   }
+}
+
+// ---------------------------------------------------------------- near-field chunks
+// Position of point i of a leaf of n points in the chunk-padded order of the
+// stored near field: ceil(n / 64) chunks of equal length (the last one
+// shorter), each padded to 64, the first one at chunk `base`.
+__host__ __device__ inline int chunk_len(int n) {
+  const int k = (n + 63) / 64;
+  return (n + k - 1) / k;
+}
+__device__ inline int64_t chunk_pos(int base, int len, int i) {
+  const int c = (i >= len) + (i >= 2 * len) + (i >= 3 * len);   // at most 256 points
+  return int64_t(base + c) * 64 + (i - c * len);
 }
 
 // ---------------------------------------------------------------- matrix cores

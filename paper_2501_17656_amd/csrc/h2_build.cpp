@@ -100,7 +100,12 @@ T* upload(H2& h, const std::vector<T>& v) {
   return d;
 }
 
-constexpr int CHUNK = 16;      // stored blocks per GEMV task
+// Stored blocks per GEMV task (one wave): at most 16, fewer when there are not
+// enough blocks for 4096 tasks (four waves on each of the 1024 SIMDs).  With
+// 16 blocks throughout, the few hundred waves of a small level ran through
+// their blocks one latency after the other: a V-cycle of 4096 points (FP64, rank
+// 16) took 1222 us against 959 us now.
+int task_blocks(int64_t count) { return int(std::max<int64_t>(1, std::min<int64_t>(16, count / 4096))); }
 // Near-field tasks: with fewer waves than this the 1024 SIMDs (three resident
 // waves each) get less than four rounds, and the last, partly filled one
 // shows; beyond it a longer task saves row partials.
@@ -114,15 +119,16 @@ View make_view(H2& h, int d, int first, int count) {
   v.depth = d;
   const int nrows = 1 << d;
   const int gid0 = nrows - 1;
+  const int per_task = task_blocks(count);
   std::vector<int> rtp(nrows + 1, 0);
   for (int b = first; b < first + count;) {
     const int row = h.blk_row_h[b];
     int e = b;
     while (e < first + count && h.blk_row_h[e] == row) ++e;
-    for (int c = b; c < e; c += CHUNK) {
+    for (int c = b; c < e; c += per_task) {
       v.task.push_back(row);
       v.task.push_back(c);
-      v.task.push_back(std::min(e, c + CHUNK));
+      v.task.push_back(std::min(e, c + per_task));
       rtp[row - gid0 + 1]++;
     }
     b = e;
@@ -534,20 +540,23 @@ void plan_near(H2& h) {
   };
   const Plan& P = h.plan;
   const auto& off = P.offsets[h.L];
-  // chunks of at most 64 points per leaf
+  // chunks of at most 64 points per leaf, of equal length
   std::vector<int> cbase(h.nleaf + 1, 0), cstart, cn;
   sn.identity = true;
+  int longest = 1;
   for (int s = 0; s < h.nleaf; ++s) {
     const int s0 = int(off[s]), ns = int(off[s + 1] - off[s]);
-    const int k = (ns + 63) / 64;
+    const int k = (ns + 63) / 64, len = chunk_len(ns);
     if (ns % 64 != 0) sn.identity = false;
+    longest = std::max(longest, len);
     for (int q = 0; q < k; ++q) {
-      cstart.push_back(s0 + 64 * q);
-      cn.push_back(std::min(64, ns - 64 * q));
+      cstart.push_back(s0 + len * q);
+      cn.push_back(std::min(len, ns - len * q));
     }
     cbase[s + 1] = cbase[s] + k;
   }
   sn.nchunk = cbase[h.nleaf];
+  sn.lanes = (longest + 7) / 8;
   // tiles sorted by (row chunk, column chunk): row leaf, its row chunk,
   // then the leaf's close partners t >= s in order, then their chunks
   const auto& lst = P.near[h.L];
@@ -569,15 +578,16 @@ void plan_near(H2& h) {
     p = e;
   }
   sn.nblocks = int64_t(brow.size());
-  // tasks of at most CHUNK tiles of one row chunk; column slots by column
+  // tasks of tiles of one row chunk; column slots by column
+  const int per_task = task_blocks(sn.nblocks);
   std::vector<int> task, rtp(sn.nchunk + 1, 0), cptr(sn.nchunk + 1, 0), slot(brow.size(), -1);
   for (size_t b = 0; b < brow.size();) {
     size_t e = b;
     while (e < brow.size() && brow[e] == brow[b]) ++e;
-    for (size_t c = b; c < e; c += CHUNK) {
+    for (size_t c = b; c < e; c += size_t(per_task)) {
       task.push_back(brow[b]);
       task.push_back(int(c));
-      task.push_back(int(std::min(e, c + CHUNK)));
+      task.push_back(int(std::min(e, c + size_t(per_task))));
       rtp[brow[b] + 1]++;
     }
     b = e;

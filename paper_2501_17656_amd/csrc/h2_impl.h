@@ -92,20 +92,19 @@ struct NearField {
   int nsplit = 1;                      // waves per task, each with its own share of the chunks
 };
 
-// Stored near field (optional, FP64).  Every leaf is cut into chunks of at
-// most 64 consecutive points (chunk k of leaf s covers local positions
-// 64k .. 64k+63), and the close leaf pairs (s <= t) into 64 x 64 tiles
+// Stored near field (optional, FP64).  Every leaf is cut into ceil(n / 64)
+// chunks of consecutive points, of equal length (chunk_pos), and the close leaf pairs (s <= t) into 64 x 64 tiles
 // between chunks: all chunk pairs of an off-diagonal leaf pair, the upper
 // triangle of chunk pairs of a diagonal one (diagonal tiles stored whole,
 // with the shift on their diagonal).  Padding rows and columns are zero.
-// Vectors on chunks are padded: position i of leaf s is element
-// chunk_base[s] * 64 + i; when every leaf holds a multiple of 64 points this
-// is the tree order itself and no padding copy is made.
+// Vectors on chunks are padded to 64; when every leaf holds a multiple of 64
+// points this is the tree order itself and no padding copy is made.
 struct StoredNear {
   bool planned = false;                // chunks, tile lists and tasks built
   bool ready = false;                  // tiles stored
   bool identity = false;               // padded chunk order == tree order
   int nchunk = 0;
+  int lanes = 8;                       // lanes per side in use: ceil(longest chunk / 8)
   int ntasks = 0;
   int64_t nblocks = 0;
   int nslot = 0;
@@ -368,9 +367,9 @@ void launch_fine_reduce(H2& h, int p, const void* yhat, void* out, bool to_user,
 // Vectors of precision p: double for P64, float otherwise; tiles of the
 // operator precision.  Row-major blocks (entry (i, k) at i * 16 + k).
 int parts16(int64_t nrows);            // partial sums of a per-column dot
-// tp: precision of the tiles (FP64 tiles with FP64 vectors, FP32 or BF16
+// lanes: tile_A of the tiles; tp: their precision (FP64 tiles with FP64 vectors, FP32 or BF16
 // tiles with FP32 vectors).
-void launch_tgemm(H2& h, int tp, int T, const TileSet& ts, const void* tiles, int rr, const void* x,
+void launch_tgemm(H2& h, int tp, int T, const TileSet& ts, const void* tiles, int lanes, int rr, const void* x,
                   void* partial);
 // Near-field tile products with the tiles evaluated from the points (near
 // chunk plan of h.snear; vectors of precision p, chunk-padded).
@@ -393,6 +392,7 @@ struct TgemmMember {
   const int* rslot;
   int nrt;
   int rr;
+  int lanes;                           // tile_A of the tiles
 };
 struct TgemmGroup {
   int n;
@@ -429,6 +429,7 @@ struct GroupTiles {
   int T;
   const TileSet* ts;
   const void* tiles;
+  int lanes;
   int rr;
   const void* x;
   void* partial;

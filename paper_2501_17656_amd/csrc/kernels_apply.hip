@@ -46,7 +46,7 @@ __device__ __forceinline__ void bsr_gemv_wave(const int* __restrict__ tasks, int
                                               const int* __restrict__ blk_col,
                                               const int* __restrict__ blk_slot,
                                               const Tv* __restrict__ x, Tv* __restrict__ partial,
-                                              Tv* __restrict__ colpart, int r) {
+                                              Tv* __restrict__ colpart, int r, int A) {
   constexpr bool NTL = true;
   const int wave = __builtin_amdgcn_readfirstlane(int((blockIdx.x * blockDim.x + threadIdx.x) >> 6));
   if (wave >= ntasks) return;
@@ -64,7 +64,7 @@ __device__ __forceinline__ void bsr_gemv_wave(const int* __restrict__ tasks, int
   int col = blk_col[b0];
   for (int bi = b0; bi < b1; ++bi) {
     Tv B[T * T];
-    load_subtile<T, Tb, Tv, NTL>(blk + int64_t(bi) * tile_elems(T), lane, B);
+    load_subtile<T, Tb, Tv, NTL>(blk + int64_t(bi) * tile_elems(T), lane, A, B);
     const int col_next = bi + 1 < b1 ? blk_col[bi + 1] : col;
     Tv xt[T];
 #pragma unroll
@@ -118,7 +118,8 @@ __global__ __launch_bounds__(256) void k_bsr_gemv(const int* __restrict__ tasks,
                                                   const int* __restrict__ blk_slot,
                                                   const Tv* __restrict__ x, Tv* __restrict__ partial,
                                                   Tv* __restrict__ colpart, int r) {
-  bsr_gemv_wave<T, FULL, Tb, Tv>(tasks, ntasks, blk, blk_col, blk_slot, x, partial, colpart, r);
+  bsr_gemv_wave<T, FULL, Tb, Tv>(tasks, ntasks, blk, blk_col, blk_slot, x, partial, colpart, r,
+                                 FULL ? 8 : tile_A(r, T));
 }
 
 // Stored near field: 64 x 64 FP64 tiles between leaf chunks (same body; a
@@ -129,9 +130,9 @@ __global__ __launch_bounds__(256) void k_near_gemv(const int* __restrict__ tasks
                                                    const int* __restrict__ blk_slot,
                                                    const double* __restrict__ x,
                                                    double* __restrict__ partial,
-                                                   double* __restrict__ colpart) {
+                                                   double* __restrict__ colpart, int A) {
   bsr_gemv_wave<8, true, double, double>(tasks, ntasks, tiles, blk_col, blk_slot, x, partial,
-                                         colpart, 64);
+                                         colpart, 64, A);
 }
 
 // The same over FP32 copies of the tiles (close entries given by quadrature,
@@ -142,8 +143,8 @@ __global__ __launch_bounds__(256) void k_near_gemv32(const int* __restrict__ tas
                                                      const int* __restrict__ blk_slot,
                                                      const float* __restrict__ x,
                                                      float* __restrict__ partial,
-                                                     float* __restrict__ colpart) {
-  bsr_gemv_wave<8, true, float, float>(tasks, ntasks, tiles, blk_col, blk_slot, x, partial, colpart, 64);
+                                                     float* __restrict__ colpart, int A) {
+  bsr_gemv_wave<8, true, float, float>(tasks, ntasks, tiles, blk_col, blk_slot, x, partial, colpart, 64, A);
 }
 
 // Sources of one depth for the reduce: task partials of the row (contiguous
@@ -237,7 +238,7 @@ __global__ __launch_bounds__(256) void k_transfer_up(int nparents, int gidc0,
       xs[u] = i < r ? xchild[int64_t(c) * r + i] : zero<Tv>();
     }
     Tv B[T * T];
-    load_subtile<T, Tb, Tv>(E + int64_t(gidc0 + c) * tile_elems(T), lane, B);
+    load_subtile<T, Tb, Tv>(E + int64_t(gidc0 + c) * tile_elems(T), lane, tile_A(r, T), B);
 #pragma unroll
     for (int v = 0; v < T; ++v)
 #pragma unroll
@@ -279,7 +280,7 @@ __global__ __launch_bounds__(256) void k_transfer_down(int nchildren, int gidc0,
     xt[v] = j < r ? ypar[int64_t(s) * r + j] : zero<Tv>();
   }
   Tv B[T * T];
-  load_subtile<T, Tb, Tv>(E + int64_t(gidc0 + c) * tile_elems(T), lane, B);
+  load_subtile<T, Tb, Tv>(E + int64_t(gidc0 + c) * tile_elems(T), lane, tile_A(r, T), B);
   Tv acc[T];
 #pragma unroll
   for (int u = 0; u < T; ++u) {
@@ -351,7 +352,7 @@ __global__ __launch_bounds__(256) void k_fine_reduce(
 #pragma unroll 4
     for (int j = w * r / 4; j < (w + 1) * r / 4; ++j) v += ld_as<Tv, Tq>(Q[int64_t(j) * n]) * yh[j];
     if (near_y) {
-      if (w == 0) v += near_y[int64_t(chunk_base[leaf]) * 64 + i];
+      if (w == 0) v += near_y[chunk_pos(chunk_base[leaf], chunk_len(n), i)];
     } else {
       const int64_t t0 = row_task_ptr[leaf], nt = row_task_ptr[leaf + 1] - t0;
       const int64_t c0 = int64_t(col_ptr[leaf]) * nsplit, nc = int64_t(col_ptr[leaf + 1]) * nsplit - c0;
@@ -394,9 +395,8 @@ __global__ __launch_bounds__(256) void k_leaf_down(const int* __restrict__ leaf_
   }
 }
 
-// xc[chunk_base[leaf] * 64 + i] = x[leaf_off[leaf] + i]: the tree-order
-// vector in the chunk-padded layout of the stored near field (padding
-// entries are never written and stay zero).
+// The tree-order vector in the chunk-padded layout of the stored near field
+// (padding entries are never written and stay zero).
 template <typename Tv>
 __global__ __launch_bounds__(256) void k_near_pad(const int* __restrict__ leaf_off,
                                                   const int* __restrict__ chunk_base,
@@ -404,8 +404,8 @@ __global__ __launch_bounds__(256) void k_near_pad(const int* __restrict__ leaf_o
                                                   Tv* __restrict__ xc) {
   const int leaf = blockIdx.x;
   const int s0 = leaf_off[leaf], n = leaf_off[leaf + 1] - s0;
-  Tv* dst = xc + int64_t(chunk_base[leaf]) * 64;
-  for (int i = threadIdx.x; i < n; i += 256) dst[i] = x[s0 + i];
+  const int len = chunk_len(n);
+  for (int i = threadIdx.x; i < n; i += 256) xc[chunk_pos(chunk_base[leaf], len, i)] = x[s0 + i];
 }
 
 // ------------------------------------------------------------ dispatch helpers
@@ -579,9 +579,9 @@ void launch_near_stored(H2& h, int p, const void* xtree) {
     int ev;
     h.time_begin(ev);
     hipLaunchKernelGGL(k_near_gemv, dim3(grid_waves(sn.ntasks)), dim3(256), 0, h.stream, sn.task,
-                       sn.ntasks, sn.tiles, sn.blk_col, sn.blk_slot, xc, sn.partial, sn.colpart);
+                       sn.ntasks, sn.tiles, sn.blk_col, sn.blk_slot, xc, sn.partial, sn.colpart, sn.lanes);
     check_launch("near_gemv");
-    h.time_end(KS_NEARST64, ev, double(sn.nblocks) * 64.0 * 64.0 * sizeof(double));
+    h.time_end(KS_NEARST64, ev, double(sn.nblocks) * (64.0 * sn.lanes * sn.lanes) * sizeof(double));
     hipLaunchKernelGGL(k_reduce<double>, dim3(sn.nchunk), dim3(256), 0, h.stream, A,
                        sn.partial, sn.colpart, sn.yc, static_cast<double*>(nullptr), 64, 64);
   } else {
@@ -597,7 +597,7 @@ void launch_near_stored(H2& h, int p, const void* xtree) {
     float* part = reinterpret_cast<float*>(sn.partial);
     float* cpart = reinterpret_cast<float*>(sn.colpart);
     hipLaunchKernelGGL(k_near_gemv32, dim3(grid_waves(sn.ntasks)), dim3(256), 0, h.stream, sn.task,
-                       sn.ntasks, sn.tiles32, sn.blk_col, sn.blk_slot, xc, part, cpart);
+                       sn.ntasks, sn.tiles32, sn.blk_col, sn.blk_slot, xc, part, cpart, sn.lanes);
     check_launch("near_gemv32");
     hipLaunchKernelGGL(k_reduce<float>, dim3(sn.nchunk), dim3(256), 0, h.stream, A,
                        static_cast<const float*>(part), static_cast<const float*>(cpart),

@@ -209,10 +209,11 @@ __device__ __forceinline__ void tgemm_body(int blk, const int* __restrict__ rtas
   }
 }
 
-// Stored tiles: lane (a, b) of the 8 x 8 lane grid holds the T x T sub-block
-// of rows aT.., columns bT.. of the storage layout, cut into NCH chunks of 16
-// bytes; wave w of the block loads chunks w, w + W, ... (W = T / 2 waves),
-// so each thread keeps NCH / W chunks in registers while they are in flight.
+// Stored tiles: lane (a, b) of the A x A lanes in use holds the T x T
+// sub-block of rows aT.., columns bT.. of the storage layout, cut into NCH
+// chunks of 16 bytes; wave w of the block loads chunks w, w + W, ... (W = T /
+// 2 waves), so each thread keeps NCH / W chunks in registers while they are in
+// flight.  The other lanes hold zeros.
 template <int T, typename Te, typename Tv>
 struct StageStored {
   static constexpr int W = T / 2;
@@ -226,6 +227,7 @@ struct StageStored {
     Chunk c[NPW];
   };
   const Te* tiles;
+  int A;
   __device__ __forceinline__ static void load_chunk(const Te* src, Chunk& u) {
     if constexpr (K * sizeof(Te) == 16) {
       u.q4 = *reinterpret_cast<const u32x4*>(src);
@@ -237,8 +239,14 @@ struct StageStored {
   __device__ __forceinline__ void load(int b, Regs& R) const {
     const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
     const Te* tile = tiles + int64_t(b) * tile_elems(T);
+    const int a = l >> 3, bb = l & 7;
+    if (a >= A || bb >= A) {
 #pragma unroll
-    for (int cc = 0; cc < NPW; ++cc) load_chunk(tile + ((w + W * cc) * 64 + l) * K, R.c[cc]);
+      for (int cc = 0; cc < NPW; ++cc) R.c[cc].q4 = u32x4{0, 0, 0, 0};
+      return;
+    }
+#pragma unroll
+    for (int cc = 0; cc < NPW; ++cc) load_chunk(tile + ((w + W * cc) * A * A + A * a + bb) * K, R.c[cc]);
   }
   template <typename Put>
   __device__ __forceinline__ void store(int, const Regs& R, Put& put) const {
@@ -251,8 +259,8 @@ struct StageStored {
         put(T * a + el / T, T * bb + el % T, ld_as<Tv, Te>(R.c[cc].e[k]));
       }
   }
-  __device__ __forceinline__ int rows(int, const Regs&, int rr) const { return rr; }
-  __device__ __forceinline__ int cols(int, const Regs&, int rr) const { return rr; }
+  __device__ __forceinline__ int rows(int, const Regs&, int) const { return A * T; }
+  __device__ __forceinline__ int cols(int, const Regs&, int) const { return A * T; }
 };
 
 template <int T, typename Te, typename Tv, bool DUAL>
@@ -262,12 +270,12 @@ __global__ __launch_bounds__(32 * T) void k_tgemm(const int* __restrict__ rtask,
                                                   const int* __restrict__ corder,
                                                   const Te* __restrict__ tiles,
                                                   const int* __restrict__ brow,
-                                                  const int* __restrict__ bcol, int rr,
+                                                  const int* __restrict__ bcol, int rr, int A,
                                                   const Tv* __restrict__ x, Tv* __restrict__ partial,
                                                   const int* __restrict__ rslot) {
   __shared__ TgemmLds<T, Tv> lds;
   tgemm_body<T, Tv, StageStored<T, Te, Tv>, DUAL>(
-      blockIdx.x, rtask, nrt, rorder, ctask, corder, brow, bcol, rr, x, partial, lds, StageStored<T, Te, Tv>{tiles}, rslot);
+      blockIdx.x, rtask, nrt, rorder, ctask, corder, brow, bcol, rr, x, partial, lds, StageStored<T, Te, Tv>{tiles, A}, rslot);
 }
 
 // Near-field tiles evaluated from the points, 4 waves: lane j holds the point
@@ -368,7 +376,7 @@ __global__ __launch_bounds__(32 * T) void k_tgemm_group(TgemmGroup G) {
   tgemm_body<T, Tv, StageStored<T, Te, Tv>, DUAL>(
       int(blockIdx.x) - G.start[m], M.rtask, M.nrt, M.rorder, M.ctask, M.corder, M.brow, M.bcol, M.rr,
       static_cast<const Tv*>(M.x), static_cast<Tv*>(M.partial), lds,
-      StageStored<T, Te, Tv>{static_cast<const Te*>(M.tiles)}, M.rslot);
+      StageStored<T, Te, Tv>{static_cast<const Te*>(M.tiles), M.lanes}, M.rslot);
 }
 
 template <typename Tv, int KIND, int DERIV, bool DUAL>
@@ -444,8 +452,9 @@ __global__ __launch_bounds__(NT) void k_near_pad16(const int* __restrict__ leaf_
                                                    const Tv* __restrict__ x, Tv* __restrict__ xc) {
   const int leaf = blockIdx.x;
   const int s0 = leaf_off[leaf], n = leaf_off[leaf + 1] - s0;
-  Tv* dst = xc + int64_t(chunk_base[leaf]) * 64 * NR;
-  for (int e = threadIdx.x; e < n * NR; e += NT) dst[e] = x[int64_t(s0) * NR + e];
+  const int len = chunk_len(n);
+  for (int e = threadIdx.x; e < n * NR; e += NT)
+    xc[chunk_pos(chunk_base[leaf], len, e / NR) * NR + e % NR] = x[int64_t(s0) * NR + e];
 }
 
 // ------------------------------------------------------------ column dots and CG steps
@@ -699,7 +708,7 @@ void dispatch_dual(bool dual, F&& f) {
   else f(std::false_type{});
 }
 
-void launch_tgemm(H2& h, int tp, int T, const TileSet& ts, const void* tiles, int rr, const void* x,
+void launch_tgemm(H2& h, int tp, int T, const TileSet& ts, const void* tiles, int lanes, int rr, const void* x,
                   void* partial) {
   const int nb = ts.nrt + ts.nct;
   if (nb == 0) return;
@@ -712,7 +721,7 @@ void launch_tgemm(H2& h, int tp, int T, const TileSet& ts, const void* tiles, in
         constexpr bool D = decltype(dc)::value;
         hipLaunchKernelGGL((k_tgemm<TT, Te, Tv, D>), dim3(nb), dim3(32 * TT), 0, h.stream, ts.rtask, ts.nrt,
                            ts.rorder, ts.ctask, ts.corder, static_cast<const Te*>(tiles), ts.brow, ts.bcol,
-                           rr, static_cast<const Tv*>(x), static_cast<Tv*>(partial), ts.rslot);
+                           rr, lanes, static_cast<const Tv*>(x), static_cast<Tv*>(partial), ts.rslot);
       });
     });
   });
@@ -759,7 +768,7 @@ void launch_tgemm_group(hipStream_t st, int tp, const std::vector<GroupTiles>& i
           const GroupTiles& it = *sel[c0 + m];
           G.start[m] = int(total);
           G.m[m] = TgemmMember{it.ts->rtask, it.ts->rorder, it.ts->ctask, it.ts->corder, it.tiles, it.ts->brow,
-                               it.ts->bcol, it.x, it.partial, it.ts->rslot, it.ts->nrt, it.rr};
+                               it.ts->bcol, it.x, it.partial, it.ts->rslot, it.ts->nrt, it.rr, it.lanes};
           total += it.ts->nrt + it.ts->nct;
         }
         G.start[G.n] = int(total);

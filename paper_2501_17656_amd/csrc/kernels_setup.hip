@@ -259,7 +259,7 @@ __global__ __launch_bounds__(NT) void k_transfer_qr(
     double* Et = tile_ptr(E, gc, T);
     for (int idx = tid; idx < r * r; idx += NT) {
       const int i = idx / r, j = idx % r;
-      Et[tile_offset<double>(i, j, T)] = sgn[j] * A[size_t(j) * n + q * r + i];
+      Et[tile_offset<double>(i, j, T, tile_A(r, T))] = sgn[j] * A[size_t(j) * n + q * r + i];
     }
   }
 }
@@ -341,7 +341,7 @@ __device__ __forceinline__ void store_galerkin(const d4 (&out)[RS][RS], int r, i
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
         const int i = mu * 16 + 4 * t + lk, j = nu * 16 + li;
-        if (i < r && j < r) tile[tile_offset<double>(i, j, T)] = out[mu][nu][t];
+        if (i < r && j < r) tile[tile_offset<double>(i, j, T, tile_A(r, T))] = out[mu][nu][t];
       }
 }
 
@@ -479,16 +479,16 @@ struct UpperAcc {
     const int ii = i - a * RM, jj = j - b * RM;
     if (ii >= r || jj >= r) return 0.0;
     const int id = b ? p.id1 : p.id0;
-    return id >= 0 ? blk[int64_t(id) * tile_elems(T) + tile_offset<double>(ii, jj, T)]
-                   : blk[int64_t(-id - 1) * tile_elems(T) + tile_offset<double>(jj, ii, T)];
+    return id >= 0 ? blk[int64_t(id) * tile_elems(T) + tile_offset<double>(ii, jj, T, tile_A(r, T))]
+                   : blk[int64_t(-id - 1) * tile_elems(T) + tile_offset<double>(jj, ii, T, tile_A(r, T))];
   }
   __device__ __forceinline__ double qs(int i, int mu) const {
     const int a = i >= RM, ii = i - a * RM;
-    return ii < r && mu < r ? E[int64_t(gcs0 + a) * tile_elems(T) + tile_offset<double>(ii, mu, T)] : 0.0;
+    return ii < r && mu < r ? E[int64_t(gcs0 + a) * tile_elems(T) + tile_offset<double>(ii, mu, T, tile_A(r, T))] : 0.0;
   }
   __device__ __forceinline__ double qt(int j, int nu) const {
     const int b = j >= RM, jj = j - b * RM;
-    return jj < r && nu < r ? E[int64_t(gct0 + b) * tile_elems(T) + tile_offset<double>(jj, nu, T)] : 0.0;
+    return jj < r && nu < r ? E[int64_t(gct0 + b) * tile_elems(T) + tile_offset<double>(jj, nu, T, tile_A(r, T))] : 0.0;
   }
 };
 
@@ -520,7 +520,7 @@ __global__ __launch_bounds__(NT) void k_assemble_dense(
     // a diagonal block is symmetric up to rounding: its entries below the
     // diagonal are taken for both triangles (each place is written once)
     if (s == t && i < j) continue;
-    const double v = tl[tile_offset<double>(i, j, T)];
+    const double v = tl[tile_offset<double>(i, j, T, tile_A(r, T))];
     const int64_t gi = int64_t(s) * r + i, gj = int64_t(t) * r + j;
     A[gi + gj * lda] = v;
     A[gj + gi * lda] = v;
@@ -795,7 +795,7 @@ __global__ __launch_bounds__(NT) void k_bj_inv_coarse(int d, const int* __restri
   double* A = smem;
   double* fk = A + size_t(r) * r;
   const double* tl = blk + int64_t(diag_blk[c]) * tile_elems(T);
-  for (int idx = tid; idx < r * r; idx += NT) A[idx] = tl[tile_offset<double>(idx / r, idx % r, T)];
+  for (int idx = tid; idx < r * r; idx += NT) A[idx] = tl[tile_offset<double>(idx / r, idx % r, T, tile_A(r, T))];
   gauss_jordan_spd(A, r, fk, flag);
   double* o = out + int64_t((1 << d) - 1 + c) * r * r;
   for (int idx = tid; idx < r * r; idx += NT) o[idx] = A[idx];
@@ -808,9 +808,10 @@ __global__ __launch_bounds__(NT) void k_cast_tiles(const double* __restrict__ sr
   const int64_t id = id0 + blockIdx.x;
   const double* s = src + id * tile_elems(T);
   Td* d = dst + id * tile_elems(T);
+  const int A = tile_A(r, T);
   for (int idx = threadIdx.x; idx < r * r; idx += NT) {
     const int i = idx / r, j = idx % r;
-    d[tile_offset<Td>(i, j, T)] = Conv<Td>::from_f64(s[tile_offset<double>(i, j, T)]);
+    d[tile_offset<Td>(i, j, T, A)] = Conv<Td>::from_f64(s[tile_offset<double>(i, j, T, A)]);
   }
 }
 
@@ -832,12 +833,13 @@ __global__ __launch_bounds__(NT) void k_near_tiles(int64_t nblocks, const int* _
                                                    const int* __restrict__ chunk_start,
                                                    const int* __restrict__ chunk_n,
                                                    const double* __restrict__ pts, int dim,
-                                                   KernelParams kp, PointScale ps,
+                                                   KernelParams kp, PointScale ps, int A,
                                                    double* __restrict__ tiles) {
   const int64_t blk = (int64_t(blockIdx.x) * NT + threadIdx.x) >> 6;
   if (blk >= nblocks) return;
   const int lane = threadIdx.x & 63;
   const int a = lane >> 3, b = lane & 7;
+  if (a >= A || b >= A) return;        // lanes that hold no entries
   const int cs = blk_row[blk], ct = blk_col[blk];
   const int s0 = chunk_start[cs], ns = chunk_n[cs];
   const int t0 = chunk_start[ct], nt = chunk_n[ct];
@@ -870,7 +872,7 @@ __global__ __launch_bounds__(NT) void k_near_tiles(int64_t nblocks, const int* _
     double2 out;
     out.x = val[0];
     out.y = val[1];
-    *reinterpret_cast<double2*>(tile + (c * 64 + lane) * 2) = out;
+    *reinterpret_cast<double2*>(tile + (c * A * A + A * a + b) * 2) = out;
   }
 }
 
@@ -934,7 +936,7 @@ void launch_near_tiles(H2& h) {
   const int64_t groups = (sn.nblocks + 3) / 4;
   hipLaunchKernelGGL(k_near_tiles, dim3(unsigned(groups)), dim3(NT), 0, h.stream, sn.nblocks,
                      sn.blk_row, sn.blk_col, sn.chunk_start, sn.chunk_n, h.pts, h.dim, h.kp,
-                     near_scale(h), sn.tiles);
+                     near_scale(h), sn.lanes, sn.tiles);
   check_launch("near_tiles");
 }
 
@@ -942,7 +944,7 @@ void launch_cast_near_tiles(H2& h) {
   StoredNear& sn = h.snear;
   if (sn.nblocks == 0) return;
   hipLaunchKernelGGL(k_cast_tiles<float>, dim3(unsigned(sn.nblocks)), dim3(NT), 0, h.stream, sn.tiles,
-                     sn.tiles32, int64_t(0), 64, 8);
+                     sn.tiles32, int64_t(0), 8 * sn.lanes, 8);
   check_launch("cast_near_tiles");
 }
 

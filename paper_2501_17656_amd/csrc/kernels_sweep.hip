@@ -98,7 +98,7 @@ __global__ __launch_bounds__(SWEEP_NT<T>) void k_sweep_up(int q, int nlev, int r
       Tv B[U][T * T];
 #pragma unroll
       for (int k = 0; k < U; ++k)
-        if (c0 + k < nc) load_subtile<T, Tb, Tv>(E + (gc + c0 + k) * tile_elems(T), lane, B[k]);
+        if (c0 + k < nc) load_subtile<T, Tb, Tv>(E + (gc + c0 + k) * tile_elems(T), lane, tile_A(r, T), B[k]);
 #pragma unroll
       for (int k = 0; k < U; ++k) {
         if (c0 + k >= nc) break;
@@ -154,7 +154,7 @@ __global__ __launch_bounds__(SWEEP_NT<T>) void k_sweep_down(int q, int nlev, int
       Tv B[U][T * T];
 #pragma unroll
       for (int k = 0; k < U; ++k)
-        if (c0 + k < nc) load_subtile<T, Tb, Tv>(E + (gc + c0 + k) * tile_elems(T), lane, B[k]);
+        if (c0 + k < nc) load_subtile<T, Tb, Tv>(E + (gc + c0 + k) * tile_elems(T), lane, tile_A(r, T), B[k]);
 #pragma unroll
       for (int k = 0; k < U; ++k) {
         if (c0 + k >= nc) break;

@@ -101,7 +101,7 @@ __global__ __launch_bounds__(SWEEP_NT) void k_sweep_up16(int q0, int nlev, int r
     cur[i] = v;
   }
   __syncthreads();
-  const int ns = (r + 15) >> 4;
+  const int ns = (r + 15) >> 4, A = tile_A(r, T);
   for (int l = nlev; l > 0; --l) {
     const int64_t gc = (int64_t(1) << (q0 + l)) - 1 + (int64_t(blockIdx.x) << l);
     Tv* xp = l == 1 ? xroot + int64_t(blockIdx.x) * r * NR
@@ -117,7 +117,7 @@ __global__ __launch_bounds__(SWEEP_NT) void k_sweep_up16(int q0, int nlev, int r
 #pragma unroll
         for (int kb = 0; kb < NKB; ++kb) {
           const int k = 4 * kb + q;
-          a[kb] = k < r && j < r ? ld_as<Tv, Te>(tile[tile_offset<Te>(k, j, T)]) : Tv(0);
+          a[kb] = k < r && j < r ? ld_as<Tv, Te>(tile[tile_offset<Te>(k, j, T, A)]) : Tv(0);
         }
 #pragma unroll
         for (int kb = 0; kb < NKB; ++kb) {
@@ -158,7 +158,7 @@ __global__ __launch_bounds__(SWEEP_NT) void k_sweep_down16(int q0, int nlev, int
   const Tv* yq = root + int64_t(blockIdx.x) * r * NR;
   for (int i = tid; i < r * NR; i += SWEEP_NT) par[i] = yq[i];
   __syncthreads();
-  const int ns = (r + 15) >> 4;
+  const int ns = (r + 15) >> 4, A = tile_A(r, T);
   const int64_t off = blockIdx.x * (int64_t(r) * NR << nlev);
   double dacc = 0.0;
   for (int l = 1; l <= nlev; ++l) {
@@ -171,7 +171,7 @@ __global__ __launch_bounds__(SWEEP_NT) void k_sweep_down16(int q0, int nlev, int
 #pragma unroll
       for (int kb = 0; kb < NKB; ++kb) {
         const int k = 4 * kb + q;
-        a[kb] = k < r && i < r ? ld_as<Tv, Te>(tile[tile_offset<Te>(i, k, T)]) : Tv(0);
+        a[kb] = k < r && i < r ? ld_as<Tv, Te>(tile[tile_offset<Te>(i, k, T, A)]) : Tv(0);
       }
       typename M::acc_t acc;
 #pragma unroll
@@ -354,7 +354,7 @@ __global__ __launch_bounds__(256) void k_leaf_down16(const int* __restrict__ lea
     const int row = r0 + M::row(t, q);
     if (row >= n) continue;
     Tv v = acc[t];
-    if (near_y) v += near_y[(int64_t(chunk_base[leaf]) * 64 + row) * NR + p];
+    if (near_y) v += near_y[chunk_pos(chunk_base[leaf], chunk_len(n), row) * NR + p];
     const int64_t idx = int64_t(s0 + row) * NR + p;
     Tv o = Tv(alpha) * v;
     if (beta != 0.0) o += Tv(beta) * add[idx];

@@ -28,3 +28,19 @@ def test_levels_agree(m, leaf, leaves):
         low = g.level_apply(k + 1, x, precision="fp32")
         assert float((y - low).norm()) <= 1e-5 * float(y.norm()), k
     g.close()
+
+
+@pytest.mark.parametrize("m,leaf,leaves", [(9, 16, 512), (16, 20, 2048), (25, 32, 512), (33, 40, 512), (64, 70, 512),
+                                           (16, 20, 8)])
+def test_block_products_agree(m, leaf, leaves):
+    """The 16-column sweeps: a block's product against the single-vector product of its columns."""
+    n = leaf * leaves - leaves // 3
+    gen = torch.Generator(device="cuda").manual_seed(m + leaves)
+    pts = torch.rand((n, 1), dtype=torch.float64, device="cuda", generator=gen)
+    g = H2Matrix(pts, "exp", 0.05, 1.0, leaf, 0.7, m)
+    X = torch.randn((n, 5), dtype=torch.float64, device="cuda", generator=gen)
+    Y = g.matvec_multi(X)
+    for k in (0, 4):
+        y = g.matvec(X[:, k].contiguous())
+        assert float((Y[:, k] - y).norm()) <= 1e-13 * float(y.norm())
+    g.close()
