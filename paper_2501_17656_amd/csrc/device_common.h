@@ -187,8 +187,9 @@ template <typename T> constexpr T MIN_R2 = T(0);
 template <> inline constexpr double MIN_R2<double> = 1e-290;
 template <> inline constexpr float MIN_R2<float> = 1e-36f;
 
+template <bool MINED = false>
 __device__ inline double sqrt_nn(double x) {
-  x = __builtin_fmax(x, MIN_R2<double>);
+  if constexpr (!MINED) x = __builtin_fmax(x, MIN_R2<double>);
   const double y = __builtin_amdgcn_rsq(x);
   double g = x * y, h = 0.5 * y;
   const double e = __builtin_fma(-h, g, 0.5);
@@ -196,11 +197,14 @@ __device__ inline double sqrt_nn(double x) {
   h = __builtin_fma(h, e, h);
   return __builtin_fma(__builtin_fma(-g, g, x), h, g);
 }
+template <bool MINED = false>
 __device__ inline float sqrt_nn(float x) {
-  x = __builtin_fmaxf(x, MIN_R2<float>);
+  const bool small = !MINED && x < 1e-28f;       // the residual below would be subnormal
+  if constexpr (!MINED) x = __builtin_fmaxf(small ? x * 0x1p64f : x, MIN_R2<float>);
   const float y = __builtin_amdgcn_rsqf(x);
   const float g = x * y;
-  return __builtin_fmaf(__builtin_fmaf(-g, g, x), 0.5f * y, g);
+  const float s = __builtin_fmaf(__builtin_fmaf(-g, g, x), 0.5f * y, g);
+  return small ? s * 0x1p-32f : s;
 }
 __device__ inline double rsqrt_nn(double x) {
   double y = __builtin_amdgcn_rsq(x);
@@ -237,10 +241,13 @@ __device__ inline float raise_to(float w, float lo) { return __builtin_fmaxf(w, 
 
 // k (or its derivative) as a function of the squared distance (no shift),
 // for a kernel fixed at compile time.  The exponent is formed in base 2 with
-// one rounding of the constant and one of the product.
-template <int KIND, int DERIV, typename T>
+// one rounding of the constant and one of the product.  MINED: r2 is finite
+// and at least MIN_R2 (r = 0 included, so not for the kernels that ask for
+// r2 = 0), and the exponent above -2^30: nothing is raised.
+template <int KIND, int DERIV, typename T, bool MINED = false>
 __device__ inline T kernel_fixed(T inv_l, T inv_2l2, T r2) {
-  constexpr T LOG2E = T(1.4426950408889634), LN2 = T(0.6931471805599453), LOW = T(-1100);
+  auto raise = [](T w) { return MINED ? w : raise_to(w, T(-1100)); };
+  constexpr T LOG2E = T(1.4426950408889634), LN2 = T(0.6931471805599453);
   if constexpr (KIND == KER_LAPLACE) {
     // 1 / (4 pi r); 0 at r = 0 (the matrix supplies its own diagonal)
     return r2 == T(0) ? T(0) : T(0.07957747154594767) * rsqrt_nn(r2);
@@ -249,19 +256,19 @@ __device__ inline T kernel_fixed(T inv_l, T inv_2l2, T r2) {
     if (r2 == T(0)) return T(0);
   }
   if constexpr (KIND == KER_GAUSS) {
-    const T e = exp2_np(raise_to(r2 * (-inv_2l2 * LOG2E), LOW));
+    const T e = exp2_np(raise(r2 * (-inv_2l2 * LOG2E)));
     if constexpr (DERIV == DER_NONE) return e;
     else if constexpr (DERIV == DER_LENGTH) return r2 * (inv_l * inv_l * inv_l) * e;
     else return -inv_l * inv_l * e;
   } else if constexpr (KIND == KER_EXP) {
-    const T rr = sqrt_nn(r2);
-    const T e = exp2_np(raise_to(rr * (-inv_l * LOG2E), LOW));
+    const T rr = sqrt_nn<MINED>(r2);
+    const T e = exp2_np(raise(rr * (-inv_l * LOG2E)));
     if constexpr (DERIV == DER_NONE) return e;
     else if constexpr (DERIV == DER_LENGTH) return rr * (inv_l * inv_l) * e;
     else return -inv_l * e / rr;
   } else {
-    const T rr = sqrt_nn(r2);
-    const T w = raise_to(rr * (-inv_l * (T(1.7320508075688772) * LOG2E)), LOW);   // -z log2(e)
+    const T rr = sqrt_nn<MINED>(r2);
+    const T w = raise(rr * (-inv_l * (T(1.7320508075688772) * LOG2E)));   // -z log2(e)
     const T e = exp2_np(w);
     if constexpr (DERIV == DER_NONE) return (T(1) - w * LN2) * e;
     else if constexpr (DERIV == DER_LENGTH) return (w * w) * (LN2 * LN2 * inv_l) * e;

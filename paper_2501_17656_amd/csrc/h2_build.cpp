@@ -364,6 +364,11 @@ h2mg_status build_h2(const double* points_dev, int64_t n, int dim, const h2mg_ke
       nf.row_task_ptr = upload(h, rtp);
       nf.col_ptr = upload(h, cptr);
       nf.ld = (h.leaf_max + 7) / 8 * 8;
+      double diam2 = 0.0;
+      for (int a = 0; a < dim; ++a) diam2 += (P.hi[0][a] - P.lo[0][a]) * (P.hi[0][a] - P.lo[0][a]);
+      const double most = h.kp.kind == KER_GAUSS ? diam2 * h.kp.inv_2l2 : std::sqrt(3.0 * diam2) * h.kp.inv_l;
+      // log2(e) < 1.5; and MIN_R2 and the largest r^2 are within FP32's range
+      nf.mined = 1.5 * most < 536870912.0 && diam2 < 1e37 && h.kp.inv_l < 1e8;
       for (int p = 0; p < nf.npairs; ++p)
         h.near_evals += int64_t(loff[prow[p] + 1] - loff[prow[p]]) * (loff[pcol[p] + 1] - loff[pcol[p]]);
     }

@@ -70,9 +70,11 @@ struct NearIn {
   int ld, nsplit;
 };
 
-// Rows [rt, rt + nrow) of leaf sl (U = ceil(nrow / 8)) against the pairs
-// [p0, p1).  first: this wave has not written these pairs' column sums yet.
-template <int U, int DIM, typename Tv, int KIND, int DERIV>
+// Rows [rt, rt + nrow) of leaf sl (U >= nrow / 8) against the pairs [p0, p1).
+// first: this wave has not written these pairs' column sums yet.  MINED: the
+// squared distance starts at MIN_R2 (its first addition is an FMA, so that
+// costs nothing) and the kernel need not raise its arguments.
+template <int U, int DIM, bool MINED, typename Tv, int KIND, int DERIV>
 __device__ __forceinline__ void near_rows(const NearIn<Tv>& A, int task, int part, int sl, int p0, int p1, int rt,
                                           int nrow, bool first) {
   const int lane = threadIdx.x & 63;
@@ -132,9 +134,10 @@ __device__ __forceinline__ void near_rows(const NearIn<Tv>& A, int task, int par
 #pragma unroll
         for (int a = 0; a < DIM; ++a) {
           const double dx = pi[u][a] - pj[a];
-          r2 = a == 0 ? dx * dx : r2 + dx * dx;
+          if (a == 0) r2 = MINED ? __builtin_fma(dx, dx, double(MIN_R2<Tv>)) : dx * dx;
+          else r2 = __builtin_fma(dx, dx, r2);
         }
-        const Tv k = kernel_fixed<KIND, DERIV, Tv>(inv_l, inv_2l2, Tv(r2));
+        const Tv k = kernel_fixed<KIND, DERIV, Tv, MINED>(inv_l, inv_2l2, Tv(r2));
         racc[u] += k * xj;
         cacc += k * xi[u];
       }
@@ -163,7 +166,8 @@ __device__ __forceinline__ void near_rows(const NearIn<Tv>& A, int task, int par
 // own place, and a chunk beyond a shorter leaf's rows writes zeros.
 template <typename Tv, int KIND, int DERIV>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_near(const int* __restrict__ tasks, int ntasks, NearIn<Tv> A, int dim,
-                                              int chunk, int nchunk) {
+                                              int chunk, int nchunk, bool mined) {
+  constexpr bool MAY = KIND != KER_LAPLACE && DERIV != DER_RADIAL;   // no question about r = 0
   const int wave = __builtin_amdgcn_readfirstlane(int((blockIdx.x * blockDim.x + threadIdx.x) >> 6));
   if (wave >= ntasks * A.nsplit) return;
   const int task = wave / A.nsplit, part = wave % A.nsplit;
@@ -181,11 +185,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
     }
     auto run = [&](auto uc) {
       constexpr int U = decltype(uc)::value;
-      if (dim == 3) near_rows<U, 3, Tv, KIND, DERIV>(A, task, part, sl, p0, p1, rt, nrow, c == part);
-      else near_rows<U, 2, Tv, KIND, DERIV>(A, task, part, sl, p0, p1, rt, nrow, c == part);
+      if (dim == 3) near_rows<U, 3, MAY, Tv, KIND, DERIV>(A, task, part, sl, p0, p1, rt, nrow, c == part);
+      else near_rows<U, 2, MAY, Tv, KIND, DERIV>(A, task, part, sl, p0, p1, rt, nrow, c == part);
     };
-    if (dim == 1) {                    // points on a line: one loop for every length
-      near_rows<8, 1, Tv, KIND, DERIV>(A, task, part, sl, p0, p1, rt, nrow, c == part);
+    // points on a line, and distances beyond any use: one loop for every length
+    if (dim == 1) {
+      near_rows<8, 1, false, Tv, KIND, DERIV>(A, task, part, sl, p0, p1, rt, nrow, c == part);
+      continue;
+    }
+    if (MAY && !mined) {
+      if (dim == 3) near_rows<8, 3, false, Tv, KIND, DERIV>(A, task, part, sl, p0, p1, rt, nrow, c == part);
+      else near_rows<8, 2, false, Tv, KIND, DERIV>(A, task, part, sl, p0, p1, rt, nrow, c == part);
       continue;
     }
     switch ((nrow + 7) >> 3) {
@@ -218,7 +228,8 @@ void launch_near(H2& h, int p, const void* xtree) {
     const NearIn<Tv> A{nf.pair_col, nf.pair_slot, h.leaf_off, h.pts, h.scale, static_cast<const Tv*>(xtree),
                        reinterpret_cast<Tv*>(h.near_partial), reinterpret_cast<Tv*>(h.near_colpart), kp, nf.ld,
                        nf.nsplit};
-    hipLaunchKernelGGL((k_near<Tv, K, D>), g, b, 0, h.stream, nf.task, nf.ntasks, A, h.dim, nf.chunk, nf.nchunk);
+    hipLaunchKernelGGL((k_near<Tv, K, D>), g, b, 0, h.stream, nf.task, nf.ntasks, A, h.dim, nf.chunk, nf.nchunk,
+                       nf.mined);
   };
   dispatch_kernel(h.kp.kind, h.kp.deriv, [&](auto kc, auto dc) {
     if (p == P64) go(double{}, kc, dc);

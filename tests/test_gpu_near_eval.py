@@ -63,3 +63,21 @@ def test_near_fp32(n, leaf):
     want = dense_product(pts, x, "exp", 1.0)
     assert float((y - want).norm()) <= 16 * n * 2.0 ** -24 * float(x.norm()), float((y - want).norm())
     g.close()
+
+
+@pytest.mark.parametrize("dim,kernel", [(2, "exp"), (3, "matern32"), (3, "gauss")])
+@pytest.mark.parametrize("unit", [1.0, 1e10, 1e-16])
+def test_near_far_out(unit, dim, kernel):
+    """Distances of up to 1e10 length scales (no entry but the diagonal counts) and coordinates whose
+    squares leave FP32's normal range, in FP64 and FP32."""
+    n = 4 * 98
+    if kernel == "gauss" and unit < 1:
+        pytest.skip("1 / (2 l^2) is not an FP32 number")
+    rng = np.random.default_rng(n)
+    pts, x = torch.from_numpy(rng.random((n, dim))).cuda(), torch.from_numpy(rng.standard_normal(n)).cuda()
+    g = H2Matrix(unit * pts, kernel, ELL * min(unit, 1.0), 1.0, 128, 1e-9, 2)
+    g.setup(["fp64", "fp32"])
+    want = dense_product(max(unit, 1.0) * pts, x, kernel, 1.0)
+    for y, eps in ((g.matvec(x), 2.0 ** -53), (g.level_apply(1, x, precision="fp32"), 2.0 ** -24)):
+        assert float((y - want).norm()) <= 16 * n * eps * float(x.norm())
+    g.close()
