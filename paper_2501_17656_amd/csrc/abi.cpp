@@ -232,9 +232,7 @@ h2mg_status h2mg_matvec(h2mg_h2_t hh, const double* x, double* y, hipStream_t st
     if (!hh || !x || !y) return fail(H2MG_ERR_INVALID_ARG, "null argument");
     H2& h = *hh->h;
     h.stream = stream;
-    launch_gather(h, x, h.vtree);
-    apply_fine(h, P64, h.vtree, h.vtree2, 1.0, nullptr, 0.0);
-    launch_scatter(h, h.vtree2, y);
+    apply_fine_user(h, x, y);
     return check_stream_err(stream);
   });
 }
@@ -274,9 +272,7 @@ h2mg_status h2mg_level_apply(h2mg_h2_t hh, int32_t level, const double* x, doubl
     H2& h = *hh->h;
     h.stream = stream;
     if (level == 1) {
-      launch_gather(h, x, h.vtree);
-      apply_fine(h, P64, h.vtree, h.vtree2, 1.0, nullptr, 0.0);
-      launch_scatter(h, h.vtree2, y);
+      apply_fine_user(h, x, y);
       return check_stream_err(stream);
     }
     if (!h.mg_built) return fail(H2MG_ERR_STATE, "call h2mg_setup_mg before applying level %d", level);

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <stdexcept>
+#include <string>
 #include <vector>
 
 #include "h2_build.h"
@@ -22,16 +23,15 @@ inline const void* at_depth(const void* base, int p, int d, int r) {
   return static_cast<const char*>(base) + size_t((1 << d) - 1) * r * vbytes(p);
 }
 
-}  // namespace
-
-void apply_fine(H2& h, int p, const void* xt, void* out, double alpha, const void* add, double beta) {
+// Everything of a fine product behind the leaf upsweep (x_L in xall).
+void fine_from_leaves(H2& h, int p, const void* xt, void* out, bool to_user, double alpha, const void* add,
+                      double beta) {
   void* xall = h.xall;
   void* yall = h.yall;
   const int r = h.r;
   if (h.d_top >= 0) {
-    // upsweep: x_L = Q^T x, then x_d = E^T x_{d+1}
-    launch_leaf_up(h, p, xt, at_depth(xall, p, h.L, r));
-    launch_sweep_up(h, p, h.L, xall, nullptr, nullptr, nullptr, nullptr, 0);
+    // upsweep: x_d = E^T x_{d+1}
+    if (h.L > h.d_top) launch_sweep_up(h, p, h.L, xall, nullptr, nullptr, nullptr, nullptr, 0);
     // couplings of every depth in one launch, then one reduce for all depths
     launch_gemv(h, p, h.fine_launch, xall);
     std::vector<const View*> vs;
@@ -47,7 +47,22 @@ void apply_fine(H2& h, int p, const void* xt, void* out, double alpha, const voi
   // near field and leaf downsweep: y = D x + Q y_L
   if (near_stored_for(h, p)) launch_near_stored(h, p, xt);
   else launch_near(h, p, xt);
-  launch_fine_reduce(h, p, at_depth(yall, p, h.L, r), out, false, alpha, add, beta, xt);
+  launch_fine_reduce(h, p, at_depth(yall, p, h.L, r), out, to_user, alpha, add, beta, xt);
+}
+
+}  // namespace
+
+void apply_fine(H2& h, int p, const void* xt, void* out, double alpha, const void* add, double beta) {
+  if (h.d_top >= 0) launch_leaf_up(h, p, xt, at_depth(h.xall, p, h.L, h.r));
+  fine_from_leaves(h, p, xt, out, false, alpha, add, beta);
+}
+
+void apply_fine_user(H2& h, const double* x, double* y) {
+  if (h.d_top >= 0)
+    launch_leaf_up_gather(h, x, h.vtree, static_cast<double*>(at_depth(h.xall, P64, h.L, h.r)));
+  else
+    launch_gather(h, x, h.vtree);
+  fine_from_leaves(h, P64, h.vtree, y, true, 1.0, nullptr, 0.0);
 }
 
 void* level_input(H2& h, int p, int k) { return at_depth(h.xall, p, h.level_depth(k), h.r); }

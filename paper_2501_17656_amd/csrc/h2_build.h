@@ -42,6 +42,8 @@ h2mg_status quadratic_gradient(H2& h, H2* hl, H2* hg, const double* b, const dou
 // Fine level, tree order: out = alpha * A_H2 x + beta * add (add may be null).
 void apply_fine(H2& h, int p, const void* xt, void* out, double alpha, const void* add,
                 double beta);
+// y = A_H2 x, both in user order (FP64; y may be x).
+void apply_fine_user(H2& h, const double* x, double* y);
 // Level k >= 2 (depth L - k + 2), coefficient order: y = A_k x.
 void apply_coarse(H2& h, int p, int k, const void* x, void* y);
 // The input of a level's product as its upsweep forms it: src, or src + beta

@@ -345,6 +345,8 @@ void launch_sweep_up(H2& h, int p, int d, void* xall, const void* src, const voi
 // their number).  yall's depths above d are used up.
 int launch_sweep_down(H2& h, int p, int d, void* yall, void* out, const void* add, const void* xd, double* dpart);
 void launch_leaf_up(H2& h, int p, const void* xtree, void* xhat);
+// The same for a vector in user order, which it also writes in tree order.
+void launch_leaf_up_gather(H2& h, const double* xuser, double* xtree, double* xhat);
 void launch_near(H2& h, int p, const void* xtree);
 // Stored near field: snear.yc = D x over the chunk-padded layout, FP64
 // tiles and vectors (p = P64) or the FP32 tile copy with FP32 vectors.

@@ -303,23 +303,37 @@ __global__ __launch_bounds__(256) void k_transfer_down(int nchildren, int gidc0,
 }
 
 // ------------------------------------------------------------ leaf bases
-// xhat[leaf] = Q_leaf^T x_leaf; 4 waves split the leaf's rows.
+// xhat[leaf] = Q_leaf^T x_leaf; 256 / rp groups (rp: the power of two that
+// holds r) split the leaf's rows.  With perm, x is in user order and is
+// written to xtree in tree order as well.
 template <typename Tq, typename Tv>
 __global__ __launch_bounds__(256) void k_leaf_up(const int* __restrict__ leaf_off,
                                                  const Tq* __restrict__ Qr,
                                                  const Tv* __restrict__ x, Tv* __restrict__ xhat,
-                                                 int r) {
-  __shared__ Tv red[4][64];
-  const int leaf = blockIdx.x;
-  const int w = threadIdx.x >> 6, j = threadIdx.x & 63;
+                                                 int r, int rp, const int64_t* __restrict__ perm,
+                                                 Tv* __restrict__ xtree) {
+  __shared__ Tv red[256];
+  __shared__ Tv xl[256];
+  const int leaf = blockIdx.x, tid = threadIdx.x;
   const int s0 = leaf_off[leaf], n = leaf_off[leaf + 1] - s0;
-  Tv acc = zero<Tv>();
-  if (j < r)
-    for (int i = w; i < n; i += 4)
-      acc += ld_as<Tv, Tq>(Qr[int64_t(s0 + i) * r + j]) * x[s0 + i];
-  red[w][j] = acc;
+  if (tid < n) {                       // at most 256 points
+    const Tv v = perm ? x[perm[s0 + tid]] : x[s0 + tid];
+    xl[tid] = v;
+    if (perm) xtree[s0 + tid] = v;
+  }
   __syncthreads();
-  if (w == 0 && j < r) xhat[int64_t(leaf) * r + j] = (red[0][j] + red[1][j]) + (red[2][j] + red[3][j]);
+  const int j = tid & (rp - 1), g = tid / rp, ng = 256 / rp;
+  Tv acc = zero<Tv>();
+  if (j < r) {
+    const Tq* Q = Qr + int64_t(s0) * r + j;
+#pragma unroll 4
+    for (int i = g; i < n; i += ng) acc += ld_as<Tv, Tq>(Q[int64_t(i) * r]) * xl[i];
+  }
+  red[tid] = acc;
+  __syncthreads();
+  if (tid >= r) return;
+  for (int k = 1; k < ng; ++k) acc += red[k * rp + tid];
+  xhat[int64_t(leaf) * r + tid] = acc;
 }
 
 // ------------------------------------------------------------ fine output
@@ -541,16 +555,26 @@ void launch_leaf_up(H2& h, int p, const void* xtree, void* xhat) {
   if (p == P64)
     hipLaunchKernelGGL((k_leaf_up<double, double>), g, b, 0, h.stream, h.leaf_off,
                        static_cast<const double*>(h.prec[P64].Qr), static_cast<const double*>(xtree),
-                       static_cast<double*>(xhat), h.r);
+                       static_cast<double*>(xhat), h.r, 8 * h.T, static_cast<const int64_t*>(nullptr),
+                       static_cast<double*>(nullptr));
   else if (p == P32)
     hipLaunchKernelGGL((k_leaf_up<float, float>), g, b, 0, h.stream, h.leaf_off,
                        static_cast<const float*>(h.prec[P32].Qr), static_cast<const float*>(xtree),
-                       static_cast<float*>(xhat), h.r);
+                       static_cast<float*>(xhat), h.r, 8 * h.T, static_cast<const int64_t*>(nullptr),
+                       static_cast<float*>(nullptr));
   else
     hipLaunchKernelGGL((k_leaf_up<bf16, float>), g, b, 0, h.stream, h.leaf_off,
                        static_cast<const bf16*>(h.prec[P16].Qr), static_cast<const float*>(xtree),
-                       static_cast<float*>(xhat), h.r);
+                       static_cast<float*>(xhat), h.r, 8 * h.T, static_cast<const int64_t*>(nullptr),
+                       static_cast<float*>(nullptr));
   check_launch("leaf_up");
+}
+
+void launch_leaf_up_gather(H2& h, const double* xuser, double* xtree, double* xhat) {
+  hipLaunchKernelGGL((k_leaf_up<double, double>), dim3(h.nleaf), dim3(256), 0, h.stream, h.leaf_off,
+                     static_cast<const double*>(h.prec[P64].Qr), xuser, xhat, h.r, 8 * h.T,
+                     static_cast<const int64_t*>(h.perm), xtree);
+  check_launch("leaf_up_gather");
 }
 
 void launch_near_stored(H2& h, int p, const void* xtree) {
