@@ -746,15 +746,17 @@ h2mg_status setup_mg(H2& h, int precision_mask) {
         h.Nl = h.n;
         h.levels = 1;
       }
+      double* work = h.arena.make<double>(64 * 64);
       h.chol = h.arena.make<double>(size_t(h.Nl) * h.Nl);
       hip_check(hipMemsetAsync(h.chol, 0, size_t(h.Nl) * h.Nl * sizeof(double), h.stream), "memset");
       if (h.d_top >= 0) launch_assemble_dense(h, h.chol, h.Nl);
       else launch_assemble_kernel_dense(h, h.chol, h.Nl);
       hip_check(hipMemsetAsync(h.flags, 0, 4 * sizeof(int), h.stream), "memset");
-      launch_potrf(h, h.chol, h.Nl);
+      launch_potrf(h, h.chol, h.Nl, work);
       int flags[4];
       hip_check(hipMemcpyAsync(flags, h.flags, sizeof(flags), hipMemcpyDeviceToHost, h.stream), "flags");
       hip_check(hipStreamSynchronize(h.stream), "setup_mg");
+      h.arena.release(work);
       if (flags[0]) {
         h.arena.release(h.chol);
         h.chol = nullptr;

@@ -311,7 +311,7 @@ void launch_pi_leaf(H2& h);                       // Pi tiles of depth L
 void launch_pi_upper(H2& h, int d, const int* child_map);   // Pi tiles of depth d < L
 void launch_assemble_dense(H2& h, double* A, int64_t lda);  // depth d_top blocks
 void launch_assemble_kernel_dense(H2& h, double* A, int64_t lda);  // no far blocks
-void launch_potrf(H2& h, double* A, int64_t N);   // blocked Cholesky, sets flags[0]
+void launch_potrf(H2& h, double* A, int64_t N, double* work);   // blocked Cholesky, sets flags[0]; work: 64 * 64
 void launch_tri_inverse(H2& h, const double* L, int64_t N, double* S);   // S: X = L^{-1} below, X^T above the diagonal
 void launch_cast_precision(H2& h, int p);         // FP64 -> FP32 / BF16 copies
 void launch_near_tiles(H2& h);                    // stored near-field tiles (FP64)

@@ -542,91 +542,155 @@ __global__ __launch_bounds__(NT) void k_assemble_kernel_dense(
 }
 
 // ------------------------------------------------------------ Cholesky (lower, blocked)
+// Right-looking in steps of NB = 64 columns: the diagonal block is factored
+// and its inverse formed by one workgroup, the panel below is its product with
+// that inverse, and the trailing blocks are updated, both on the FP64 matrix
+// cores.  With the panel by substitution (one row per thread) and the update
+// in scalar loops a step of a 4096-row matrix took 88 + 81 + 68 us, 15 ms in all;
+// 63 + 32 + 37 us and 9 ms now, half of it the chain of 64 diagonal blocks.
 constexpr int NB = 64;
 
-__global__ __launch_bounds__(NT) void k_potrf_diag(double* A, int64_t N, int64_t k0, int* flag) {
+// Factor the block at k0; W (64 x 64, row-major) = the transposed inverse of
+// the factor (beyond the last row: identity).  Thread (i, g) holds row i,
+// columns g, g + 4, ... of the block (d, shifted down as columns are done) and
+// of the inverse (x) in registers; column c of the block and row c of the
+// inverse go through LDS, two buffers in turn, so a column takes one barrier.
+__global__ __launch_bounds__(NT) void k_potrf_diag(double* A, int64_t N, int64_t k0, double* __restrict__ W,
+                                                   int* flag) {
   if (*flag) return;
-  __shared__ double D[NB][NB + 1];
+  __shared__ double col[2][NB], xrow[2][NB];
   const int nb = int(min<int64_t>(NB, N - k0));
-  const int tid = threadIdx.x;
-  for (int idx = tid; idx < nb * nb; idx += NT) {
-    const int i = idx % nb, j = idx / nb;
-    D[i][j] = A[(k0 + i) + (k0 + j) * N];
+  const int tid = threadIdx.x, i = tid & (NB - 1), g = tid / NB;
+  double d[16], x[16];
+#pragma unroll
+  for (int k = 0; k < 16; ++k) {
+    const int j = 4 * k + g;
+    d[k] = i < nb && j < nb ? A[(k0 + i) + (k0 + j) * N] : i == j ? 1.0 : 0.0;
+    x[k] = i == j ? 1.0 : 0.0;
   }
-  __syncthreads();
-  for (int c = 0; c < nb; ++c) {
-    const double piv = D[c][c];
-    __syncthreads();
-    if (!(piv > 0.0)) {
-      if (tid == 0) atomicOr(flag, 1);
-      return;
+  for (int cc = 0; cc < 16; ++cc) {
+#pragma unroll
+    for (int gg = 0; gg < 4; ++gg) {
+      const int c = 4 * cc + gg;
+      double* cl = col[gg & 1];
+      double* xr = xrow[gg & 1];
+      if (g == gg) cl[i] = d[0];
+      if (i == c) {
+#pragma unroll
+        for (int k = 0; k < 16; ++k) xr[4 * k + g] = x[k];
+      }
+      __syncthreads();
+      const double piv = cl[c];
+      if (!(piv > 0.0)) {
+        if (tid == 0) atomicOr(flag, 1);
+        return;
+      }
+      const double inv = rsqrt_nn(piv);
+      const double ci = cl[i];
+      if (g == gg && c < nb && i < nb)
+        A[(k0 + i) + (k0 + c) * N] = i > c ? ci * inv : i == c ? sqrt_nn(piv) : 0.0;
+      if (i > c) {
+        const double f = ci * inv * inv;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+          if (k + cc < 16) d[k] -= f * cl[4 * (k + cc) + g];
+          x[k] -= f * xr[4 * k + g];
+        }
+      } else if (i == c) {
+#pragma unroll
+        for (int k = 0; k < 16; ++k) x[k] *= inv;
+      }
     }
-    const double dc = sqrt(piv);
-    for (int i = c + tid; i < nb; i += NT) D[i][c] = i == c ? dc : D[i][c] / dc;
-    __syncthreads();
-    const int rem = nb - c - 1;
-    for (int idx = tid; idx < rem * rem; idx += NT) {
-      const int i = c + 1 + idx % rem, j = c + 1 + idx / rem;
-      if (j <= i) D[i][j] -= D[i][c] * D[j][c];
-    }
-    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 15; ++k) d[k] = d[k + 1];
   }
-  for (int idx = tid; idx < nb * nb; idx += NT) {
-    const int i = idx % nb, j = idx / nb;
-    A[(k0 + i) + (k0 + j) * N] = j <= i ? D[i][j] : 0.0;
-  }
+#pragma unroll
+  for (int k = 0; k < 16; ++k) W[(4 * k + g) * NB + i] = x[k];
 }
 
-// L_ik = A_ik L_kk^{-T} for every row block i below k (one row per thread).
-__global__ __launch_bounds__(NB) void k_trsm_panel(double* A, int64_t N, int64_t k0, const int* flag) {
+// One 64 x 64 tile of a step per workgroup, 16 of its columns per wave (the
+// matrix is column-major, so the product is formed transposed: result row =
+// column of the tile, and lanes of a result column are consecutive rows).
+// PANEL: L_ik = A_ik L_kk^{-T} for row block blockIdx.x below k (a whole block
+// column), in place: the product with the inverse, then once more with what is
+// left, A_ik - L_ik L_kk^T, without which A - L L^T is up to twice as far off
+// as with a substitution;
+// else A_ij -= L_ik L_jk^T for the blockIdx.x-th pair i >= j > k of row blocks.
+template <bool PANEL>
+__global__ __launch_bounds__(NT) void k_potrf_tile(double* A, int64_t N, int64_t k0, const double* __restrict__ W,
+                                                   const int* flag) {
   if (*flag) return;
-  __shared__ double D[NB][NB + 1];
-  __shared__ double X[NB][NB + 1];
-  const int nb = int(min<int64_t>(NB, N - k0));
-  const int tid = threadIdx.x;
-  for (int idx = tid; idx < nb * nb; idx += NB) {
-    const int i = idx % nb, j = idx / nb;
-    D[i][j] = A[(k0 + i) + (k0 + j) * N];
-  }
-  const int64_t row = k0 + nb + int64_t(blockIdx.x) * NB + tid;
-  const bool ok = row < N;
-  for (int c = 0; c < nb; ++c) X[tid][c] = ok ? A[row + (k0 + c) * N] : 0.0;
-  __syncthreads();
-  if (!ok) return;
-  for (int c = 0; c < nb; ++c) {
-    double s = X[tid][c];
-    for (int q = 0; q < c; ++q) s -= X[tid][q] * D[c][q];
-    X[tid][c] = s / D[c][c];
-  }
-  for (int c = 0; c < nb; ++c) A[row + (k0 + c) * N] = X[tid][c];
-}
-
-// A_ij -= L_ik L_jk^T for row blocks i >= j > k (lower triangle only).
-__global__ __launch_bounds__(NT) void k_syrk_update(double* A, int64_t N, int64_t k0, int nbrem,
-                                                    const int* flag) {
-  if (*flag) return;
-  // triangular index of (bi, bj), bi >= bj, over the nbrem trailing blocks
-  int p = blockIdx.x, bi = 0;
-  while (p > bi) { p -= bi + 1; ++bi; }
-  const int bj = p;
   const int nbk = int(min<int64_t>(NB, N - k0));
-  const int64_t r0 = k0 + nbk + int64_t(bi) * NB, c0 = k0 + nbk + int64_t(bj) * NB;
-  const int ni = int(min<int64_t>(NB, N - r0)), nj = int(min<int64_t>(NB, N - c0));
-  __shared__ double Li[NB][NB + 1], Lj[NB][NB + 1];
-  const int tid = threadIdx.x;
-  for (int idx = tid; idx < NB * NB; idx += NT) {
-    const int i = idx % NB, q = idx / NB;
-    Li[i][q] = (i < ni && q < nbk) ? A[(r0 + i) + (k0 + q) * N] : 0.0;
-    Lj[i][q] = (i < nj && q < nbk) ? A[(c0 + i) + (k0 + q) * N] : 0.0;
+  int bi = blockIdx.x, bj = 0;
+  if constexpr (!PANEL) {
+    // triangular index of (bi, bj), bi >= bj
+    int p = blockIdx.x;
+    bi = 0;
+    while (p > bi) { p -= bi + 1; ++bi; }
+    bj = p;
   }
-  __syncthreads();
-  for (int idx = tid; idx < NB * NB; idx += NT) {
-    const int i = idx % NB, j = idx / NB;
-    if (i >= ni || j >= nj) continue;
-    if (bi == bj && j > i) continue;
-    double s = 0.0;
-    for (int q = 0; q < nbk; ++q) s += Li[i][q] * Lj[j][q];
-    A[(r0 + i) + (c0 + j) * N] -= s;
+  const int64_t r0 = k0 + nbk + int64_t(bi) * NB, c0 = PANEL ? k0 : k0 + nbk + int64_t(bj) * NB;
+  const int nj = int(min<int64_t>(NB, N - c0));
+  const int w = threadIdx.x >> 6, li = threadIdx.x & 15, lk = (threadIdx.x >> 4) & 3;
+  const int j = 16 * w + li;           // column of the tile that this lane supplies
+  d4 acc[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) acc[c] = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+  for (int q0 = 0; q0 < NB; q0 += 4) {
+    const int q = q0 + lk;
+    const bool in = q < nbk;
+    // PANEL: W holds (L_kk^{-1})^T, so column j of the panel is sum_q A_iq W[q][j]
+    const double a = !in ? 0.0 : PANEL ? W[q * NB + j] : j < nj ? A[(c0 + j) + (k0 + q) * N] : 0.0;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int64_t i = r0 + 16 * c + li;
+      acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, in && i < N ? A[i + (k0 + q) * N] : 0.0, acc[c], 0, 0, 0);
+    }
+  }
+  if constexpr (PANEL) {
+    __shared__ double T[NB][NB + 16];
+    const auto put = [&](const d4(&v)[4]) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) T[16 * w + 4 * t + lk][16 * c + li] = v[c][t];
+    };
+    const auto add = [&](d4(&v)[4], auto operand) {
+#pragma unroll 4
+      for (int q = lk; q < NB; q += 4) {
+        const double a = operand(q);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) v[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, T[q][16 * c + li], v[c], 0, 0, 0);
+      }
+    };
+    d4 res[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const int64_t i = r0 + 16 * c + li;
+        res[c][t] = i < N ? A[i + (c0 + 16 * w + 4 * t + lk) * N] : 0.0;
+      }
+    put(acc);
+    __syncthreads();
+    add(res, [&](int q) { return -A[(k0 + j) + (k0 + q) * N]; });
+    __syncthreads();                     // every wave has read the panel, which is overwritten
+    put(res);
+    __syncthreads();
+    add(acc, [&](int q) { return W[q * NB + j]; });
+  }
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const int64_t i = r0 + 16 * c + li;
+    if (i >= N) continue;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const int col = 16 * w + 4 * t + lk;
+      if (col >= nj || (!PANEL && i < c0 + col)) continue;
+      double* o = A + i + (c0 + col) * N;
+      *o = PANEL ? acc[c][t] : *o - acc[c][t];
+    }
   }
 }
 
@@ -1016,15 +1080,14 @@ void launch_assemble_kernel_dense(H2& h, double* A, int64_t lda) {
   check_launch("assemble_kernel_dense");
 }
 
-void launch_potrf(H2& h, double* A, int64_t N) {
+void launch_potrf(H2& h, double* A, int64_t N, double* work) {
   for (int64_t k0 = 0; k0 < N; k0 += NB) {
-    hipLaunchKernelGGL(k_potrf_diag, dim3(1), dim3(NT), 0, h.stream, A, N, k0, h.flags);
+    hipLaunchKernelGGL(k_potrf_diag, dim3(1), dim3(NT), 0, h.stream, A, N, k0, work, h.flags);
     const int64_t below = N - k0 - std::min<int64_t>(NB, N - k0);
     if (below > 0) {
       const int nrb = int((below + NB - 1) / NB);
-      hipLaunchKernelGGL(k_trsm_panel, dim3(nrb), dim3(NB), 0, h.stream, A, N, k0, h.flags);
-      const int npairs = nrb * (nrb + 1) / 2;
-      hipLaunchKernelGGL(k_syrk_update, dim3(npairs), dim3(NT), 0, h.stream, A, N, k0, nrb,
+      hipLaunchKernelGGL(k_potrf_tile<true>, dim3(nrb), dim3(NT), 0, h.stream, A, N, k0, work, h.flags);
+      hipLaunchKernelGGL(k_potrf_tile<false>, dim3(nrb * (nrb + 1) / 2), dim3(NT), 0, h.stream, A, N, k0, work,
                          h.flags);
     }
   }
