@@ -61,7 +61,7 @@ T* upload_owned(H2& h, const std::vector<T>& v) {
 bool use_dual(int T, int rr) { return T == 8 && rr * NR * 2 <= (8 * T) * (8 * T); }
 
 TileSet make_set(H2& h, const std::vector<int>& ids, const std::vector<int>& rows, const std::vector<int>& cols,
-                 int nrows_total, int row0, int nrows, const int* brow, const int* bcol, int run,
+                 int nrows_total, int row0, int nrows, int used, const int* brow, const int* bcol, int run,
                  bool dual) {
   TileSet ts;
   ts.run = run;
@@ -70,6 +70,7 @@ TileSet make_set(H2& h, const std::vector<int>& ids, const std::vector<int>& row
   ts.bcol = bcol;
   ts.row0 = row0;
   ts.nrows = nrows;
+  ts.used = used;
   ts.ntiles = int64_t(ids.size());
   auto build = [&](bool by_col, int runlen, std::vector<int>& order, std::vector<int>& tasks,
                    std::vector<int>& ptr) {
@@ -160,10 +161,10 @@ void run_set(H2& h, int p, const TileSet& ts, bool near, const void* x, void* ou
 TileSet tuned_set(H2& h, int p, bool near, const void* x, void* out, const std::vector<int>& ids,
                   const std::vector<int>& rows, const std::vector<int>& cols, int nrows_total, int row0,
                   int nrows, const int* brow, const int* bcol) {
-  const int rr = near ? 64 : h.r;
+  const int rr = near ? 64 : h.r, used = near ? 8 * h.snear.lanes : h.r;
   const bool dual = use_dual(near ? 8 : h.T, rr);
   if (!h.autotune || ids.empty())
-    return make_set(h, ids, rows, cols, nrows_total, row0, nrows, brow, bcol, RUN, dual);
+    return make_set(h, ids, rows, cols, nrows_total, row0, nrows, used, brow, bcol, RUN, dual);
   hipEvent_t e0, e1;
   hip_check(hipEventCreate(&e0), "event");
   hip_check(hipEventCreate(&e1), "event");
@@ -171,7 +172,7 @@ TileSet tuned_set(H2& h, int p, bool near, const void* x, void* out, const std::
   float best_ms = 0.0f;
   try {
     for (int run : RUNS) {
-      TileSet ts = make_set(h, ids, rows, cols, nrows_total, row0, nrows, brow, bcol, run, dual);
+      TileSet ts = make_set(h, ids, rows, cols, nrows_total, row0, nrows, used, brow, bcol, run, dual);
       const int64_t need = ts.nslots() * rr * NR;
       size_t free_b = 0, total_b = 0;
       hip_check(hipMemGetInfo(&free_b, &total_b), "memory info");

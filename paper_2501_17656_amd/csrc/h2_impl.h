@@ -146,6 +146,7 @@ struct TileSet {
   const int* brow = nullptr;           // device: block row / column of every tile
   const int* bcol = nullptr;
   int row0 = 0, nrows = 0;             // rows the reduce writes
+  int used = 0;                        // rows of a block that are not padding (partial results hold these)
   int run = 0;                         // tiles per task
   double tuned_ms = 0.0;               // measured product + reduce time (tuned sets)
   int64_t ntiles = 0;                  // tiles in the set (each read by the row pass)
@@ -396,6 +397,7 @@ struct TgemmMember {
   int nrt;
   int rr;
   int lanes;                           // tile_A of the tiles
+  int used;
 };
 struct TgemmGroup {
   int n;
@@ -419,6 +421,7 @@ struct TevalMember {
   KernelParams kp;
   int nrt;
   int dim;
+  int used;
 };
 struct TevalGroup {
   int n;

@@ -71,7 +71,8 @@ __device__ __forceinline__ int swz(int i) {
 // column bcol[b]; the operand of a row task is the block of bcol[b], of a
 // column task that of brow[b], at x + index * rr * 16 (rr rows: the rank for
 // coupling tiles, 64 for near-field tiles; rows >= rr of the RP = 8T padded
-// tile are zero).  out[block] = the rr x 16 result.
+// tile are zero).  out[block] = the result's first `used` rows (a near-field
+// chunk of 39 points has 40 of 64), 16 columns each.
 // A block has one wave per 16-row slab of the result (RP / 16 = T / 2
 // waves); all of them stage the tile and its operand rows into LDS together,
 // then wave w runs the matrix-core products of slab w.  The stage object fills
@@ -106,7 +107,7 @@ __device__ __forceinline__ void tgemm_body(int blk, const int* __restrict__ rtas
                                            const int* __restrict__ ctask,
                                            const int* __restrict__ corder,
                                            const int* __restrict__ brow,
-                                           const int* __restrict__ bcol, int rr,
+                                           const int* __restrict__ bcol, int rr, int used,
                                            const Tv* __restrict__ x, Tv* out_base,
                                            TgemmLds<T, Tv>& lds, const Stage& stage,
                                            const int* __restrict__ rslot = nullptr) {
@@ -189,11 +190,11 @@ __device__ __forceinline__ void tgemm_body(int blk, const int* __restrict__ rtas
         if (slot >= 0) {
           const typename M::acc_t at = products(std::integral_constant<bool, true>{}, (nrow + 3) >> 2, lds.xs,
                                                 typename M::acc_t{Tv(0), Tv(0), Tv(0), Tv(0)});
-          Tv* oc = out_base + int64_t(nrt + slot) * rr * NR;
+          Tv* oc = out_base + int64_t(nrt + slot) * used * NR;
 #pragma unroll
           for (int t = 0; t < 4; ++t) {
             const int row = 16 * w + M::row(t, q);
-            if (row < rr) oc[row * NR + p] = at[t];
+            if (row < used) oc[row * NR + p] = at[t];
           }
         }
       }
@@ -201,11 +202,11 @@ __device__ __forceinline__ void tgemm_body(int blk, const int* __restrict__ rtas
   };
   if (tr) run(std::integral_constant<bool, true>{});
   else run(std::integral_constant<bool, false>{});
-  Tv* out = out_base + int64_t(blk) * rr * NR;
+  Tv* out = out_base + int64_t(blk) * used * NR;
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
     const int row = 16 * w + M::row(t, q);
-    if (row < rr) out[row * NR + p] = acc[t];
+    if (row < used) out[row * NR + p] = acc[t];
   }
 }
 
@@ -270,12 +271,13 @@ __global__ __launch_bounds__(32 * T) void k_tgemm(const int* __restrict__ rtask,
                                                   const int* __restrict__ corder,
                                                   const Te* __restrict__ tiles,
                                                   const int* __restrict__ brow,
-                                                  const int* __restrict__ bcol, int rr, int A,
+                                                  const int* __restrict__ bcol, int rr, int A, int used,
                                                   const Tv* __restrict__ x, Tv* __restrict__ partial,
                                                   const int* __restrict__ rslot) {
   __shared__ TgemmLds<T, Tv> lds;
   tgemm_body<T, Tv, StageStored<T, Te, Tv>, DUAL>(
-      blockIdx.x, rtask, nrt, rorder, ctask, corder, brow, bcol, rr, x, partial, lds, StageStored<T, Te, Tv>{tiles, A}, rslot);
+      blockIdx.x, rtask, nrt, rorder, ctask, corder, brow, bcol, rr, used, x, partial, lds,
+      StageStored<T, Te, Tv>{tiles, A}, rslot);
 }
 
 // Near-field tiles evaluated from the points, 4 waves: lane j holds the point
@@ -353,12 +355,12 @@ __global__ __launch_bounds__(256) void k_tgemm_eval(const int* __restrict__ rtas
                                                     const int* __restrict__ chunk_start,
                                                     const int* __restrict__ chunk_n,
                                                     const double* __restrict__ pts, int dim,
-                                                    KernelParams kp, PointScale ps,
+                                                    KernelParams kp, PointScale ps, int used,
                                                     const Tv* __restrict__ x, Tv* __restrict__ partial,
                                                     const int* __restrict__ rslot) {
   __shared__ TgemmLds<8, Tv> lds;
   tgemm_body<8, Tv, StageEval<Tv, KIND, DERIV>, DUAL>(
-      blockIdx.x, rtask, nrt, rorder, ctask, corder, brow, bcol, 64, x, partial, lds,
+      blockIdx.x, rtask, nrt, rorder, ctask, corder, brow, bcol, 64, used, x, partial, lds,
       StageEval<Tv, KIND, DERIV>{brow, bcol, chunk_start, chunk_n, pts, dim, kp, ps}, rslot);
 }
 
@@ -374,7 +376,7 @@ __global__ __launch_bounds__(32 * T) void k_tgemm_group(TgemmGroup G) {
   while (m + 1 < G.n && G.start[m + 1] <= int(blockIdx.x)) ++m;
   const TgemmMember& M = G.m[m];
   tgemm_body<T, Tv, StageStored<T, Te, Tv>, DUAL>(
-      int(blockIdx.x) - G.start[m], M.rtask, M.nrt, M.rorder, M.ctask, M.corder, M.brow, M.bcol, M.rr,
+      int(blockIdx.x) - G.start[m], M.rtask, M.nrt, M.rorder, M.ctask, M.corder, M.brow, M.bcol, M.rr, M.used,
       static_cast<const Tv*>(M.x), static_cast<Tv*>(M.partial), lds,
       StageStored<T, Te, Tv>{static_cast<const Te*>(M.tiles), M.lanes}, M.rslot);
 }
@@ -386,7 +388,7 @@ __global__ __launch_bounds__(256) void k_tgemm_eval_group(TevalGroup G) {
   while (m + 1 < G.n && G.start[m + 1] <= int(blockIdx.x)) ++m;
   const TevalMember& M = G.m[m];
   tgemm_body<8, Tv, StageEval<Tv, KIND, DERIV>, DUAL>(
-      int(blockIdx.x) - G.start[m], M.rtask, M.nrt, M.rorder, M.ctask, M.corder, M.brow, M.bcol, 64,
+      int(blockIdx.x) - G.start[m], M.rtask, M.nrt, M.rorder, M.ctask, M.corder, M.brow, M.bcol, 64, M.used,
       static_cast<const Tv*>(M.x), static_cast<Tv*>(M.partial), lds,
       StageEval<Tv, KIND, DERIV>{M.brow, M.bcol, M.chunk_start, M.chunk_n, M.pts, M.dim, M.kp, M.ps}, M.rslot);
 }
@@ -406,22 +408,23 @@ __device__ __forceinline__ void sum_run(Tv& v, const Tv* __restrict__ p, int64_t
   for (; t < b; ++t) v += p[int64_t(t) * stride];
 }
 
-// out[row] (rr x 16) = the row-pass partials [rtp[row], rtp[row+1]) plus the
-// column-pass partials [ctp[row], ctp[row+1]) (after the nrt row-pass ones),
-// summed in that order, for rows row0 .. row0 + nrows - 1.  Workgroup
-// (row, y) sums elements y * NT .. of its row, one element per thread.
+// out[row] (rr x 16, the first `used` rows of it) = the row-pass partials
+// [rtp[row], rtp[row+1]) plus the column-pass partials [ctp[row], ctp[row+1])
+// (after the nrt row-pass ones), summed in that order, for rows row0 .. row0 +
+// nrows - 1.  Workgroup (row, y) sums elements y * NT .. of its row, one
+// element per thread.
 template <typename Tv>
 __global__ __launch_bounds__(NT) void k_reduce16(int row0, const int* __restrict__ rtp,
-                                                 const int* __restrict__ ctp, int nrt, int rr,
+                                                 const int* __restrict__ ctp, int nrt, int rr, int used,
                                                  const Tv* __restrict__ partial, Tv* __restrict__ out) {
   const int row = row0 + blockIdx.x;
   const int e = blockIdx.y * NT + threadIdx.x;
-  if (e >= rr * NR) return;
-  const int64_t stride = int64_t(rr) * NR;
+  if (e >= used * NR) return;
+  const int64_t stride = int64_t(used) * NR;
   Tv v = Tv(0);
   sum_run(v, partial + e, stride, rtp[row], rtp[row + 1]);
   sum_run(v, partial + e, stride, nrt + ctp[row], nrt + ctp[row + 1]);
-  out[row * stride + e] = v;
+  out[int64_t(row) * rr * NR + e] = v;
 }
 
 // Tree-order FP64 block from user order (columns >= nrhs zero), and back.
@@ -465,7 +468,15 @@ __global__ __launch_bounds__(NT) void k_near_pad16(const int* __restrict__ leaf_
 __device__ inline void colsum16(const double* __restrict__ part, int np, double* sums, double* red) {
   const int k = threadIdx.x & 15, g = threadIdx.x >> 4;
   double s = 0.0;
-  for (int b = g; b < np; b += 16) s += part[b * NR + k];
+  int b = g;
+  for (; b + 7 * 16 < np; b += 8 * 16) {
+    double v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = part[(b + u * 16) * NR + k];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s += v[u];
+  }
+  for (; b < np; b += 16) s += part[b * NR + k];
   red[threadIdx.x] = s;
   __syncthreads();
   if (threadIdx.x < NR) {
@@ -721,7 +732,7 @@ void launch_tgemm(H2& h, int tp, int T, const TileSet& ts, const void* tiles, in
         constexpr bool D = decltype(dc)::value;
         hipLaunchKernelGGL((k_tgemm<TT, Te, Tv, D>), dim3(nb), dim3(32 * TT), 0, h.stream, ts.rtask, ts.nrt,
                            ts.rorder, ts.ctask, ts.corder, static_cast<const Te*>(tiles), ts.brow, ts.bcol,
-                           rr, lanes, static_cast<const Tv*>(x), static_cast<Tv*>(partial), ts.rslot);
+                           rr, lanes, ts.used, static_cast<const Tv*>(x), static_cast<Tv*>(partial), ts.rslot);
       });
     });
   });
@@ -741,12 +752,12 @@ void launch_tgemm_eval(H2& h, int p, const TileSet& ts, const void* x, void* par
       if (p == P64)
         hipLaunchKernelGGL((k_tgemm_eval<double, KIND, DERIV, D>), dim3(nb), dim3(256), 0, h.stream, ts.rtask,
                            ts.nrt, ts.rorder, ts.ctask, ts.corder, ts.brow, ts.bcol, sn.chunk_start, sn.chunk_n,
-                           h.pts, h.dim, h.kp, ps, static_cast<const double*>(x), static_cast<double*>(partial),
+                           h.pts, h.dim, h.kp, ps, ts.used, static_cast<const double*>(x), static_cast<double*>(partial),
                            ts.rslot);
       else
         hipLaunchKernelGGL((k_tgemm_eval<float, KIND, DERIV, D>), dim3(nb), dim3(256), 0, h.stream, ts.rtask,
                            ts.nrt, ts.rorder, ts.ctask, ts.corder, ts.brow, ts.bcol, sn.chunk_start, sn.chunk_n,
-                           h.pts, h.dim, h.kp, ps, static_cast<const float*>(x), static_cast<float*>(partial),
+                           h.pts, h.dim, h.kp, ps, ts.used, static_cast<const float*>(x), static_cast<float*>(partial),
                            ts.rslot);
     });
   });
@@ -768,7 +779,7 @@ void launch_tgemm_group(hipStream_t st, int tp, const std::vector<GroupTiles>& i
           const GroupTiles& it = *sel[c0 + m];
           G.start[m] = int(total);
           G.m[m] = TgemmMember{it.ts->rtask, it.ts->rorder, it.ts->ctask, it.ts->corder, it.tiles, it.ts->brow,
-                               it.ts->bcol, it.x, it.partial, it.ts->rslot, it.ts->nrt, it.rr, it.lanes};
+                               it.ts->bcol, it.x, it.partial, it.ts->rslot, it.ts->nrt, it.rr, it.lanes, it.ts->used};
           total += it.ts->nrt + it.ts->nct;
         }
         G.start[G.n] = int(total);
@@ -814,7 +825,7 @@ void launch_tgemm_eval_group(hipStream_t st, int p, const std::vector<GroupEval>
         G.start[m] = int(total);
         G.m[m] = TevalMember{it.ts->rtask, it.ts->rorder, it.ts->ctask, it.ts->corder, it.ts->brow, it.ts->bcol,
                              h.snear.chunk_start, h.snear.chunk_n, h.pts, it.x, it.partial, it.ts->rslot,
-                             PointScale{h.scale, h.diag, nullptr, nullptr, 0}, h.kp, it.ts->nrt, h.dim};
+                             PointScale{h.scale, h.diag, nullptr, nullptr, 0}, h.kp, it.ts->nrt, h.dim, it.ts->used};
         total += it.ts->nrt + it.ts->nct;
       }
       G.start[G.n] = int(total);
@@ -838,13 +849,13 @@ void launch_tgemm_eval_group(hipStream_t st, int p, const std::vector<GroupEval>
 
 void launch_reduce16(H2& h, int p, const TileSet& ts, int rr, const void* partial, void* out) {
   if (ts.nrows == 0) return;
-  const dim3 grid(ts.nrows, (rr * NR + NT - 1) / NT);
+  const dim3 grid(ts.nrows, (ts.used * NR + NT - 1) / NT);
   if (p == P64)
     hipLaunchKernelGGL(k_reduce16<double>, grid, dim3(NT), 0, h.stream, ts.row0, ts.rtp, ts.ctp,
-                       ts.nrt, rr, static_cast<const double*>(partial), static_cast<double*>(out));
+                       ts.nrt, rr, ts.used, static_cast<const double*>(partial), static_cast<double*>(out));
   else
     hipLaunchKernelGGL(k_reduce16<float>, grid, dim3(NT), 0, h.stream, ts.row0, ts.rtp, ts.ctp,
-                       ts.nrt, rr, static_cast<const float*>(partial), static_cast<float*>(out));
+                       ts.nrt, rr, ts.used, static_cast<const float*>(partial), static_cast<float*>(out));
   check_launch("reduce16");
 }
 

@@ -35,9 +35,11 @@ void check_launch(const char* what) {
 // holds at once: 64 elements per lane.
 template <int T> constexpr int SWEEP_NT = T == 8 ? 512 : 1024;
 template <int T> constexpr int SWEEP_UNROLL = T == 8 ? 1 : T == 4 ? 2 : 8;
-// Levels per launch: at most 2^5 to 2^7 tiles per workgroup (about 1 MB of
-// FP64 tiles), and at most 1024 coefficients a level.
-constexpr int sweep_levels(int T) { return T == 8 ? 4 : T == 4 ? 5 : 6; }
+// Levels per launch: up to half a megabyte of FP64 tiles per workgroup, and at
+// most 1024 coefficients a level.  Four levels of 64 x 64 tiles in one launch
+// (a megabyte for each of 64 workgroups) took 27 us up and 22 us down, two and
+// two of them 21 and 22 us (100k points).
+constexpr int sweep_levels(int T) { return T == 8 ? 3 : T == 4 ? 4 : 6; }
 constexpr int SWEEP_BUF = 1024;        // coefficients of one level of a subtree: 2^nlev * r at most
 
 // Sum of np partial sums by the whole workgroup, in a fixed order.
