@@ -170,13 +170,14 @@ struct KernelParams {
 // products that evaluate their close blocks spend nearly all their time here
 // (FP64 vector issue), and the arguments are known: x = r^2 >= 0 and an
 // exponent <= 0.  So nothing is spent on signs, special cases and subnormal
-// scaling: a Matern entry with its distance and its two sums issues about 40
-// FP64 operations instead of 66 with the library's sqrt and exp (a product at
-// N = 131072, 3D, close blocks evaluated: 3453 to 2697 us).
-//   sqrt_nn, rsqrt_nn: Goldschmidt's and Newton's iterations from the
-//     hardware's reciprocal square root (about 2^-22 off in FP64, 1 ulp in
-//     FP32), the last correction with an exact residual: within 0.51 ulp.
-//     x is raised to MIN_R2, so that r = 0 gives a root too small to matter.
+// scaling: a Matern entry with its distance and its two sums issues 33
+// operations, most of them FP64, instead of 66 with the library's sqrt and exp
+// (a product at N = 131072, 3D, close blocks evaluated: 3453 to 2398 us).
+//   sqrt_nn: from the hardware's reciprocal square root y (about 2^-24 off in
+//     FP64, 1 ulp in FP32), g = x y and the exact residual d = x - g^2 =
+//     e g^2: sqrt(x) = g + d y (1/2 + 3/8 e) + O(e^3), within 0.501 ulp.
+//   rsqrt_nn: Newton's iteration.
+//     sqrt_nn raises x to MIN_R2, so that r = 0 gives a root too small to matter.
 //   exp2_np(w) = 2^w, w <= 0: n = rint(w) and f = w - n are exact, 2^f =
 //     1 + f q(f) with q the degree-10 interpolant of (2^f - 1) / f in the
 //     Chebyshev nodes of [-1/2, 1/2] (2e-17 off), scaled by 2^n exactly;
@@ -191,11 +192,9 @@ template <bool MINED = false>
 __device__ inline double sqrt_nn(double x) {
   if constexpr (!MINED) x = __builtin_fmax(x, MIN_R2<double>);
   const double y = __builtin_amdgcn_rsq(x);
-  double g = x * y, h = 0.5 * y;
-  const double e = __builtin_fma(-h, g, 0.5);
-  g = __builtin_fma(g, e, g);
-  h = __builtin_fma(h, e, h);
-  return __builtin_fma(__builtin_fma(-g, g, x), h, g);
+  const double g = x * y;
+  const double t = __builtin_fma(-g, g, x) * y;
+  return __builtin_fma(t, __builtin_fma(0.375, t * y, 0.5), g);
 }
 template <bool MINED = false>
 __device__ inline float sqrt_nn(float x) {
