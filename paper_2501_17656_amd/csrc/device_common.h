@@ -91,11 +91,15 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 // the tile starting at `tile`.  Lanes that hold no entries get those of
 // another one: their rows and columns meet zero coefficients, and their own
 // results are not used.  NT: non-temporal (streaming) loads, for
-// blocks read once per product so they do not evict reused vectors.
-template <int T, typename Tb, typename Tacc, bool NT = false>
-__device__ inline void load_subtile(const Tb* __restrict__ tile, int lane, int A, Tacc (&B)[T * T]) {
+// blocks read once per product so they do not evict reused vectors.  PARTS:
+// only rows [part T / PARTS, (part + 1) T / PARTS) of the sub-tile.
+template <int T, typename Tb, typename Tacc, bool NT = false, int PARTS = 1>
+__device__ inline void load_subtile(const Tb* __restrict__ tile, int lane, int A, Tacc (&B)[T * T / PARTS],
+                                    int part = 0) {
   constexpr int K = tile_K<Tb>(T);
-  constexpr int NC = T * T / K;
+  constexpr int NC = T * T / K / PARTS;
+  static_assert(NC * K * PARTS == T * T);
+  tile += part * NC * A * A * K;
   // a uniform base and one 32-bit lane offset for all chunks (an address per
   // chunk would take 64 registers)
   const uint32_t off = uint32_t(A * min(lane >> 3, A - 1) + min(lane & 7, A - 1)) * uint32_t(K * sizeof(Tb));

@@ -29,11 +29,13 @@ void fine_from_leaves(H2& h, int p, const void* xt, void* out, bool to_user, dou
   void* xall = h.xall;
   void* yall = h.yall;
   const int r = h.r;
+  bool near_done = false;
   if (h.d_top >= 0) {
     // upsweep: x_d = E^T x_{d+1}
     if (h.L > h.d_top) launch_sweep_up(h, p, h.L, xall, nullptr, nullptr, nullptr, nullptr, 0);
     // couplings of every depth in one launch, then one reduce for all depths
-    launch_gemv(h, p, h.fine_launch, xall);
+    near_done = p == P64 && !near_stored_for(h, p) && launch_near_far(h, xt, h.fine_launch, xall);
+    if (!near_done) launch_gemv(h, p, h.fine_launch, xall);
     std::vector<const View*> vs;
     std::vector<int> bs;
     for (int d = h.d_top; d <= h.L; ++d) {
@@ -46,7 +48,7 @@ void fine_from_leaves(H2& h, int p, const void* xt, void* out, bool to_user, dou
   }
   // near field and leaf downsweep: y = D x + Q y_L
   if (near_stored_for(h, p)) launch_near_stored(h, p, xt);
-  else launch_near(h, p, xt);
+  else if (!near_done) launch_near(h, p, xt);
   launch_fine_reduce(h, p, at_depth(yall, p, h.L, r), out, to_user, alpha, add, beta, xt);
 }
 

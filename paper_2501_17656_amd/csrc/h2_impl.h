@@ -349,6 +349,9 @@ void launch_leaf_up(H2& h, int p, const void* xtree, void* xhat);
 // The same for a vector in user order, which it also writes in tree order.
 void launch_leaf_up_gather(H2& h, const double* xuser, double* xtree, double* xhat);
 void launch_near(H2& h, int p, const void* xtree);
+// launch_near and launch_gemv(h, P64, l, xall) in one launch, where there is a
+// kernel for both (returns whether).
+bool launch_near_far(H2& h, const void* xtree, const Launch& l, const void* xall);
 // Stored near field: snear.yc = D x over the chunk-padded layout, FP64
 // tiles and vectors (p = P64) or the FP32 tile copy with FP32 vectors.
 void launch_near_stored(H2& h, int p, const void* xtree);

@@ -18,6 +18,7 @@
 #include <string>
 
 #include "h2_impl.h"
+#include "tile_gemv.h"
 
 namespace h2mg {
 
@@ -28,88 +29,6 @@ void check_launch(const char* what) {
   if (e != hipSuccess) throw std::runtime_error(std::string(what) + ": " + hipGetErrorString(e));
 }
 
-template <typename Tv> __device__ inline Tv zero() { return Tv(0); }
-
-// ------------------------------------------------------------ symmetric block GEMV
-// One wave per task (row gid s, blocks [b0, b1)).  partial[task] = sum_b B_b x_{col b};
-// colpart[slot of b] = B_b^T x_s for every off-diagonal block (slots are
-// ordered by column, so the reduce reads each column's run contiguously).
-// FULL: r == 8T (no padding, no guards).  Each iteration requests its tile
-// first, then the coefficients of its column (the next column index is
-// prefetched by a scalar load), so one tile is in flight per wave while the
-// previous is consumed.  Every tile is read once per launch, with
-// non-temporal loads (measured faster than ordinary loads for FP64, FP32 and
-// BF16 tiles alike on the same machine and run).
-template <int T, bool FULL, typename Tb, typename Tv>
-__device__ __forceinline__ void bsr_gemv_wave(const int* __restrict__ tasks, int ntasks,
-                                              const Tb* __restrict__ blk,
-                                              const int* __restrict__ blk_col,
-                                              const int* __restrict__ blk_slot,
-                                              const Tv* __restrict__ x, Tv* __restrict__ partial,
-                                              Tv* __restrict__ colpart, int r, int A) {
-  constexpr bool NTL = true;
-  const int wave = __builtin_amdgcn_readfirstlane(int((blockIdx.x * blockDim.x + threadIdx.x) >> 6));
-  if (wave >= ntasks) return;
-  const int lane = threadIdx.x & 63;
-  const int a = lane >> 3, b = lane & 7;
-  const int row = tasks[3 * wave], b0 = tasks[3 * wave + 1], b1 = tasks[3 * wave + 2];
-  const int rr = FULL ? 8 * T : r;
-  Tv xs[T], acc[T];
-#pragma unroll
-  for (int u = 0; u < T; ++u) {
-    const int i = a * T + u;
-    xs[u] = (FULL || i < rr) ? x[int64_t(row) * rr + i] : zero<Tv>();
-    acc[u] = zero<Tv>();
-  }
-  int col = blk_col[b0];
-  for (int bi = b0; bi < b1; ++bi) {
-    Tv B[T * T];
-    load_subtile<T, Tb, Tv, NTL>(blk + int64_t(bi) * tile_elems(T), lane, A, B);
-    const int col_next = bi + 1 < b1 ? blk_col[bi + 1] : col;
-    Tv xt[T];
-#pragma unroll
-    for (int v = 0; v < T; ++v) {
-      const int j = b * T + v;
-      xt[v] = (FULL || j < rr) ? x[int64_t(col) * rr + j] : zero<Tv>();
-    }
-#pragma unroll
-    for (int u = 0; u < T; ++u)
-#pragma unroll
-      for (int v = 0; v < T; ++v) acc[u] += B[u * T + v] * xt[v];
-    if (col != row) {
-      Tv z[T];
-#pragma unroll
-      for (int v = 0; v < T; ++v) {
-        Tv s = zero<Tv>();
-#pragma unroll
-        for (int u = 0; u < T; ++u) s += B[u * T + v] * xs[u];
-        z[v] = s;
-      }
-      const Tv zs = transpose_reduce_a<T, Tv>(z, a);
-      const int v = reduced_index<T>(a);
-      const int j = b * T + v;
-      if ((T == 8 || (a & ((8 / T) - 1)) == 0) && (FULL || j < rr))
-        colpart[int64_t(blk_slot[bi]) * rr + j] = zs;
-    }
-    col = col_next;
-  }
-#pragma unroll
-  for (int u = 0; u < T; ++u) {
-    Tv s = acc[u];
-    s += shfl_xor(s, 1);
-    s += shfl_xor(s, 2);
-    s += shfl_xor(s, 4);
-    acc[u] = s;
-  }
-  if (b == 0) {
-#pragma unroll
-    for (int u = 0; u < T; ++u) {
-      const int i = a * T + u;
-      if (FULL || i < rr) partial[int64_t(wave) * rr + i] = acc[u];
-    }
-  }
-}
-
 // Couplings and projected close blocks (r x r tiles).
 template <int T, bool FULL, typename Tb, typename Tv>
 __global__ __launch_bounds__(256) void k_bsr_gemv(const int* __restrict__ tasks, int ntasks,
@@ -118,7 +37,7 @@ __global__ __launch_bounds__(256) void k_bsr_gemv(const int* __restrict__ tasks,
                                                   const int* __restrict__ blk_slot,
                                                   const Tv* __restrict__ x, Tv* __restrict__ partial,
                                                   Tv* __restrict__ colpart, int r) {
-  bsr_gemv_wave<T, FULL, Tb, Tv>(tasks, ntasks, blk, blk_col, blk_slot, x, partial, colpart, r,
+  bsr_gemv_wave<T, FULL, 1, Tb, Tv>(wave_id(), tasks, ntasks, blk, blk_col, blk_slot, x, partial, colpart, r,
                                  FULL ? 8 : tile_A(r, T));
 }
 
@@ -131,7 +50,7 @@ __global__ __launch_bounds__(256) void k_near_gemv(const int* __restrict__ tasks
                                                    const double* __restrict__ x,
                                                    double* __restrict__ partial,
                                                    double* __restrict__ colpart, int A) {
-  bsr_gemv_wave<8, true, double, double>(tasks, ntasks, tiles, blk_col, blk_slot, x, partial,
+  bsr_gemv_wave<8, true, 1, double, double>(wave_id(), tasks, ntasks, tiles, blk_col, blk_slot, x, partial,
                                          colpart, 64, A);
 }
 
@@ -144,7 +63,7 @@ __global__ __launch_bounds__(256) void k_near_gemv32(const int* __restrict__ tas
                                                      const float* __restrict__ x,
                                                      float* __restrict__ partial,
                                                      float* __restrict__ colpart, int A) {
-  bsr_gemv_wave<8, true, float, float>(tasks, ntasks, tiles, blk_col, blk_slot, x, partial, colpart, 64, A);
+  bsr_gemv_wave<8, true, 1, float, float>(wave_id(), tasks, ntasks, tiles, blk_col, blk_slot, x, partial, colpart, 64, A);
 }
 
 // Sources of one depth for the reduce: task partials of the row (contiguous

@@ -2,7 +2,7 @@
 // close leaf pairs), one vector, the entries formed from the points in every
 // product.
 //
-// FP64 vector issue bounds it (about 40 operations an entry), so what counts
+// FP64 vector issue bounds it (33 operations an entry), so what counts
 // is that no entry is formed for padding and that nothing else is issued.
 //   * One wave per task: a row leaf s and a run of its close pairs (s <= t),
 //     in chunks of up to 64 rows.  No LDS and no barrier, so the waves of a
@@ -17,17 +17,18 @@
 //     leaves.
 //   * A column sum over the 8 lanes of a column takes three DPP steps per 8 U
 //     entries; eight columns are collected and written as one 64-word run.
-// Measured, one FP64 pass (before / after): 2270 / 401 us on 50000 points of a
-// Gaussian mixture (leaves of 49), 1059 / 133 us on a 300 x 300 grid (leaves of
-// 44), 40 / 14 us on 4096 points, 3073 / 2282 us (with the cheaper entries) on
+// Measured, one FP64 pass (before / after): 2270 / 388 us on 50000 points of a
+// Gaussian mixture (leaves of 49), 1059 / 126 us on a 300 x 300 grid (leaves of
+// 44), 40 / 14 us on 4096 points, 3073 / 2140 us (with the cheaper entries) on
 // 131072 points with full leaves, where three waves per SIMD issue an FP64
-// operation every 5.3 cycles (eight would reach 4.5) and an entry takes 40.
+// operation every 5.3 cycles (eight would reach 4.5).
 #include <hip/hip_runtime.h>
 
 #include <stdexcept>
 #include <string>
 
 #include "h2_impl.h"
+#include "tile_gemv.h"
 
 namespace h2mg {
 
@@ -165,10 +166,9 @@ __device__ __forceinline__ void near_rows(const NearIn<Tv>& A, int task, int par
 // leaf's chunks in turn and adds their column sums; else each chunk has its
 // own place, and a chunk beyond a shorter leaf's rows writes zeros.
 template <typename Tv, int KIND, int DERIV>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_near(const int* __restrict__ tasks, int ntasks, NearIn<Tv> A, int dim,
-                                              int chunk, int nchunk, bool mined) {
+__device__ __forceinline__ void near_wave(int wave, const int* __restrict__ tasks, int ntasks, const NearIn<Tv>& A,
+                                          int dim, int chunk, int nchunk, bool mined) {
   constexpr bool MAY = KIND != KER_LAPLACE && DERIV != DER_RADIAL;   // no question about r = 0
-  const int wave = __builtin_amdgcn_readfirstlane(int((blockIdx.x * blockDim.x + threadIdx.x) >> 6));
   if (wave >= ntasks * A.nsplit) return;
   const int task = wave / A.nsplit, part = wave % A.nsplit;
   const int sl = tasks[3 * task], p0 = tasks[3 * task + 1], p1 = tasks[3 * task + 2];
@@ -211,7 +211,91 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
   }
 }
 
+template <typename Tv, int KIND, int DERIV>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void
+k_near(const int* __restrict__ tasks, int ntasks, NearIn<Tv> A, int dim, int chunk, int nchunk, bool mined) {
+  near_wave<Tv, KIND, DERIV>(wave_id(), tasks, ntasks, A, dim, chunk, nchunk, mined);
+}
+
+// Near field and couplings of a fine FP64 product in one launch.  The first is
+// bound by vector issue, the second by HBM, and neither needs the other.
+// far_share: 2^32 times the share of the coupling blocks, rounded up, which
+// spreads them evenly over the launch.  (On two streams nothing overlapped: the
+// near field of the one took every wave slot before the other started.)
+// Registers for three waves a SIMD, as the near field alone, so a 64 x 64 tile
+// is read in two halves; the coupling waves go first when their data is there.
+// A product of 131072 points (3D, rank 64) took 2438 us with two launches and
+// 2246 with one, 50000 points (rank 25 in tiles of 32) 593 and 566; with
+// tiles of 16, which want more waves in flight than three, 90000 points took 190
+// and 199 us, 4096 points 35.6 and 36.8: those stay two launches.
+struct FarIn {
+  const int* tasks;
+  int ntasks;
+  const double* blk;
+  const int* blk_col;
+  const int* blk_slot;
+  const double* x;
+  double* partial;
+  double* colpart;
+  int r, T;
+};
+
+template <int KIND>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void
+k_near_far(const int* __restrict__ tasks, int ntasks, NearIn<double> A, int dim, int chunk, int nchunk, bool mined,
+           FarIn F, uint32_t far_share) {
+  const int wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+  const uint32_t b = blockIdx.x, f = __umulhi(b, far_share);
+  if (__umulhi(b + 1, far_share) == f) {
+    near_wave<double, KIND, DER_NONE>(int(b - f) * 4 + wv, tasks, ntasks, A, dim, chunk, nchunk, mined);
+    return;
+  }
+  __builtin_amdgcn_s_setprio(3);         // few instructions, each behind a load
+  auto go = [&](auto tc, auto fullc) {
+    constexpr int T = decltype(tc)::value;
+    constexpr bool FULL = decltype(fullc)::value;
+    bsr_gemv_wave<T, FULL, T == 8 ? 2 : 1, double, double>(int(f) * 4 + wv, F.tasks, F.ntasks, F.blk, F.blk_col,
+                                                           F.blk_slot, F.x, F.partial, F.colpart, F.r,
+                                                           FULL ? 8 : tile_A(F.r, T));
+  };
+  auto pick = [&](auto tc) {
+    if (F.r == 8 * decltype(tc)::value) go(tc, std::true_type{});
+    else go(tc, std::false_type{});
+  };
+  switch (F.T) {
+    case 1: pick(std::integral_constant<int, 1>{}); break;
+    case 2: pick(std::integral_constant<int, 2>{}); break;
+    case 4: pick(std::integral_constant<int, 4>{}); break;
+    default: pick(std::integral_constant<int, 8>{}); break;
+  }
+}
+
 }  // namespace
+
+bool launch_near_far(H2& h, const void* xtree, const Launch& l, const void* xall) {
+  const NearField& nf = h.near;
+  if (h.T < 4 || h.nq > 0 || h.timing || h.kp.deriv != DER_NONE || nf.ntasks == 0 || l.ntasks == 0) return false;
+  const int64_t nn = (int64_t(nf.ntasks) * nf.nsplit + 3) / 4, nfar = (l.ntasks + 3) / 4;
+  const uint32_t share = uint32_t((uint64_t(nfar) << 32) / uint64_t(nn + nfar) + 1);
+  KernelParams kp = h.kp;
+  if (h.diag) kp.shift = 0.0;          // the per-point diagonal is added by k_fine_reduce
+  const NearIn<double> A{nf.pair_col, nf.pair_slot, h.leaf_off, h.pts, h.scale, static_cast<const double*>(xtree),
+                         h.near_partial, h.near_colpart, kp, nf.ld, nf.nsplit};
+  const FarIn F{l.task, l.ntasks, static_cast<const double*>(h.prec[P64].blk), h.blk_col, h.blk_slot,
+                static_cast<const double*>(xall), h.partial, h.colpart, h.r, h.T};
+  auto go = [&](auto kc) {
+    hipLaunchKernelGGL((k_near_far<decltype(kc)::value>), dim3(unsigned(nn + nfar)), dim3(256), 0, h.stream, nf.task,
+                       nf.ntasks, A, h.dim, nf.chunk, nf.nchunk, nf.mined, F, share);
+  };
+  switch (h.kp.kind) {
+    case KER_EXP: go(std::integral_constant<int, KER_EXP>{}); break;
+    case KER_GAUSS: go(std::integral_constant<int, KER_GAUSS>{}); break;
+    case KER_LAPLACE: go(std::integral_constant<int, KER_LAPLACE>{}); break;
+    default: go(std::integral_constant<int, KER_MATERN32>{}); break;
+  }
+  check_launch("near_far");
+  return true;
+}
 
 void launch_near(H2& h, int p, const void* xtree) {
   if (h.nq > 0) throw std::runtime_error("close entries by quadrature are applied from the stored tiles only");

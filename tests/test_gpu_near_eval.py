@@ -81,3 +81,24 @@ def test_near_far_out(unit, dim, kernel):
     for y, eps in ((g.matvec(x), 2.0 ** -53), (g.level_apply(1, x, precision="fp32"), 2.0 ** -24)):
         assert float((y - want).norm()) <= 16 * n * eps * float(x.norm())
     g.close()
+
+
+@pytest.mark.parametrize("n,dim,m,leaf,kernel", [
+    (3000, 1, 20, 40, "exp"), (5000, 2, 5, 60, "gauss"), (4099, 2, 6, 80, "matern32"), (6000, 2, 8, 100, "exp"),
+    (6001, 3, 3, 50, "laplace"), (8000, 3, 4, 130, "matern32"), (20000, 3, 4, 90, "gauss")])
+def test_near_with_couplings(n, dim, m, leaf, kernel):
+    """One launch for close pairs and couplings gives what two give, bit for bit (kernel timing asks for
+    two): tiles of 32 and 64, full and not, leaves on both sides of 64 points, scaled and not."""
+    rng = np.random.default_rng(n)
+    dev = lambda a: torch.from_numpy(a).cuda()  # noqa: E731
+    pts, x = dev(rng.random((n, dim))), dev(rng.standard_normal(n))
+    scaled = {"scale": dev(0.5 + rng.random(n)), "diag": dev(1.0 + rng.random(n))}
+    for kw in ({}, scaled):
+        g = H2Matrix(pts, kernel, ELL, 0.0 if kernel == "laplace" else 1.0, leaf, 0.7, m, **kw)
+        y = g.matvec(x)
+        g.set_timing(True)
+        assert torch.equal(y, g.matvec(x))
+        assert g.kernel_stats("gemv_fp64")["launches"] == 1 and g.kernel_stats("near_fp64")["launches"] == 1
+        g.set_timing(False)
+        assert torch.equal(y, g.matvec(x))
+        g.close()
