@@ -170,7 +170,7 @@ Launch make_launch(H2& h, const std::vector<const View*>& views) {
 
 h2mg_status build_h2(const double* points_dev, int64_t n, int dim, const h2mg_kernel* kernel,
                      const h2mg_build_opts* opts, hipStream_t stream, H2** out,
-                     const double* scale_dev, const double* diag_dev) {
+                     const double* scale_dev, const double* diag_dev, const Plan* plan) {
   if (!points_dev || !kernel || !opts || !out) return fail(H2MG_ERR_INVALID_ARG, "null argument");
   if (kernel->kind < 0 || kernel->kind > 3) return fail(H2MG_ERR_INVALID_ARG, "unknown kernel kind %d", kernel->kind);
   if (kernel->derivative < 0 || kernel->derivative > 2)
@@ -206,12 +206,15 @@ h2mg_status build_h2(const double* points_dev, int64_t n, int dim, const h2mg_ke
   H2* hp = new (std::nothrow) H2();
   if (!hp) return fail(H2MG_ERR_OOM, "host allocation failed");
   H2& h = *hp;
-  h2mg_status st = build_plan(pts_h.data(), n, dim, opts, &h.plan);
-  if (st != H2MG_OK) {
-    delete hp;
-    return st;
+  if (!plan) {
+    const h2mg_status st = build_plan(pts_h.data(), n, dim, opts, &h.plan);
+    if (st != H2MG_OK) {
+      delete hp;
+      return st;
+    }
   }
   try {
+    if (plan) h.plan = *plan;
     const Plan& P = h.plan;
     h.stream = stream;
     h.n = int(n);
@@ -440,13 +443,8 @@ h2mg_status build_derivative(H2& h, int which, H2** out) {
   h2mg_kernel k = h.kernel;
   k.derivative = which;
   k.shift = 0.0;
-  const h2mg_status st = build_h2(user, h.n, h.dim, &k, &h.opts, h.stream, out);
+  const h2mg_status st = build_h2(user, h.n, h.dim, &k, &h.opts, h.stream, out, nullptr, nullptr, &h.plan);
   h.arena.release(user);
-  if (st == H2MG_OK && (*out)->plan.perm != h.plan.perm) {
-    delete *out;
-    *out = nullptr;
-    return fail(H2MG_ERR_HIP, "derivative build produced a different tree");
-  }
   return st;
 }
 

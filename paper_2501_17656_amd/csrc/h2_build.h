@@ -5,10 +5,12 @@
 namespace h2mg {
 
 // scale_dev, diag_dev: optional per-point scale and diagonal (device, user
-// order) of the scaled form diag(s) K diag(s) + diag(d).
+// order) of the scaled form diag(s) K diag(s) + diag(d).  plan: the plan of
+// these points and options, if there is one already (copied).
 h2mg_status build_h2(const double* points_dev, int64_t n, int dim, const h2mg_kernel* kernel,
                      const h2mg_build_opts* opts, hipStream_t stream, H2** out,
-                     const double* scale_dev = nullptr, const double* diag_dev = nullptr);
+                     const double* scale_dev = nullptr, const double* diag_dev = nullptr,
+                     const Plan* plan = nullptr);
 h2mg_status setup_mg(H2& h, int precision_mask);
 // Close entries by quadrature (user order: nq x dim sub-points and nq
 // weights per point); stores the near field, which every later product

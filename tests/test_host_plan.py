@@ -70,6 +70,17 @@ def test_plan_matches_oracle_exactly(kind, n, dim, leaf, eta, m):
     assert plan.rank == m ** dim
 
 
+@pytest.mark.parametrize("n", [255, 256, 257, 2050])
+def test_plan_order_of_ties_signs_and_zeros(n):
+    """Equal coordinates keep their order, and -0 equals 0, on both sides of the shortest list that is
+    sorted by bytes; values of both signs over the whole exponent range."""
+    rng = np.random.default_rng(n)
+    P = np.concatenate([rng.choice([-0.0, 0.0, 1.0, -1.0, 5e-324], (n // 2, 2)),
+                        rng.standard_normal((n - n // 2, 2)) * 10.0 ** rng.integers(-300, 100, (n - n // 2, 2))])
+    P = rng.permutation(P)
+    np.testing.assert_array_equal(Plan(P, 16, 0.7, 2).perm(), build_tree(P, 16).perm)
+
+
 @pytest.mark.slow
 def test_plan_matches_oracle_at_matern3d_1m_size():
     w = synth.workload("matern3d_1m")
