@@ -467,11 +467,12 @@ void cg16(H2& h, Work16& w, int k, const void* rhs, void* e, bool e0_zero, int n
 }
 
 // Direct solve on the coarsest level with the FP64 Cholesky factor, or its
-// inverse (w.tmp holds n x 16 doubles and is free here).
+// inverse (w.tmp holds n x 16 doubles and is free here, as is w.q).
 void coarse_solve16(H2& h, Work16& w, const void* r, void* e) {
   const int64_t nf = h.Nl * NR;
   if (h.cinv) {
-    launch_inverse_solve16(h, vprec(w.p), r, e, static_cast<double*>(w.tmp));
+    launch_inverse_solve16(h, vprec(w.p), r, e, static_cast<double*>(w.tmp),
+                           w.p == P64 ? static_cast<double*>(w.q) : w.coarse64);
   } else if (w.p == P64) {
     launch_copy(h, P64, r, e, nf);
     launch_chol_solve16(h, h.chol, h.Nl, static_cast<double*>(e));

@@ -765,8 +765,6 @@ h2mg_status setup_mg(H2& h, int precision_mask) {
         h.cinv = h.arena.make<double>(size_t(h.Nl) * h.Nl);
         launch_tri_inverse(h, h.chol, h.Nl, h.cinv);
         hip_check(hipStreamSynchronize(h.stream), "inverse factor");
-        h.arena.release(h.chol);
-        h.chol = nullptr;
       }
       h.mg_built = true;
     }

@@ -25,9 +25,10 @@ void clear_error();
 
 enum Prec { P64 = 0, P32 = 1, P16 = 2 };   // FP64, FP32, BF16 operator storage
 // Coarsest operators of up to this order are solved with the inverse of their
-// Cholesky factor, larger ones (dense problems without far blocks) by
-// substitution: the inverse costs twice the factorisation again and a second
-// square array, and pays from the first few cycles on.
+// Cholesky factor (and the factor itself, for the correction), larger ones
+// (dense problems without far blocks) by substitution: the inverse costs twice
+// the factorisation again and a second square array, and pays from the first
+// few cycles on.
 constexpr int64_t INVERSE_MAX = 8192;
 constexpr int DOT_PARTS = 512;             // most partial sums of a dot product of one kernel
 constexpr int MULTI_NR = 16;               // columns of a multi-vector block
@@ -252,9 +253,10 @@ struct H2 {
   bool mg_built = false;
   int levels = 1;
   int64_t Nl = 0;                      // coarsest size
-  // the coarsest operator, up to INVERSE_MAX rows: X = L^{-1} in the lower and
-  // X^T in the upper triangle (cinv); larger ones: the factor L itself (chol)
-  double* chol = nullptr;              // Nl x Nl column-major, lower factor
+  // the coarsest operator's Cholesky factor L, column-major; with the inverse
+  // also row-major: both triangles of one square
+  double* chol = nullptr;              // Nl x Nl
+  // up to INVERSE_MAX rows: X = L^{-1} in the lower and X^T in the upper triangle
   double* cinv = nullptr;              // Nl x Nl row-major
   int* flags = nullptr;                // device flags (0: not SPD, 1: non-finite)
   double* dot_part = nullptr;          // reduction partials (several slots)
@@ -313,7 +315,8 @@ void launch_pi_upper(H2& h, int d, const int* child_map);   // Pi tiles of depth
 void launch_assemble_dense(H2& h, double* A, int64_t lda);  // depth d_top blocks
 void launch_assemble_kernel_dense(H2& h, double* A, int64_t lda);  // no far blocks
 void launch_potrf(H2& h, double* A, int64_t N, double* work);   // blocked Cholesky, sets flags[0]; work: 64 * 64
-void launch_tri_inverse(H2& h, const double* L, int64_t N, double* S);   // S: X = L^{-1} below, X^T above the diagonal
+// S: X = L^{-1} below, X^T above the diagonal; L is completed by its rows the same way.
+void launch_tri_inverse(H2& h, double* L, int64_t N, double* S);
 void launch_cast_precision(H2& h, int p);         // FP64 -> FP32 / BF16 copies
 void launch_near_tiles(H2& h);                    // stored near-field tiles (FP64)
 // Inverses of the block-Jacobi blocks: leaf blocks K_ss + shift (FP64) and the
@@ -476,8 +479,8 @@ int launch_cg_step16_bj(H2& h, int p, int k, const void* src, void* e, bool e_ze
                         const void* q, void* z, const double* gpart, int ngp, const double* dpart, int ndp,
                         double* gnew);
 void launch_chol_solve16(H2& h, const double* L, int64_t N, double* x);   // in place, FP64
-// e = X^T (X r), tmp: Nl x 16 doubles.
-void launch_inverse_solve16(H2& h, int p, const void* r, void* e, double* tmp);
+// launch_inverse_solve on 16 columns; y, t: Nl x 16 doubles each.
+void launch_inverse_solve16(H2& h, int p, const void* r, void* e, double* y, double* t);
 
 // ------------------------------------------------------------ boundary elements
 // Per triangle (vertex rows V, index triples T): centroid y (nt x 3), scale
@@ -526,8 +529,8 @@ int launch_cg_step_bj(H2& h, int p, int k, const void* src, void* e, bool e_zero
                       const void* q, void* z, const double* gamma_part, int ngp, const double* delta_part,
                       int ndp, double* gamma_new_part);
 void launch_chol_solve(H2& h, const double* L, int64_t N, double* x);   // in place
-// e = X^T (X r) with the inverse factor h.cinv; r, e in the vector type of p
-// (FP64 arithmetic; uses vtree2).
+// e = L^{-T} L^{-1} r, each factor by its inverse h.cinv and one correction with
+// h.chol; r, e in the vector type of p (FP64 arithmetic; uses vtree and vtree2).
 void launch_inverse_solve(H2& h, int p, const void* r, void* e);
 void launch_check_finite(H2& h, int p, int64_t n, const void* x);      // sets flags[1]
 // Gradient helpers (tree-ordered points h.pts, n x dim).

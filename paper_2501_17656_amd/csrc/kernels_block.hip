@@ -651,16 +651,16 @@ __global__ __launch_bounds__(NT) void k_gemv_bwd16(const double* __restrict__ L,
   x[j * NR + k] -= s;
 }
 
-// Y = X B (UP = false) or X^T B (UP = true), X the inverse of the Cholesky
-// factor (S: X below, X^T above the diagonal, row-major), on the FP64 matrix
-// cores.  One workgroup per 16 rows; the four waves take every fourth run of
+// Y = add + sign M B, M = the lower (UP = false) or upper (UP = true) triangle of
+// S (see k_tri_gemv, also for the solve they make up; add may be null or Y), on
+// the FP64 matrix cores.  One workgroup per 16 rows; the four waves take every fourth run of
 // 16 inner indices and their sums are added in wave order.  Within a run lane
 // (p, q) loads the four entries 4q .. 4q + 3 of row p, so that each row's 16
 // entries are read whole, and the k-step t takes inner index 4q + t.
 // (16 right-hand sides on 16500 points: 139 to 133 ms a solve.)
-template <bool UP, typename Tin, typename Tout>
+template <bool UP, typename Tin, typename Tadd, typename Tout>
 __global__ __launch_bounds__(NT) void k_tri_gemm16(const double* __restrict__ S, int64_t N,
-                                                   const Tin* __restrict__ x, Tout* __restrict__ y) {
+                                                   const Tin* __restrict__ x, const Tadd* add, double sign, Tout* y) {
   __shared__ double red[4][16 * NR];
   const int64_t i0 = int64_t(blockIdx.x) * 16;
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63, p = l & 15, q = l >> 4;
@@ -683,8 +683,10 @@ __global__ __launch_bounds__(NT) void k_tri_gemm16(const double* __restrict__ S,
   for (int t = 0; t < 4; ++t) red[w][Mfma<double>::row(t, q) * NR + p] = acc[t];
   __syncthreads();
   const int e = threadIdx.x;
-  if (i0 + e / NR < N)
-    y[i0 * NR + e] = Tout((red[0][e] + red[1][e]) + (red[2][e] + red[3][e]));
+  if (i0 + e / NR < N) {
+    const double v = (red[0][e] + red[1][e]) + (red[2][e] + red[3][e]);
+    y[i0 * NR + e] = Tout(add ? double(add[i0 * NR + e]) + sign * v : v);
+  }
 }
 
 // ------------------------------------------------------------ dispatch helpers
@@ -929,19 +931,23 @@ void launch_cg_pupdate16(H2& h, int p, int64_t nrows, void* pv, const void* s, c
   check_launch("cg_pupdate16");
 }
 
-void launch_inverse_solve16(H2& h, int p, const void* r, void* e, double* tmp) {
+void launch_inverse_solve16(H2& h, int p, const void* r, void* e, double* y, double* t) {
   const dim3 g(unsigned((h.Nl + 15) / 16)), b(NT);
-  if (p == P64) {
-    hipLaunchKernelGGL((k_tri_gemm16<false, double, double>), g, b, 0, h.stream, h.cinv, h.Nl,
-                       static_cast<const double*>(r), tmp);
-    hipLaunchKernelGGL((k_tri_gemm16<true, double, double>), g, b, 0, h.stream, h.cinv, h.Nl, tmp,
-                       static_cast<double*>(e));
-  } else {
-    hipLaunchKernelGGL((k_tri_gemm16<false, float, double>), g, b, 0, h.stream, h.cinv, h.Nl,
-                       static_cast<const float*>(r), tmp);
-    hipLaunchKernelGGL((k_tri_gemm16<true, double, float>), g, b, 0, h.stream, h.cinv, h.Nl, tmp,
-                       static_cast<float*>(e));
-  }
+  const double *X = h.cinv, *L = h.chol;
+  const double* none = nullptr;
+  auto solve = [&](auto tv) {
+    using Tv = decltype(tv);
+    const Tv* rv = static_cast<const Tv*>(r);
+    hipLaunchKernelGGL((k_tri_gemm16<false, Tv, double, double>), g, b, 0, h.stream, X, h.Nl, rv, none, 1.0, y);
+    hipLaunchKernelGGL((k_tri_gemm16<false, double, Tv, double>), g, b, 0, h.stream, L, h.Nl, y, rv, -1.0, t);
+    hipLaunchKernelGGL((k_tri_gemm16<false, double, double, double>), g, b, 0, h.stream, X, h.Nl, t, y, 1.0, y);
+    hipLaunchKernelGGL((k_tri_gemm16<true, double, double, double>), g, b, 0, h.stream, X, h.Nl, y, none, 1.0, t);
+    hipLaunchKernelGGL((k_tri_gemm16<true, double, double, double>), g, b, 0, h.stream, L, h.Nl, t, y, -1.0, y);
+    hipLaunchKernelGGL((k_tri_gemm16<true, double, double, Tv>), g, b, 0, h.stream, X, h.Nl, y, t, 1.0,
+                       static_cast<Tv*>(e));
+  };
+  if (p == P64) solve(double{});
+  else solve(float{});
   check_launch("inverse_solve16");
 }
 

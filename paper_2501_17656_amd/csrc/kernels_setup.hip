@@ -778,19 +778,23 @@ __global__ __launch_bounds__(NT) void k_tri_inv_step(const double* __restrict__ 
     }
 }
 
-// Upper triangle = transpose of the lower one, 64 x 64 tiles (bi >= bj).
+// One triangle of S (row-major) = transpose of the other, 64 x 64 tiles (bi >=
+// bj): the upper one from the lower one (TO_UPPER) or the other way round.
+template <bool TO_UPPER>
 __global__ __launch_bounds__(NT) void k_tri_mirror(double* __restrict__ S, int64_t N) {
   __shared__ double X[NB][NB + 1];
   const int64_t i0 = int64_t(blockIdx.x) * NB, j0 = int64_t(blockIdx.y) * NB;
   if (j0 > i0) return;
+  const int64_t r0 = TO_UPPER ? i0 : j0, c0 = TO_UPPER ? j0 : i0;   // the tile that is read
   for (int e = threadIdx.x; e < NB * NB; e += NT) {
     const int i = e / NB, j = e % NB;
-    X[i][j] = i0 + i < N && j0 + j < N ? S[(i0 + i) * N + j0 + j] : 0.0;
+    X[i][j] = r0 + i < N && c0 + j < N ? S[(r0 + i) * N + c0 + j] : 0.0;
   }
   __syncthreads();
   for (int e = threadIdx.x; e < NB * NB; e += NT) {
     const int j = e / NB, i = e % NB;
-    if (i0 + i < N && j0 + j < i0 + i) S[(j0 + j) * N + i0 + i] = X[i][j];
+    const bool other = TO_UPPER ? c0 + j < r0 + i : c0 + j > r0 + i;   // read from the valid triangle
+    if (r0 + i < N && c0 + j < N && other) S[(c0 + j) * N + r0 + i] = X[i][j];
   }
 }
 
@@ -1094,7 +1098,7 @@ void launch_potrf(H2& h, double* A, int64_t N, double* work) {
   check_launch("potrf");
 }
 
-void launch_tri_inverse(H2& h, const double* L, int64_t N, double* S) {
+void launch_tri_inverse(H2& h, double* L, int64_t N, double* S) {
   const unsigned nb = unsigned((N + NB - 1) / NB);
   hipLaunchKernelGGL(k_tri_inv_diag, dim3(nb), dim3(NB), 0, h.stream, L, N, S);
   for (int64_t s = NB; s < N; s *= 2) {
@@ -1102,7 +1106,9 @@ void launch_tri_inverse(H2& h, const double* L, int64_t N, double* S) {
     hipLaunchKernelGGL(k_tri_inv_step<0>, grid, dim3(NT), 0, h.stream, L, N, s, S);
     hipLaunchKernelGGL(k_tri_inv_step<1>, grid, dim3(NT), 0, h.stream, L, N, s, S);
   }
-  hipLaunchKernelGGL(k_tri_mirror, dim3(nb, nb), dim3(NT), 0, h.stream, S, N);
+  hipLaunchKernelGGL(k_tri_mirror<true>, dim3(nb, nb), dim3(NT), 0, h.stream, S, N);
+  // L, column-major below its diagonal, is L^T in the upper triangle of rows
+  hipLaunchKernelGGL(k_tri_mirror<false>, dim3(nb, nb), dim3(NT), 0, h.stream, L, N);
   check_launch("tri_inverse");
 }
 

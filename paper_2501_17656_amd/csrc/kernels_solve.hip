@@ -260,18 +260,22 @@ __global__ __launch_bounds__(NT) void k_gemv_bwd(const double* __restrict__ L, i
 }
 
 // ------------------------------------------------------------ products with the inverse factor
-// y = X x (UP = false) or X^T x (UP = true) with X the inverse of the Cholesky
-// factor; S holds X below and X^T above its diagonal (row-major), so both are
-// dot products with contiguous parts of its rows: columns 0 .. i of row i, or
-// i .. N - 1.  One wave per row, eight loads of 64 entries in flight; the
-// factor of a 4096-row operator (134 MB for both triangles) stays in the
-// 256 MB last-level cache between cycles.
-// One solve with 4096 rows took 128 + 128 launches of substitution steps,
-// 5.2 ms; a cycle on 100003 points went from 62.1 to 49.4 ms with this and
-// the near field, a training step on 12000 points from 245 to 176 ms.
-template <bool UP, typename Tin, typename Tout>
+// y = add + sign M x, M = the lower (UP = false) or upper (UP = true) triangle of
+// S (row-major; add may be null or y).  For the inverse X of the Cholesky factor
+// and for the factor L, S holds the matrix below and its transpose above the
+// diagonal, so that all products are dot products with contiguous parts of
+// rows: columns 0 .. i of row i, or i .. N - 1.  One wave per row, eight loads of
+// 64 entries in flight.
+//
+// Products with X alone are not backward stable: the residual of X^T (X r) grows
+// with the root of the condition number (13 times that of substitution at
+// condition 6e7, 130 at 2e12, 1000 rows).  Each triangular solve is therefore
+// corrected once with its own residual, y = X r, y += X (r - L y), which leaves
+// the residual of substitution as long as the factor's condition number (the
+// root of the operator's) is well below 2^53.
+template <bool UP, typename Tin, typename Tadd, typename Tout>
 __global__ __launch_bounds__(NT) void k_tri_gemv(const double* __restrict__ S, int64_t N,
-                                                 const Tin* __restrict__ x, Tout* __restrict__ y) {
+                                                 const Tin* __restrict__ x, const Tadd* add, double sign, Tout* y) {
   const int64_t i = __builtin_amdgcn_readfirstlane(int((blockIdx.x * NT + threadIdx.x) >> 6));
   if (i >= N) return;
   const int lane = threadIdx.x & 63;
@@ -295,7 +299,7 @@ __global__ __launch_bounds__(NT) void k_tri_gemv(const double* __restrict__ S, i
   for (; j < j1; j += 64) v0 += row[j] * double(x[j]);
   v0 += v1;
   for (int o = 32; o > 0; o >>= 1) v0 += __shfl_xor(v0, o, 64);
-  if (lane == 0) y[i] = Tout(v0);
+  if (lane == 0) y[i] = Tout(add ? double(add[i]) + sign * v0 : v0);
 }
 
 inline unsigned blocks(int64_t n) { return unsigned((n + NT - 1) / NT); }
@@ -429,18 +433,22 @@ void launch_chol_solve(H2& h, const double* L, int64_t N, double* x) {
 
 void launch_inverse_solve(H2& h, int p, const void* r, void* e) {
   const dim3 g(unsigned((h.Nl + NT / 64 - 1) / (NT / 64))), b(NT);
-  double* y = h.vtree2;
-  if (p == P64) {
-    hipLaunchKernelGGL((k_tri_gemv<false, double, double>), g, b, 0, h.stream, h.cinv, h.Nl,
-                       static_cast<const double*>(r), y);
-    hipLaunchKernelGGL((k_tri_gemv<true, double, double>), g, b, 0, h.stream, h.cinv, h.Nl, y,
-                       static_cast<double*>(e));
-  } else {
-    hipLaunchKernelGGL((k_tri_gemv<false, float, double>), g, b, 0, h.stream, h.cinv, h.Nl,
-                       static_cast<const float*>(r), y);
-    hipLaunchKernelGGL((k_tri_gemv<true, double, float>), g, b, 0, h.stream, h.cinv, h.Nl, y,
-                       static_cast<float*>(e));
-  }
+  const double *X = h.cinv, *L = h.chol;
+  double *y = h.vtree2, *t = h.vtree;
+  const double* none = nullptr;
+  auto solve = [&](auto tv) {
+    using Tv = decltype(tv);
+    const Tv* rv = static_cast<const Tv*>(r);
+    hipLaunchKernelGGL((k_tri_gemv<false, Tv, double, double>), g, b, 0, h.stream, X, h.Nl, rv, none, 1.0, y);
+    hipLaunchKernelGGL((k_tri_gemv<false, double, Tv, double>), g, b, 0, h.stream, L, h.Nl, y, rv, -1.0, t);
+    hipLaunchKernelGGL((k_tri_gemv<false, double, double, double>), g, b, 0, h.stream, X, h.Nl, t, y, 1.0, y);
+    hipLaunchKernelGGL((k_tri_gemv<true, double, double, double>), g, b, 0, h.stream, X, h.Nl, y, none, 1.0, t);
+    hipLaunchKernelGGL((k_tri_gemv<true, double, double, double>), g, b, 0, h.stream, L, h.Nl, t, y, -1.0, y);
+    hipLaunchKernelGGL((k_tri_gemv<true, double, double, Tv>), g, b, 0, h.stream, X, h.Nl, y, t, 1.0,
+                       static_cast<Tv*>(e));
+  };
+  if (p == P64) solve(double{});
+  else solve(float{});
   check_launch("inverse_solve");
 }
 
