@@ -687,86 +687,114 @@ h2mg_status set_near_quadrature(H2& h, const double* qy_user, const double* qu_u
   return st;
 }
 
-h2mg_status setup_mg(H2& h, int precision_mask) {
+namespace {
+
+// The restricted operators and the coarsest factor.  What a failed attempt has
+// allocated is given back.
+h2mg_status build_hierarchy(H2& h) {
+  const size_t mark = h.arena.ptrs.size();
+  auto give_back = [&] {
+    (void)hipStreamSynchronize(h.stream);
+    while (h.arena.ptrs.size() > mark) h.arena.release(h.arena.ptrs.back().first);
+    h.chol = h.cinv = nullptr;
+  };
   try {
-    if (!h.mg_built) {
-      if (h.d_top >= 0) {
-        launch_pi_leaf(h);
-        // child block lookup: (row gid, col gid) -> block id.  The coupling
-        // and close blocks of a depth are each sorted by (row, column) (the
-        // plan sorts its pair lists), so a binary search finds a child.
-        auto key = [](int a, int b) { return (int64_t(a) << 32) | uint32_t(b); };
-        auto find_block = [&](int first, int count, int64_t k) {
-          int lo = first, hi = first + count;
-          while (lo < hi) {
-            const int mid = lo + (hi - lo) / 2;
-            if (key(h.blk_row_h[mid], h.blk_col_h[mid]) < k) lo = mid + 1;
-            else hi = mid;
-          }
-          return lo < first + count && key(h.blk_row_h[lo], h.blk_col_h[lo]) == k ? lo : -1;
+    if (h.d_top >= 0) {
+      launch_pi_leaf(h);
+      // child block lookup: (row gid, col gid) -> block id.  The coupling
+      // and close blocks of a depth are each sorted by (row, column) (the
+      // plan sorts its pair lists), so a binary search finds a child.
+      auto key = [](int a, int b) { return (int64_t(a) << 32) | uint32_t(b); };
+      auto find_block = [&](int first, int count, int64_t k) {
+        int lo = first, hi = first + count;
+        while (lo < hi) {
+          const int mid = lo + (hi - lo) / 2;
+          if (key(h.blk_row_h[mid], h.blk_col_h[mid]) < k) lo = mid + 1;
+          else hi = mid;
+        }
+        return lo < first + count && key(h.blk_row_h[lo], h.blk_col_h[lo]) == k ? lo : -1;
+      };
+      // all maps first (host work that may throw), then the launches
+      std::vector<std::vector<int>> host_maps;   // alive until the copies are done
+      for (int d = h.L - 1; d >= h.d_top; --d) {
+        auto child = [&](int cs, int ct) {
+          const int64_t k = key(cs, ct);
+          int b = find_block(h.s_first[d + 1], h.s_count[d + 1], k);
+          if (b < 0) b = find_block(h.p_first[d + 1], h.p_count[d + 1], k);
+          if (b < 0) throw std::runtime_error("child block not found");
+          return b;
         };
-        // all maps first (host work that may throw), then the launches
-        std::vector<std::vector<int>> host_maps;   // alive until the copies are done
-        for (int d = h.L - 1; d >= h.d_top; --d) {
-          auto child = [&](int cs, int ct) {
-            const int64_t k = key(cs, ct);
-            int b = find_block(h.s_first[d + 1], h.s_count[d + 1], k);
-            if (b < 0) b = find_block(h.p_first[d + 1], h.p_count[d + 1], k);
-            if (b < 0) throw std::runtime_error("child block not found");
-            return b;
-          };
-          host_maps.emplace_back();
-          std::vector<int>& cmap = host_maps.back();
-          cmap.reserve(size_t(h.p_count[d]) * 4);
-          for (int b = h.p_first[d]; b < h.p_first[d] + h.p_count[d]; ++b) {
-            const int gs = h.blk_row_h[b], gt = h.blk_col_h[b];
-            for (int a = 0; a < 2; ++a)
-              for (int bb = 0; bb < 2; ++bb) {
-                const int cs = 2 * gs + 1 + a, ct = 2 * gt + 1 + bb;
-                cmap.push_back(cs <= ct ? child(cs, ct) : -child(ct, cs) - 1);
-              }
-          }
+        host_maps.emplace_back();
+        std::vector<int>& cmap = host_maps.back();
+        cmap.reserve(size_t(h.p_count[d]) * 4);
+        for (int b = h.p_first[d]; b < h.p_first[d] + h.p_count[d]; ++b) {
+          const int gs = h.blk_row_h[b], gt = h.blk_col_h[b];
+          for (int a = 0; a < 2; ++a)
+            for (int bb = 0; bb < 2; ++bb) {
+              const int cs = 2 * gs + 1 + a, ct = 2 * gt + 1 + bb;
+              cmap.push_back(cs <= ct ? child(cs, ct) : -child(ct, cs) - 1);
+            }
         }
-        std::vector<int*> maps;
-        for (int d = h.L - 1, k = 0; d >= h.d_top; --d, ++k) {
-          maps.push_back(upload(h, host_maps[k]));
-          // stream order: depth d reads the blocks depth d + 1 wrote
-          launch_pi_upper(h, d, maps.back());
-        }
-        hip_check(hipStreamSynchronize(h.stream), "pi_upper");
-        for (int* m : maps) h.arena.release(m);
-        h.Nl = int64_t(1 << h.d_top) * h.r;
-        h.levels = h.L - h.d_top + 2;
-      } else {
-        if (h.n > 32768)
-          return fail(H2MG_ERR_INVALID_ARG,
-                      "no far blocks: the dense direct solve is limited to n <= 32768");
-        h.Nl = h.n;
-        h.levels = 1;
       }
-      double* work = h.arena.make<double>(64 * 64);
-      h.chol = h.arena.make<double>(size_t(h.Nl) * h.Nl);
-      hip_check(hipMemsetAsync(h.chol, 0, size_t(h.Nl) * h.Nl * sizeof(double), h.stream), "memset");
-      if (h.d_top >= 0) launch_assemble_dense(h, h.chol, h.Nl);
-      else launch_assemble_kernel_dense(h, h.chol, h.Nl);
-      hip_check(hipMemsetAsync(h.flags, 0, 4 * sizeof(int), h.stream), "memset");
-      launch_potrf(h, h.chol, h.Nl, work);
-      int flags[4];
-      hip_check(hipMemcpyAsync(flags, h.flags, sizeof(flags), hipMemcpyDeviceToHost, h.stream), "flags");
-      hip_check(hipStreamSynchronize(h.stream), "setup_mg");
-      h.arena.release(work);
-      if (flags[0]) {
-        h.arena.release(h.chol);
-        h.chol = nullptr;
-        return fail(H2MG_ERR_NOT_SPD, "the coarsest operator (order %lld) is not positive definite",
-                    (long long)h.Nl);
+      std::vector<int*> maps;
+      for (int d = h.L - 1, k = 0; d >= h.d_top; --d, ++k) {
+        maps.push_back(upload(h, host_maps[k]));
+        // stream order: depth d reads the blocks depth d + 1 wrote
+        launch_pi_upper(h, d, maps.back());
       }
-      if (h.Nl <= INVERSE_MAX) {
+      hip_check(hipStreamSynchronize(h.stream), "pi_upper");
+      for (int* m : maps) h.arena.release(m);
+      h.Nl = int64_t(1 << h.d_top) * h.r;
+      h.levels = h.L - h.d_top + 2;
+    } else {
+      if (h.n > 32768)
+        return fail(H2MG_ERR_INVALID_ARG,
+                    "no far blocks: the dense direct solve is limited to n <= 32768");
+      h.Nl = h.n;
+      h.levels = 1;
+    }
+    double* work = h.arena.make<double>(64 * 64);
+    h.chol = h.arena.make<double>(size_t(h.Nl) * h.Nl);
+    hip_check(hipMemsetAsync(h.chol, 0, size_t(h.Nl) * h.Nl * sizeof(double), h.stream), "memset");
+    if (h.d_top >= 0) launch_assemble_dense(h, h.chol, h.Nl);
+    else launch_assemble_kernel_dense(h, h.chol, h.Nl);
+    hip_check(hipMemsetAsync(h.flags, 0, 4 * sizeof(int), h.stream), "memset");
+    launch_potrf(h, h.chol, h.Nl, work);
+    int flags[4];
+    hip_check(hipMemcpyAsync(flags, h.flags, sizeof(flags), hipMemcpyDeviceToHost, h.stream), "flags");
+    hip_check(hipStreamSynchronize(h.stream), "setup_mg");
+    h.arena.release(work);
+    if (flags[0]) {
+      give_back();
+      return fail(H2MG_ERR_NOT_SPD, "the coarsest operator (order %lld) is not positive definite",
+                  (long long)h.Nl);
+    }
+    if (h.Nl <= INVERSE_MAX) {
+      try {
         h.cinv = h.arena.make<double>(size_t(h.Nl) * h.Nl);
+      } catch (const std::bad_alloc&) {
+        // no room for it: the factor alone serves, by substitution
+      }
+      if (h.cinv) {
         launch_tri_inverse(h, h.chol, h.Nl, h.cinv);
         hip_check(hipStreamSynchronize(h.stream), "inverse factor");
       }
-      h.mg_built = true;
+    }
+    h.mg_built = true;
+  } catch (...) {
+    give_back();
+    throw;
+  }
+  return H2MG_OK;
+}
+
+}  // namespace
+
+h2mg_status setup_mg(H2& h, int precision_mask) {
+  try {
+    if (!h.mg_built) {
+      const h2mg_status st = build_hierarchy(h);
+      if (st != H2MG_OK) return st;
     }
     for (int p = P32; p <= P16; ++p) {
       if (!(precision_mask & (1 << p)) || h.prec[p].ready) continue;
