@@ -166,15 +166,26 @@ struct KernelParams {
   int kind;
   int deriv;
   double inv_l;        // 1 / l
-  double inv_2l2;      // 1 / (2 l^2)
+  // k = f(z) 2^(c s) with s = r, or r^2 for the Gaussian: the constants of both,
+  // each rounded once from extended precision
+  double c;            // -log2(e) / l; Gaussian -log2(e) / (2 l^2); Matern -sqrt(3) log2(e) / l
+  double z;            // z / s: 1 / l; Matern sqrt(3) / l
+  double far;          // the s from which on 2^(c s) is 0 in FP64: 1100 / -c
   double shift;
+};
+// What a kernel evaluation needs of them, in its precision.
+template <typename T>
+struct KernelConst {
+  T inv_l, c, z, far;
+  __host__ __device__ explicit KernelConst(const KernelParams& kp)
+      : inv_l(T(kp.inv_l)), c(T(kp.c)), z(T(kp.z)), far(T(kp.far)) {}
 };
 
 // Square root, reciprocal square root and exponential of the kernels.  The
 // products that evaluate their close blocks spend nearly all their time here
 // (FP64 vector issue), and the arguments are known: x = r^2 >= 0 and an
 // exponent <= 0.  So nothing is spent on signs, special cases and subnormal
-// scaling: a Matern entry with its distance and its two sums issues 33
+// scaling: a Matern entry with its distance and its two sums issues 32
 // operations, most of them FP64, instead of 66 with the library's sqrt and exp
 // (a product at N = 131072, 3D, close blocks evaluated: 3453 to 2398 us).
 //   sqrt_nn: from the hardware's reciprocal square root y (about 2^-24 off in
@@ -182,12 +193,13 @@ struct KernelParams {
 //     e g^2: sqrt(x) = g + d y (1/2 + 3/8 e) + O(e^3), within 0.501 ulp.
 //   rsqrt_nn: Newton's iteration.
 //     sqrt_nn raises x to MIN_R2, so that r = 0 gives a root too small to matter.
-//   exp2_np(w) = 2^w, w <= 0: n = rint(w) and f = w - n are exact, 2^f =
-//     1 + f q(f) with q the degree-10 interpolant of (2^f - 1) / f in the
-//     Chebyshev nodes of [-1/2, 1/2] (2e-17 off), scaled by 2^n exactly;
-//     2^0 is exactly 1.  w is raised to -1100, where 2^w is 0 (an overflowed
-//     r^2, whose root is a NaN here, ends up there too).  In FP32 the
-//     hardware's 2^w (1 ulp).
+//   exp2_prod(s, c) = 2^(c s), c s <= 0: n = rint(c s), f = c s - n with one
+//     rounding (the product's own rounding, up to |c s| times larger, does not
+//     occur), 2^f = 1 + f q(f) with q the degree-10 interpolant of (2^f - 1) / f
+//     in the Chebyshev nodes of [-1/2, 1/2] (2e-17 off), scaled by 2^n exactly;
+//     2^0 is exactly 1.  s is lowered to where 2^(c s) is 0 (an overflowed r^2,
+//     whose root is a NaN here, ends up there too).  In FP32 the hardware's 2^w
+//     (1 ulp) of the rounded product.
 template <typename T> constexpr T MIN_R2 = T(0);
 template <> inline constexpr double MIN_R2<double> = 1e-290;
 template <> inline constexpr float MIN_R2<float> = 1e-36f;
@@ -221,10 +233,10 @@ __device__ inline float rsqrt_nn(float x) {
   const float y = __builtin_amdgcn_rsqf(x);
   return __builtin_fmaf(0.5f * y, __builtin_fmaf(-x * y, y, 1.0f), y);
 }
-__device__ inline double exp2_np(double w) {
+__device__ inline double exp2_prod(double s, double c) {
   constexpr double MAGIC = 6755399441055744.0;   // 1.5 * 2^52: w + MAGIC holds rint(w) in its low bits
-  const double t = w + MAGIC;
-  const double f = w - (t - MAGIC);
+  const double t = __builtin_fma(s, c, MAGIC);
+  const double f = __builtin_fma(s, c, -(t - MAGIC));
   double q = 4.4549605981865186e-10;
   q = __builtin_fma(q, f, 7.072585949269223e-09);
   q = __builtin_fma(q, f, 1.0178062445845774e-07);
@@ -238,19 +250,17 @@ __device__ inline double exp2_np(double w) {
   q = __builtin_fma(q, f, 0.6931471805599453);
   return __builtin_ldexp(__builtin_fma(q, f, 1.0), int(__double2loint(t)));
 }
-__device__ inline float exp2_np(float w) { return __builtin_amdgcn_exp2f(w); }
-__device__ inline double raise_to(double w, double lo) { return __builtin_fmax(w, lo); }
-__device__ inline float raise_to(float w, float lo) { return __builtin_fmaxf(w, lo); }
+__device__ inline float exp2_prod(float s, float c) { return __builtin_amdgcn_exp2f(s * c); }
+__device__ inline double lower_to(double s, double hi) { return __builtin_fmin(s, hi); }
+__device__ inline float lower_to(float s, float hi) { return __builtin_fminf(s, hi); }
 
 // k (or its derivative) as a function of the squared distance (no shift),
-// for a kernel fixed at compile time.  The exponent is formed in base 2 with
-// one rounding of the constant and one of the product.  MINED: r2 is finite
-// and at least MIN_R2 (r = 0 included, so not for the kernels that ask for
-// r2 = 0), and the exponent above -2^30: nothing is raised.
+// for a kernel fixed at compile time.  MINED: r2 is finite and at least MIN_R2
+// (r = 0 included, so not for the kernels that ask for r2 = 0), and the exponent
+// above -2^30: nothing is lowered.
 template <int KIND, int DERIV, typename T, bool MINED = false>
-__device__ inline T kernel_fixed(T inv_l, T inv_2l2, T r2) {
-  auto raise = [](T w) { return MINED ? w : raise_to(w, T(-1100)); };
-  constexpr T LOG2E = T(1.4426950408889634), LN2 = T(0.6931471805599453);
+__device__ inline T kernel_fixed(const KernelConst<T>& k, T r2) {
+  auto lower = [&](T s) { return MINED ? s : lower_to(s, k.far); };
   if constexpr (KIND == KER_LAPLACE) {
     // 1 / (4 pi r); 0 at r = 0 (the matrix supplies its own diagonal)
     return r2 == T(0) ? T(0) : T(0.07957747154594767) * rsqrt_nn(r2);
@@ -259,23 +269,23 @@ __device__ inline T kernel_fixed(T inv_l, T inv_2l2, T r2) {
     if (r2 == T(0)) return T(0);
   }
   if constexpr (KIND == KER_GAUSS) {
-    const T e = exp2_np(raise(r2 * (-inv_2l2 * LOG2E)));
+    const T s = lower(r2);
+    const T e = exp2_prod(s, k.c);
     if constexpr (DERIV == DER_NONE) return e;
-    else if constexpr (DERIV == DER_LENGTH) return r2 * (inv_l * inv_l * inv_l) * e;
-    else return -inv_l * inv_l * e;
+    else if constexpr (DERIV == DER_LENGTH) return s * (k.inv_l * k.inv_l * k.inv_l) * e;
+    else return -k.inv_l * k.inv_l * e;
   } else if constexpr (KIND == KER_EXP) {
-    const T rr = sqrt_nn<MINED>(r2);
-    const T e = exp2_np(raise(rr * (-inv_l * LOG2E)));
+    const T rr = lower(sqrt_nn<MINED>(r2));
+    const T e = exp2_prod(rr, k.c);
     if constexpr (DERIV == DER_NONE) return e;
-    else if constexpr (DERIV == DER_LENGTH) return rr * (inv_l * inv_l) * e;
-    else return -inv_l * e / rr;
+    else if constexpr (DERIV == DER_LENGTH) return rr * (k.inv_l * k.inv_l) * e;
+    else return -k.inv_l * e / rr;
   } else {
-    const T rr = sqrt_nn<MINED>(r2);
-    const T w = raise(rr * (-inv_l * (T(1.7320508075688772) * LOG2E)));   // -z log2(e)
-    const T e = exp2_np(w);
-    if constexpr (DERIV == DER_NONE) return (T(1) - w * LN2) * e;
-    else if constexpr (DERIV == DER_LENGTH) return (w * w) * (LN2 * LN2 * inv_l) * e;
-    else return T(-3) * inv_l * inv_l * e;
+    const T rr = lower(sqrt_nn<MINED>(r2));
+    const T e = exp2_prod(rr, k.c);
+    if constexpr (DERIV == DER_NONE) return (T(1) + rr * k.z) * e;
+    else if constexpr (DERIV == DER_LENGTH) return (rr * k.z) * (rr * k.z) * k.inv_l * e;
+    else return T(-3) * k.inv_l * k.inv_l * e;
   }
 }
 
@@ -295,21 +305,12 @@ __host__ __device__ inline void dispatch_kernel(int kind, int deriv, F&& f) {
   else d(std::integral_constant<I, KER_MATERN32>{});
 }
 
-template <typename T>
-__device__ inline T kernel_r2_t(int kind, int deriv, T inv_l, T inv_2l2, T r2) {
-  T v = T(0);
-  dispatch_kernel(kind, deriv, [&](auto kc, auto dc) {
-    v = kernel_fixed<decltype(kc)::value, decltype(dc)::value, T>(inv_l, inv_2l2, r2);
+__device__ inline double kernel_r2(const KernelParams& kp, double r2) {
+  double v = 0.0;
+  dispatch_kernel(kp.kind, kp.deriv, [&](auto kc, auto dc) {
+    v = kernel_fixed<decltype(kc)::value, decltype(dc)::value, double>(KernelConst<double>(kp), r2);
   });
   return v;
-}
-
-__device__ inline double kernel_r2(const KernelParams& kp, double r2) {
-  return kernel_r2_t<double>(kp.kind, kp.deriv, kp.inv_l, kp.inv_2l2, r2);
-}
-
-__device__ inline float kernel_r2(const KernelParams& kp, float r2) {
-  return kernel_r2_t<float>(kp.kind, kp.deriv, float(kp.inv_l), float(kp.inv_2l2), r2);
 }
 
 // Per-point scale s (on rows and columns) and diagonal d of the scaled form

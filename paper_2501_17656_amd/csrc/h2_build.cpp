@@ -232,7 +232,14 @@ h2mg_status build_h2(const double* points_dev, int64_t n, int dim, const h2mg_ke
     h.kp.kind = kernel->kind;
     h.kp.deriv = kernel->derivative;
     h.kp.inv_l = 1.0 / kernel->length_scale;
-    h.kp.inv_2l2 = 1.0 / (2.0 * kernel->length_scale * kernel->length_scale);
+    {
+      const long double l = kernel->length_scale, log2e = 1.442695040888963407359924681001892137L;
+      const long double z = h.kp.kind == KER_MATERN32 ? std::sqrt(3.0L) / l : 1.0L / l;
+      const long double c = h.kp.kind == KER_GAUSS ? -log2e / (2.0L * l * l) : -log2e * z;
+      h.kp.c = double(c);
+      h.kp.z = double(z);
+      h.kp.far = double(-1100.0L / c);
+    }
     h.kp.shift = kernel->shift;
 
     // ---- geometry
@@ -369,9 +376,9 @@ h2mg_status build_h2(const double* points_dev, int64_t n, int dim, const h2mg_ke
       nf.ld = (h.leaf_max + 7) / 8 * 8;
       double diam2 = 0.0;
       for (int a = 0; a < dim; ++a) diam2 += (P.hi[0][a] - P.lo[0][a]) * (P.hi[0][a] - P.lo[0][a]);
-      const double most = h.kp.kind == KER_GAUSS ? diam2 * h.kp.inv_2l2 : std::sqrt(3.0 * diam2) * h.kp.inv_l;
-      // log2(e) < 1.5; and MIN_R2 and the largest r^2 are within FP32's range
-      nf.mined = 1.5 * most < 536870912.0 && diam2 < 1e37 && h.kp.inv_l < 1e8;
+      const double most = (h.kp.kind == KER_GAUSS ? diam2 : std::sqrt(diam2)) * -h.kp.c;
+      // and MIN_R2 and the largest r^2 are within FP32's range
+      nf.mined = most < 536870912.0 && diam2 < 1e37 && h.kp.inv_l < 1e8;
       for (int p = 0; p < nf.npairs; ++p)
         h.near_evals += int64_t(loff[prow[p] + 1] - loff[prow[p]]) * (loff[pcol[p] + 1] - loff[pcol[p]]);
     }

@@ -315,7 +315,7 @@ struct StageEval {
   template <typename Put>
   __device__ __forceinline__ void store(int, const Regs& R, Put& put) const {
     const int w = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6)), j = threadIdx.x & 63;
-    const Tv inv_l = Tv(kp.inv_l), inv_2l2 = Tv(kp.inv_2l2);
+    const KernelConst<Tv> kc(kp);
     const bool colok = j < R.nc;
 #pragma unroll 4
     for (int i = w; i < R.nr; i += 4) {
@@ -328,7 +328,7 @@ struct StageEval {
         const Tv dx = Tv((d < dim ? pts[gi * dim + d] : 0.0) - R.pc[d]);
         r2 += dx * dx;
       }
-      Tv e = kernel_fixed<KIND, DERIV, Tv>(inv_l, inv_2l2, r2);
+      Tv e = kernel_fixed<KIND, DERIV, Tv>(kc, r2);
       if (ps.s) e *= Tv(ps.s[gi] * R.sc);
       if (R.rs == R.cs && i == j) e += Tv(ps.d ? ps.d[gi] : kp.shift);
       put(i, j, colok ? e : Tv(0));

@@ -2,7 +2,7 @@
 // close leaf pairs), one vector, the entries formed from the points in every
 // product.
 //
-// FP64 vector issue bounds it (33 operations an entry), so what counts
+// FP64 vector issue bounds it (32 operations an entry), so what counts
 // is that no entry is formed for padding and that nothing else is issued.
 //   * One wave per task: a row leaf s and a run of its close pairs (s <= t),
 //     in chunks of up to 64 rows.  No LDS and no barrier, so the waves of a
@@ -74,7 +74,7 @@ struct NearIn {
 // Rows [rt, rt + nrow) of leaf sl (U >= nrow / 8) against the pairs [p0, p1).
 // first: this wave has not written these pairs' column sums yet.  MINED: the
 // squared distance starts at MIN_R2 (its first addition is an FMA, so that
-// costs nothing) and the kernel need not raise its arguments.
+// costs nothing) and the kernel need not bound its arguments.
 template <int U, int DIM, bool MINED, typename Tv, int KIND, int DERIV>
 __device__ __forceinline__ void near_rows(const NearIn<Tv>& A, int task, int part, int sl, int p0, int p1, int rt,
                                           int nrow, bool first) {
@@ -106,7 +106,7 @@ __device__ __forceinline__ void near_rows(const NearIn<Tv>& A, int task, int par
   int tl = A.pair_col[p0];
   int t0 = A.leaf_off[tl], nt = A.leaf_off[tl + 1] - t0;
   load(t0, nt, 0);
-  const Tv inv_l = Tv(A.kp.inv_l), inv_2l2 = Tv(A.kp.inv_2l2);
+  const KernelConst<Tv> kc(A.kp);
   for (int p = p0; p < p1; ++p) {
     const int slot = A.pair_slot[p];
     Tv* dst = slot < 0 ? nullptr : A.colpart + (int64_t(slot) * A.nsplit + part) * A.ld;
@@ -138,7 +138,7 @@ __device__ __forceinline__ void near_rows(const NearIn<Tv>& A, int task, int par
           if (a == 0) r2 = MINED ? __builtin_fma(dx, dx, double(MIN_R2<Tv>)) : dx * dx;
           else r2 = __builtin_fma(dx, dx, r2);
         }
-        const Tv k = kernel_fixed<KIND, DERIV, Tv, MINED>(inv_l, inv_2l2, Tv(r2));
+        const Tv k = kernel_fixed<KIND, DERIV, Tv, MINED>(kc, Tv(r2));
         racc[u] += k * xj;
         cacc += k * xi[u];
       }

@@ -435,7 +435,7 @@ struct LeafAcc {
       }
     const bool self = diag && i == j;
     if constexpr (KIND >= 0)
-      return scaled_entry(kernel_fixed<KIND, DER_NONE, double>(kp.inv_l, kp.inv_2l2, r2), s0 + i, t0 + j,
+      return scaled_entry(kernel_fixed<KIND, DER_NONE, double>(KernelConst<double>(kp), r2), s0 + i, t0 + j,
                           self, ps, kp.shift);
     else
       return near_entry(kp, ps, dim, r2, s0 + i, t0 + j, self);

@@ -1,0 +1,71 @@
+"""Roundings and range of the kernel entries.  One leaf and no far block, so the product with a unit
+vector is a column of the kernel matrix: point 0 at the origin, the others on an axis."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2501_17656_amd import H2Matrix
+
+pytestmark = pytest.mark.gpu
+
+LOG2E = np.float64(1.4426950408889634)
+
+
+def column(r, kernel, ell, path="fp64", derivative="value", diag=None):
+    """Entries k(r) as a product with the unit vector of point 0 gives them (r[0] = 0: with the diagonal)."""
+    pts = np.zeros((r.size, 3))
+    pts[:, 0] = r
+    kw = {"diag": torch.full((r.size,), diag, dtype=torch.float64, device="cuda")} if diag else {}
+    shift = 1.0 if derivative == "value" and not diag else 0.0
+    g = H2Matrix(torch.from_numpy(pts).cuda(), kernel, ell, shift, 256, 0.7, 3, derivative=derivative, **kw)
+    e0 = torch.zeros(r.size, dtype=torch.float64, device="cuda")
+    e0[0] = 1.0
+    if path == "fp64":
+        k = g.matvec(e0)
+    elif path == "fp64_block":
+        k = g.matvec_multi(torch.stack([e0, 2 * e0], 1).contiguous())[:, 0]
+    else:
+        g.setup(["fp64", "fp32"])
+        k = g.level_apply(1, e0, precision="fp32")
+    g.close()
+    return k.cpu().numpy()
+
+
+def exponent(kernel, r, ell):
+    """The exponent z of the kernel, and what a relative error of z is in the entry."""
+    r, ell = r.astype(np.longdouble), np.longdouble(ell)
+    if kernel == "gauss":
+        z = r * r / (2 * ell * ell)
+    else:
+        z = r / ell * (np.sqrt(np.longdouble(3)) if kernel == "matern32" else 1)
+    return z, (z * z / (1 + z) if kernel == "matern32" else z)
+
+
+def value(kernel, z):
+    return (1 + z) * np.exp(-z) if kernel == "matern32" else np.exp(-z)
+
+
+@pytest.mark.parametrize("path", ["fp64", "fp32", "fp64_block"])
+@pytest.mark.parametrize("kernel", ["exp", "gauss", "matern32"])
+def test_exponent_coefficient_is_rounded_once(kernel, path):
+    """The factor of the distance in the exponent is off by one rounding at most (u), also for length
+    scales for which the product of a rounded 1 / l (or 1 / (2 l^2)) with a rounded log2(e) is off by
+    nearly two and more.  The other roundings of an entry have no sign: over 255 entries their mean is
+    below a quarter of u (each is at most u, the exponential's twice that over z >= 10)."""
+    ft, u = (np.float32, 2.0 ** -24) if path == "fp32" else (np.float64, 2.0 ** -53)
+    ells = 0.1 * (1 + 1e-3 * np.arange(400))
+    if kernel == "gauss":
+        twice = ft(1.0 / (2.0 * ells * ells)) * ft(LOG2E)
+        once = np.log2(np.exp(np.longdouble(1))) / (2 * ells.astype(np.longdouble) ** 2)
+    else:
+        c = np.sqrt(np.longdouble(3)) if kernel == "matern32" else np.longdouble(1)
+        twice = ft(1.0 / ells) * ft(c.astype(np.float64) * LOG2E)
+        once = c * np.log2(np.exp(np.longdouble(1))) / ells.astype(np.longdouble)
+    off = np.abs(twice / once - 1).astype(np.float64)
+    for ell in ells[np.argsort(off)[-3:]]:
+        z0 = np.geomspace(10, 40, 255)
+        s = {"gauss": np.sqrt(2 * z0), "exp": z0, "matern32": z0 / 3.0 ** 0.5}[kernel]
+        r = np.concatenate([[0.0], ell * s])
+        z, sens = exponent(kernel, r[1:], ell)
+        err = (column(r, kernel, ell, path)[1:] / value(kernel, z) - 1) / sens
+        assert abs(float(err.mean())) <= 1.25 * u, (ell, float(err.mean()) / u)
