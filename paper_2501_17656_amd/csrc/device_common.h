@@ -199,7 +199,8 @@ struct KernelConst {
 //     in the Chebyshev nodes of [-1/2, 1/2] (2e-17 off), scaled by 2^n exactly;
 //     2^0 is exactly 1.  s is lowered to where 2^(c s) is 0 (an overflowed r^2,
 //     whose root is a NaN here, ends up there too).  In FP32 the hardware's 2^w
-//     (1 ulp) of the rounded product.
+//     (1 ulp) of the rounded product; it flushes subnormal results, which are
+//     scaled into its range unless there are none (NORMAL).
 template <typename T> constexpr T MIN_R2 = T(0);
 template <> inline constexpr double MIN_R2<double> = 1e-290;
 template <> inline constexpr float MIN_R2<float> = 1e-36f;
@@ -233,6 +234,7 @@ __device__ inline float rsqrt_nn(float x) {
   const float y = __builtin_amdgcn_rsqf(x);
   return __builtin_fmaf(0.5f * y, __builtin_fmaf(-x * y, y, 1.0f), y);
 }
+template <bool NORMAL = false>
 __device__ inline double exp2_prod(double s, double c) {
   constexpr double MAGIC = 6755399441055744.0;   // 1.5 * 2^52: w + MAGIC holds rint(w) in its low bits
   const double t = __builtin_fma(s, c, MAGIC);
@@ -250,14 +252,20 @@ __device__ inline double exp2_prod(double s, double c) {
   q = __builtin_fma(q, f, 0.6931471805599453);
   return __builtin_ldexp(__builtin_fma(q, f, 1.0), int(__double2loint(t)));
 }
-__device__ inline float exp2_prod(float s, float c) { return __builtin_amdgcn_exp2f(s * c); }
+template <bool NORMAL = false>
+__device__ inline float exp2_prod(float s, float c) {
+  const float w = s * c;
+  if constexpr (NORMAL) return __builtin_amdgcn_exp2f(w);
+  const bool small = w < -126.0f;
+  return __builtin_amdgcn_exp2f(small ? w + 64.0f : w) * (small ? 0x1p-64f : 1.0f);
+}
 __device__ inline double lower_to(double s, double hi) { return __builtin_fmin(s, hi); }
 __device__ inline float lower_to(float s, float hi) { return __builtin_fminf(s, hi); }
 
 // k (or its derivative) as a function of the squared distance (no shift),
 // for a kernel fixed at compile time.  MINED: r2 is finite and at least MIN_R2
 // (r = 0 included, so not for the kernels that ask for r2 = 0), and the exponent
-// above -2^30: nothing is lowered.
+// above -2^30, in FP32 above -126: nothing is lowered or scaled.
 template <int KIND, int DERIV, typename T, bool MINED = false>
 __device__ inline T kernel_fixed(const KernelConst<T>& k, T r2) {
   auto lower = [&](T s) { return MINED ? s : lower_to(s, k.far); };
@@ -270,19 +278,19 @@ __device__ inline T kernel_fixed(const KernelConst<T>& k, T r2) {
   }
   if constexpr (KIND == KER_GAUSS) {
     const T s = lower(r2);
-    const T e = exp2_prod(s, k.c);
+    const T e = exp2_prod<MINED>(s, k.c);
     if constexpr (DERIV == DER_NONE) return e;
     else if constexpr (DERIV == DER_LENGTH) return s * (k.inv_l * k.inv_l * k.inv_l) * e;
     else return -k.inv_l * k.inv_l * e;
   } else if constexpr (KIND == KER_EXP) {
     const T rr = lower(sqrt_nn<MINED>(r2));
-    const T e = exp2_prod(rr, k.c);
+    const T e = exp2_prod<MINED>(rr, k.c);
     if constexpr (DERIV == DER_NONE) return e;
     else if constexpr (DERIV == DER_LENGTH) return rr * (k.inv_l * k.inv_l) * e;
     else return -k.inv_l * e / rr;
   } else {
     const T rr = lower(sqrt_nn<MINED>(r2));
-    const T e = exp2_prod(rr, k.c);
+    const T e = exp2_prod<MINED>(rr, k.c);
     if constexpr (DERIV == DER_NONE) return (T(1) + rr * k.z) * e;
     else if constexpr (DERIV == DER_LENGTH) return (rr * k.z) * (rr * k.z) * k.inv_l * e;
     else return T(-3) * k.inv_l * k.inv_l * e;

@@ -379,6 +379,20 @@ h2mg_status build_h2(const double* points_dev, int64_t n, int dim, const h2mg_ke
       const double most = (h.kp.kind == KER_GAUSS ? diam2 : std::sqrt(diam2)) * -h.kp.c;
       // and MIN_R2 and the largest r^2 are within FP32's range
       nf.mined = most < 536870912.0 && diam2 < 1e37 && h.kp.inv_l < 1e8;
+      // no entry below FP32's normal range: the largest distance of two points
+      // of a close pair, from the boxes
+      double far2 = 0.0;
+      for (int p = 0; p < nf.npairs; ++p) {
+        const double *ls = &P.lo[h.L][prow[p] * dim], *hs = &P.hi[h.L][prow[p] * dim];
+        const double *lt = &P.lo[h.L][pcol[p] * dim], *ht = &P.hi[h.L][pcol[p] * dim];
+        double d2 = 0.0;
+        for (int a = 0; a < dim; ++a) {
+          const double d = std::max(ht[a] - ls[a], hs[a] - lt[a]);
+          d2 += d * d;
+        }
+        far2 = std::max(far2, d2);
+      }
+      nf.mined32 = nf.mined && (h.kp.kind == KER_GAUSS ? far2 : std::sqrt(far2)) * -h.kp.c < 125.0;
       for (int p = 0; p < nf.npairs; ++p)
         h.near_evals += int64_t(loff[prow[p] + 1] - loff[prow[p]]) * (loff[pcol[p] + 1] - loff[pcol[p]]);
     }

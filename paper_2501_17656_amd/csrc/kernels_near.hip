@@ -188,7 +188,8 @@ __device__ __forceinline__ void near_wave(int wave, const int* __restrict__ task
       if (dim == 3) near_rows<U, 3, MAY, Tv, KIND, DERIV>(A, task, part, sl, p0, p1, rt, nrow, c == part);
       else near_rows<U, 2, MAY, Tv, KIND, DERIV>(A, task, part, sl, p0, p1, rt, nrow, c == part);
     };
-    // points on a line, and distances beyond any use: one loop for every length
+    // points on a line, distances beyond any use, and entries below FP32's normal
+    // range: one loop for every length
     if (dim == 1) {
       near_rows<8, 1, false, Tv, KIND, DERIV>(A, task, part, sl, p0, p1, rt, nrow, c == part);
       continue;
@@ -313,7 +314,7 @@ void launch_near(H2& h, int p, const void* xtree) {
                        reinterpret_cast<Tv*>(h.near_partial), reinterpret_cast<Tv*>(h.near_colpart), kp, nf.ld,
                        nf.nsplit};
     hipLaunchKernelGGL((k_near<Tv, K, D>), g, b, 0, h.stream, nf.task, nf.ntasks, A, h.dim, nf.chunk, nf.nchunk,
-                       nf.mined);
+                       p == P64 ? nf.mined : nf.mined32);
   };
   dispatch_kernel(h.kp.kind, h.kp.deriv, [&](auto kc, auto dc) {
     if (p == P64) go(double{}, kc, dc);

@@ -69,3 +69,16 @@ def test_exponent_coefficient_is_rounded_once(kernel, path):
         z, sens = exponent(kernel, r[1:], ell)
         err = (column(r, kernel, ell, path)[1:] / value(kernel, z) - 1) / sens
         assert abs(float(err.mean())) <= 1.25 * u, (ell, float(err.mean()) / u)
+
+
+@pytest.mark.parametrize("kernel", ["exp", "gauss", "matern32"])
+def test_fp32_entries_below_the_normal_range(kernel):
+    """FP32 entries underflow gradually: off by the roundings of the exponent (2 ulp of z) and of the
+    entry, and by one unit of the subnormal numbers in the exponential."""
+    ell, z0 = 0.1, np.linspace(87.5, 102.0, 255)
+    s = {"gauss": np.sqrt(2 * z0), "exp": z0, "matern32": z0 / 3.0 ** 0.5}[kernel]
+    r = np.concatenate([[0.0], ell * s])
+    z, _ = exponent(kernel, r[1:], ell)
+    want = value(kernel, z)
+    err = np.abs(column(r, kernel, ell, "fp32")[1:] - want)
+    assert (err <= (6 + 4 * z) * 2.0 ** -24 * want + (1 + z) * 2.0 ** -149).all()
