@@ -191,8 +191,11 @@ struct KernelConst {
 //   sqrt_nn: from the hardware's reciprocal square root y (about 2^-24 off in
 //     FP64, 1 ulp in FP32), g = x y and the exact residual d = x - g^2 =
 //     e g^2: sqrt(x) = g + d y (1/2 + 3/8 e) + O(e^3), within 0.501 ulp.
+//     At x = 0 only the reciprocal root is kept finite, and the root is 0.  (The
+//     hardware's FP64 reciprocal root takes subnormals, measured; its FP32 one
+//     does not.)  MINED arguments start at MIN_R2, whose root is too small to
+//     matter.
 //   rsqrt_nn: Newton's iteration.
-//     sqrt_nn raises x to MIN_R2, so that r = 0 gives a root too small to matter.
 //   exp2_prod(s, c) = 2^(c s), c s <= 0: n = rint(c s), f = c s - n with one
 //     rounding (the product's own rounding, up to |c s| times larger, does not
 //     occur), 2^f = 1 + f q(f) with q the degree-10 interpolant of (2^f - 1) / f
@@ -207,8 +210,7 @@ template <> inline constexpr float MIN_R2<float> = 1e-36f;
 
 template <bool MINED = false>
 __device__ inline double sqrt_nn(double x) {
-  if constexpr (!MINED) x = __builtin_fmax(x, MIN_R2<double>);
-  const double y = __builtin_amdgcn_rsq(x);
+  const double y = __builtin_amdgcn_rsq(MINED ? x : __builtin_fmax(x, 0x1p-1074));
   const double g = x * y;
   const double t = __builtin_fma(-g, g, x) * y;
   return __builtin_fma(t, __builtin_fma(0.375, t * y, 0.5), g);
@@ -216,8 +218,8 @@ __device__ inline double sqrt_nn(double x) {
 template <bool MINED = false>
 __device__ inline float sqrt_nn(float x) {
   const bool small = !MINED && x < 1e-28f;       // the residual below would be subnormal
-  if constexpr (!MINED) x = __builtin_fmaxf(small ? x * 0x1p64f : x, MIN_R2<float>);
-  const float y = __builtin_amdgcn_rsqf(x);
+  if constexpr (!MINED) x = small ? x * 0x1p64f : x;
+  const float y = __builtin_amdgcn_rsqf(MINED ? x : __builtin_fmaxf(x, MIN_R2<float>));
   const float g = x * y;
   const float s = __builtin_fmaf(__builtin_fmaf(-g, g, x), 0.5f * y, g);
   return small ? s * 0x1p-32f : s;

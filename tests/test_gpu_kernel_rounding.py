@@ -82,3 +82,17 @@ def test_fp32_entries_below_the_normal_range(kernel):
     want = value(kernel, z)
     err = np.abs(column(r, kernel, ell, "fp32")[1:] - want)
     assert (err <= (6 + 4 * z) * 2.0 ** -24 * want + (1 + z) * 2.0 ** -149).all()
+
+
+@pytest.mark.parametrize("path", ["fp64", "fp64_block"])
+@pytest.mark.parametrize("kernel", ["exp", "matern32"])
+@pytest.mark.parametrize("ell", [1e-140, 1e-150])
+def test_tiny_length_scales(ell, kernel, path):
+    """Coincident points have the kernel's value at 0, and distances whose squares are near the end of the
+    normal range their own root: within the roundings of the exponent (2 ulp of z) and the entry."""
+    r = np.concatenate([[0.0, 0.0], ell * np.geomspace(1e-3, 30.0, 60)])
+    z, _ = exponent(kernel, r, ell)
+    want = value(kernel, z)
+    k = column(r, kernel, ell, path)
+    assert k[1] == 1.0
+    assert (np.abs(k[1:] - want[1:]) <= (6 + 4 * z[1:]) * 2.0 ** -53 * want[1:]).all()
