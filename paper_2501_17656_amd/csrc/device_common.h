@@ -17,6 +17,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <limits>
 #include <type_traits>
 
 namespace h2mg {
@@ -232,9 +233,11 @@ __device__ inline double rsqrt_nn(double x) {
   return __builtin_fma(0.5 * y, e, y);
 }
 __device__ inline float rsqrt_nn(float x) {
-  x = __builtin_fmaxf(x, 1.1754944e-38f);        // the hardware's root takes no subnormals
+  const bool small = x < 1.1754944e-38f;         // the hardware's root takes no subnormals
+  x = small ? x * 0x1p64f : x;
   const float y = __builtin_amdgcn_rsqf(x);
-  return __builtin_fmaf(0.5f * y, __builtin_fmaf(-x * y, y, 1.0f), y);
+  const float s = __builtin_fmaf(0.5f * y, __builtin_fmaf(-x * y, y, 1.0f), y);
+  return small ? s * 0x1p32f : s;
 }
 template <bool NORMAL = false>
 __device__ inline double exp2_prod(double s, double c) {
@@ -272,8 +275,9 @@ template <int KIND, int DERIV, typename T, bool MINED = false>
 __device__ inline T kernel_fixed(const KernelConst<T>& k, T r2) {
   auto lower = [&](T s) { return MINED ? s : lower_to(s, k.far); };
   if constexpr (KIND == KER_LAPLACE) {
-    // 1 / (4 pi r); 0 at r = 0 (the matrix supplies its own diagonal)
-    return r2 == T(0) ? T(0) : T(0.07957747154594767) * rsqrt_nn(r2);
+    // 1 / (4 pi r); 0 at r = 0 (the matrix supplies its own diagonal) and for an
+    // overflowed r^2
+    return r2 == T(0) || r2 > std::numeric_limits<T>::max() ? T(0) : T(0.07957747154594767) * rsqrt_nn(r2);
   }
   if constexpr (DERIV == DER_RADIAL) {
     if (r2 == T(0)) return T(0);

@@ -96,3 +96,19 @@ def test_tiny_length_scales(ell, kernel, path):
     k = column(r, kernel, ell, path)
     assert k[1] == 1.0
     assert (np.abs(k[1:] - want[1:]) <= (6 + 4 * z[1:]) * 2.0 ** -53 * want[1:]).all()
+
+
+@pytest.mark.parametrize("path", ["fp64", "fp32", "fp64_block"])
+def test_laplace_entries_over_the_whole_range(path):
+    """1 / (4 pi r) also where r^2 is subnormal in FP32, and 0 where it is no finite number."""
+    r = np.concatenate([[0.0], np.geomspace(1e-20, 1e-17, 20), np.geomspace(1e-10, 1e10, 20), [1e25, 1e160]])
+    k = column(r, "laplace", 1.0, path, diag=1e23)[1:]
+    r = r[1:]
+    if path == "fp32":
+        # r^2 has an absolute error of 2^-150 there, besides 4 roundings
+        bound = (2.0 ** -22 + 0.5 * 2.0 ** -150 / r / r) / (4 * np.pi * r)
+        zero = r >= 1e25
+    else:
+        bound, zero = 2.0 ** -50 / (4 * np.pi * r), r >= 1e160
+    assert (k[zero] == 0.0).all()
+    assert (np.abs(k - 1 / (4 * np.pi * r)) <= bound)[~zero].all()
