@@ -286,7 +286,7 @@ __device__ inline T kernel_fixed(const KernelConst<T>& k, T r2) {
     const T s = lower(r2);
     const T e = exp2_prod<MINED>(s, k.c);
     if constexpr (DERIV == DER_NONE) return e;
-    else if constexpr (DERIV == DER_LENGTH) return s * (k.inv_l * k.inv_l * k.inv_l) * e;
+    else if constexpr (DERIV == DER_LENGTH) return s * (k.inv_l * k.inv_l) * (k.inv_l * e);   // 1 / l^3 may overflow
     else return -k.inv_l * k.inv_l * e;
   } else if constexpr (KIND == KER_EXP) {
     const T rr = lower(sqrt_nn<MINED>(r2));

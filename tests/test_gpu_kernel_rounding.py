@@ -112,3 +112,23 @@ def test_laplace_entries_over_the_whole_range(path):
         bound, zero = 2.0 ** -50 / (4 * np.pi * r), r >= 1e160
     assert (k[zero] == 0.0).all()
     assert (np.abs(k - 1 / (4 * np.pi * r)) <= bound)[~zero].all()
+
+
+@pytest.mark.parametrize("kernel", ["exp", "gauss", "matern32"])
+@pytest.mark.parametrize("derivative", ["dl", "g"])
+def test_derivative_entries_over_the_whole_range(derivative, kernel):
+    """Tiny length scales, whose inverse cube is no finite number, and distances whose squares are none:
+    the exact value within the roundings of the exponent (2 ulp of z) and of the factors, 0 where it
+    underflows."""
+    for ell, r in ((1e-110, 1e-110 * np.geomspace(1e-2, 20.0, 60)), (0.1, np.append(np.geomspace(0.01, 1.0, 40), 1e160))):
+        z, _ = exponent(kernel, r, ell)
+        x, L, e = r.astype(np.longdouble), np.longdouble(ell), np.exp(-z)
+        if derivative == "dl":
+            want = {"exp": x / L ** 2, "gauss": x * x / L ** 3, "matern32": z * z / L}[kernel] * e
+        else:
+            want = {"exp": -1 / (L * x), "gauss": -1 / L ** 2, "matern32": -3 / L ** 2}[kernel] * e
+        k = column(np.concatenate([[0.0], r]), kernel, ell, "fp64", derivative)[1:]
+        big = r > 1e100
+        assert (k[big] == 0.0).all()
+        err = np.abs(k - want) <= (12 + 4 * np.minimum(z, 1e3)) * 2.0 ** -53 * np.abs(want)
+        assert err[~big].all(), (ell, k[~big], want[~big])
