@@ -145,13 +145,22 @@ void free_set(H2& h, TileSet& ts) {
   ts = TileSet();
 }
 
+// The near-field tile product of a block: from the stored tiles of this
+// precision where there are some, else with the entries evaluated.
+void near_product16(H2& h, int p, const TileSet& ts, const void* xc) {
+  const StoredNear& sn = h.snear;
+  void* partial = h.blk16.partial;
+  if (!near_stored_for(h, p)) launch_tgemm_eval(h, p == P64 ? P64 : P32, ts, xc, partial);
+  else if (p == P64) launch_tgemm(h, P64, 8, ts, sn.tiles, sn.lanes, 64, xc, partial);
+  else launch_tgemm(h, P32, 8, ts, sn.tiles32, sn.lanes, 64, xc, partial);
+}
+
 // The tile product and reduce of one set, as run inside a product.
 void run_set(H2& h, int p, const TileSet& ts, bool near, const void* x, void* out) {
   BlockWork& w = h.blk16;
   const int rr = near ? 64 : h.r;
   if (!near) launch_tgemm(h, p, h.T, ts, h.prec[p].blk, tile_A(h.r, h.T), rr, x, w.partial);
-  else if (p == P64 && h.snear.ready) launch_tgemm(h, P64, 8, ts, h.snear.tiles, h.snear.lanes, 64, x, w.partial);
-  else launch_tgemm_eval(h, p == P64 ? P64 : P32, ts, x, w.partial);
+  else near_product16(h, p, ts, x);
   launch_reduce16(h, p, ts, rr, w.partial, out);
 }
 
@@ -309,16 +318,11 @@ void apply_fine16(H2& h, int p, const void* X, void* out, double alpha, const vo
     launch_near_pad16(h, p, X, buf);
     xc = buf;
   }
-  if (p == P64 && sn.ready) {
-    int ev;
-    h.time_begin(ev);
-    launch_tgemm(h, P64, 8, w.near, sn.tiles, sn.lanes, 64, xc, w.partial);
-    h.time_end(KS_NEAR16, ev, double(w.near.ntiles) * 4096.0 * sizeof(double));   // each stored tile once
-  } else if (near_stored_for(h, p)) {
-    launch_tgemm(h, P32, 8, w.near, sn.tiles32, sn.lanes, 64, xc, w.partial);
-  } else {
-    launch_tgemm_eval(h, vprec(p), w.near, xc, w.partial);
-  }
+  int ev = -1;
+  const bool timed = p == P64 && sn.ready;
+  if (timed) h.time_begin(ev);
+  near_product16(h, p, w.near, xc);
+  if (timed) h.time_end(KS_NEAR16, ev, double(w.near.ntiles) * 4096.0 * sizeof(double));   // each stored tile once
   launch_reduce16(h, p, w.near, 64, w.partial, w.yc);
   launch_leaf_down16(h, p, yhat, w.yc, out, alpha, add, beta);
 }
