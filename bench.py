@@ -483,10 +483,9 @@ def block_product(args, torch, g, w, single_ms):
     tuning = g.block_tuning()
     # every tile also reads its column's 64 x 16 operand block and, off the
     # diagonal, writes a 64 x 16 column contribution (FP64): the pass moves
-    # tiles + 8 KiB per tile + 8 KiB per off-diagonal tile (the diagonal
-    # tiles are those of a 64-point chunk with itself, n / 64 of them)
-    ntiles = tile_bytes / 32768.0
-    vec_bytes = 64 * 16 * 8.0 * (2.0 * ntiles - g.n / 64.0)
+    # tiles + 8 KiB per tile + 8 KiB per off-diagonal tile, which is 8 KiB per
+    # tile read as the tuning counts them
+    vec_bytes = 64 * 16 * 8.0 * tuning["near"]["tiles_read"]
     return {"ms": round(ms, 3), "ms_per_vector": round(ms / 16, 3),
             "speedup_vs_16_single_products": round(16 * single_ms / ms, 2),
             "tile_runs": {k: v["run"] for k, v in tuning.items()},

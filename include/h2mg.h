@@ -531,9 +531,10 @@ h2mg_status h2mg_block_tuning(h2mg_h2_t h, int32_t which, int32_t* run, double* 
  * they streamed (stored block words x element size); for kind 3/4 (near
  * field evaluated in FP64/FP32) the summed kernel evaluations instead of
  * bytes; for kind 5 (block GEMV over the stored FP64 near-field tiles) the
- * bytes of the tiles it streamed; for kind 6 (both passes of the FP64
- * 16-column tile product over the near-field tiles) the bytes of the tiles
- * read by the two passes. */
+ * bytes of the tiles it streamed, without the padding of chunks that are
+ * shorter than a tile (rows and columns in multiples of 8); for kind 6 (the
+ * FP64 16-column tile product over the same tiles, each read once) the same
+ * bytes. */
 h2mg_status h2mg_set_timing(h2mg_h2_t h, int32_t enabled);
 h2mg_status h2mg_kernel_stats(h2mg_h2_t h, int32_t kind, int64_t* launches, double* total_ms,
                               double* total_work);

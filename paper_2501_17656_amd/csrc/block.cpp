@@ -322,7 +322,8 @@ void apply_fine16(H2& h, int p, const void* X, void* out, double alpha, const vo
   const bool timed = p == P64 && sn.ready;
   if (timed) h.time_begin(ev);
   near_product16(h, p, w.near, xc);
-  if (timed) h.time_end(KS_NEAR16, ev, double(w.near.ntiles) * 4096.0 * sizeof(double));   // each stored tile once
+  // each stored tile once, the lanes that hold entries
+  if (timed) h.time_end(KS_NEAR16, ev, double(w.near.ntiles) * (64.0 * sn.lanes * sn.lanes) * sizeof(double));
   launch_reduce16(h, p, w.near, 64, w.partial, w.yc);
   launch_leaf_down16(h, p, yhat, w.yc, out, alpha, add, beta);
 }

@@ -68,7 +68,7 @@ struct Launch {
 enum KStatKind {
   KS_GEMV64 = 0, KS_GEMV32 = 1, KS_GEMV16 = 2, KS_NEAR64 = 3, KS_NEAR32 = 4,
   KS_NEARST64 = 5,                     // block GEMV over the stored near-field tiles
-  KS_NEAR16 = 6,                       // both passes of the 16-vector product over the near tiles
+  KS_NEAR16 = 6,                       // 16-vector product over the stored near tiles (each read once)
   KS_COUNT = 7
 };
 struct KStat {
