@@ -151,9 +151,13 @@ def profiled_traffic(kind, avg_bytes):
     import re
     csrc = os.path.join(ROOT, "paper_2501_17656_amd", "csrc")
     h = hashlib.sha256()
-    for f in ("kernels_apply.hip", "device_common.h"):
-        with open(os.path.join(csrc, f), "rb") as fh:
-            h.update(fh.read())
+    # the kernels, the tile layout, and the wave program (in kernels_apply.hip
+    # itself in trees without the header)
+    for f in ("kernels_apply.hip", "device_common.h", "tile_gemv.h"):
+        path = os.path.join(csrc, f)
+        if os.path.exists(path):
+            with open(path, "rb") as fh:
+                h.update(fh.read())
     cur = h.hexdigest()[:16]
     for path in sorted(glob.glob(os.path.join(ROOT, "profiles", "gemv_counters_*.md"))):
         with open(path) as fh:
