@@ -226,7 +226,7 @@ k_near(const int* __restrict__ tasks, int ntasks, NearIn<Tv> A, int dim, int chu
 // Registers for three waves a SIMD, as the near field alone, so a 64 x 64 tile
 // is read in two halves; the coupling waves go first when their data is there.
 // A product of 131072 points (3D, rank 64) took 2438 us with two launches and
-// 2246 with one, 50000 points (rank 25 in tiles of 32) 593 and 566; with
+// 2246 with one, 50000 points (rank 27 in tiles of 32) 593 and 566; with
 // tiles of 16, which want more waves in flight than three, 90000 points took 190
 // and 199 us, 4096 points 35.6 and 36.8: those stay two launches.
 struct FarIn {
@@ -263,12 +263,8 @@ k_near_far(const int* __restrict__ tasks, int ntasks, NearIn<double> A, int dim,
     if (F.r == 8 * decltype(tc)::value) go(tc, std::true_type{});
     else go(tc, std::false_type{});
   };
-  switch (F.T) {
-    case 1: pick(std::integral_constant<int, 1>{}); break;
-    case 2: pick(std::integral_constant<int, 2>{}); break;
-    case 4: pick(std::integral_constant<int, 4>{}); break;
-    default: pick(std::integral_constant<int, 8>{}); break;
-  }
+  if (F.T == 4) pick(std::integral_constant<int, 4>{});
+  else pick(std::integral_constant<int, 8>{});
 }
 
 }  // namespace
