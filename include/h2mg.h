@@ -524,7 +524,11 @@ h2mg_status h2mg_block_tuning(h2mg_h2_t h, int32_t which, int32_t* run, double* 
 
 /* Kernel timing, for measurement harnesses.  While enabled, every launch of
  * the block GEMV and of the near-field kernel is bracketed by HIP events on
- * the handle's stream (a small per-launch overhead).  h2mg_set_timing
+ * the handle's stream (a small per-launch overhead).  A fine FP64 product of
+ * rank above 16 whose near field is evaluated runs near field and couplings in
+ * one launch while timing is off; while it is on it launches them apart, so
+ * kinds 0 and 3 then time launches that an untimed product does not make, and
+ * their sum exceeds what that product takes.  h2mg_set_timing
  * resets the counters.  h2mg_kernel_stats synchronises the stream and
  * returns, for kind 0/1/2 (block GEMV with FP64/FP32/BF16 blocks), the
  * number of launches, their summed duration in ms and the algorithmic bytes

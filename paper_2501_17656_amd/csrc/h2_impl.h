@@ -246,7 +246,7 @@ struct H2 {
   double* partial = nullptr;           // max_tasks * r
   double* colpart = nullptr;           // nblk * r
   double* near_partial = nullptr;      // near.ntasks * ld
-  double* near_colpart = nullptr;      // near.npairs * ld
+  double* near_colpart = nullptr;      // near.npairs * near.nsplit * ld
   double* vtree = nullptr;             // N scratch (tree order)
   double* vtree2 = nullptr;
 
@@ -354,7 +354,7 @@ void launch_leaf_up(H2& h, int p, const void* xtree, void* xhat);
 void launch_leaf_up_gather(H2& h, const double* xuser, double* xtree, double* xhat);
 void launch_near(H2& h, int p, const void* xtree);
 // launch_near and launch_gemv(h, P64, l, xall) in one launch, where there is a
-// kernel for both (returns whether).
+// kernel for both (returns whether; not while launches are timed one by one).
 bool launch_near_far(H2& h, const void* xtree, const Launch& l, const void* xall);
 // Stored near field: snear.yc = D x over the chunk-padded layout, FP64
 // tiles and vectors (p = P64) or the FP32 tile copy with FP32 vectors.

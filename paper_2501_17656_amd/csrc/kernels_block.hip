@@ -90,7 +90,7 @@ __device__ __forceinline__ int swz(int i) {
 // a 64 x 64 FP64 tile, the block-row operand another 64): in LDS a workgroup
 // reads them from the L2 once instead of four times, and three workgroups fit
 // on a compute unit instead of two.
-// 16 FP64 products of 66k points (rank 64, near field evaluated) went from 2114
+// 16 FP64 products of 66k points (rank 64, near field stored) went from 2114
 // to 2012 us, 5 of 20k points from 1321 to 803 us, a 16-column solve of 16k
 // points from 122 to 117 ms.
 template <int T, typename Tv>

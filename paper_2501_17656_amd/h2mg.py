@@ -337,6 +337,8 @@ class H2Matrix:
         return out
 
     def set_timing(self, enabled: bool) -> None:
+        """Kernel timing for kernel_stats().  While on, fine FP64 products launch the evaluated near field
+        and the couplings apart, which otherwise share a launch (rank above 16)."""
         check(lib().h2mg_set_timing(self._h, int(bool(enabled))))
 
     def kernel_stats(self, kind: str) -> dict:
