@@ -717,7 +717,7 @@ h2mg_status build_hierarchy(H2& h) {
   auto give_back = [&] {
     (void)hipStreamSynchronize(h.stream);
     while (h.arena.ptrs.size() > mark) h.arena.release(h.arena.ptrs.back().first);
-    h.chol = h.cinv = nullptr;
+    h.chol = h.cinv = h.cdiag = nullptr;
   };
   try {
     if (h.d_top >= 0) {
@@ -792,13 +792,18 @@ h2mg_status build_hierarchy(H2& h) {
     }
     if (h.Nl <= INVERSE_MAX) {
       try {
+        h.cdiag = h.arena.make<double>(size_t(h.Nl));
         h.cinv = h.arena.make<double>(size_t(h.Nl) * h.Nl);
       } catch (const std::bad_alloc&) {
         // no room for it: the factor alone serves, by substitution
+        h.arena.release(h.cdiag);
+        h.cdiag = nullptr;
       }
       if (h.cinv) {
-        launch_tri_inverse(h, h.chol, h.Nl, h.cinv);
+        launch_tri_inverse(h, h.chol, h.Nl, h.cinv, h.cdiag);
         hip_check(hipStreamSynchronize(h.stream), "inverse factor");
+        h.arena.release(h.chol);
+        h.chol = nullptr;
       }
     }
     h.mg_built = true;

@@ -254,11 +254,12 @@ struct H2 {
   bool mg_built = false;
   int levels = 1;
   int64_t Nl = 0;                      // coarsest size
-  // the coarsest operator's Cholesky factor L, column-major; with the inverse
-  // also row-major: both triangles of one square
-  double* chol = nullptr;              // Nl x Nl
-  // up to INVERSE_MAX rows: X = L^{-1} in the lower and X^T in the upper triangle
+  // the coarsest operator, up to INVERSE_MAX rows: X = L^{-1} up to the diagonal,
+  // L^T above it (cinv), and the diagonal of L (cdiag); larger ones: the Cholesky
+  // factor L itself (chol)
+  double* chol = nullptr;              // Nl x Nl column-major, lower factor
   double* cinv = nullptr;              // Nl x Nl row-major
+  double* cdiag = nullptr;             // Nl
   int* flags = nullptr;                // device flags (0: not SPD, 1: non-finite)
   double* dot_part = nullptr;          // reduction partials (several slots)
   double* sweep_part = nullptr;        // those of the downsweeps (at most one per cluster of depth L - 1)
@@ -316,8 +317,8 @@ void launch_pi_upper(H2& h, int d, const int* child_map);   // Pi tiles of depth
 void launch_assemble_dense(H2& h, double* A, int64_t lda);  // depth d_top blocks
 void launch_assemble_kernel_dense(H2& h, double* A, int64_t lda);  // no far blocks
 void launch_potrf(H2& h, double* A, int64_t N, double* work);   // blocked Cholesky, sets flags[0]; work: 64 * 64
-// S: X = L^{-1} below, X^T above the diagonal; L is completed by its rows the same way.
-void launch_tri_inverse(H2& h, double* L, int64_t N, double* S);
+// S: X = L^{-1} up to the diagonal, L^T above it; diag: the diagonal of L.
+void launch_tri_inverse(H2& h, const double* L, int64_t N, double* S, double* diag);
 void launch_cast_precision(H2& h, int p);         // FP64 -> FP32 / BF16 copies
 void launch_near_tiles(H2& h);                    // stored near-field tiles (FP64)
 // Inverses of the block-Jacobi blocks: leaf blocks K_ss + shift (FP64) and the
@@ -530,8 +531,8 @@ int launch_cg_step_bj(H2& h, int p, int k, const void* src, void* e, bool e_zero
                       const void* q, void* z, const double* gamma_part, int ngp, const double* delta_part,
                       int ndp, double* gamma_new_part);
 void launch_chol_solve(H2& h, const double* L, int64_t N, double* x);   // in place
-// e = L^{-T} L^{-1} r, each factor by its inverse h.cinv and one correction with
-// h.chol; r, e in the vector type of p (FP64 arithmetic; uses vtree and vtree2).
+// e = L^{-T} L^{-1} r, each factor by its inverse and one correction with the
+// factor itself (both in h.cinv); r, e in the vector type of p (FP64 arithmetic; uses vtree and vtree2).
 void launch_inverse_solve(H2& h, int p, const void* r, void* e);
 void launch_check_finite(H2& h, int p, int64_t n, const void* x);      // sets flags[1]
 // Gradient helpers (tree-ordered points h.pts, n x dim).

@@ -651,16 +651,20 @@ __global__ __launch_bounds__(NT) void k_gemv_bwd16(const double* __restrict__ L,
   x[j * NR + k] -= s;
 }
 
-// Y = add + sign M B, M = the lower (UP = false) or upper (UP = true) triangle of
-// S (see k_tri_gemv, also for the solve they make up; add may be null or Y), on
-// the FP64 matrix cores.  One workgroup per 16 rows; the four waves take every fourth run of
+// Y = add + sign M B on the FP64 matrix cores, with M one of the four matrices in
+// the square S (see k_tri_gemv, also for the solve they make up): X or (FACTOR)
+// L^T by rows of S, X^T or L by its columns (COL); add may be null or Y.  One
+// workgroup per 16 rows of M; the four waves take every fourth run of
 // 16 inner indices and their sums are added in wave order.  Within a run lane
 // (p, q) loads the four entries 4q .. 4q + 3 of row p, so that each row's 16
-// entries are read whole, and the k-step t takes inner index 4q + t.
+// entries are read whole (or, by columns, whole cache lines of 16 rows of M), and
+// the k-step t takes inner index 4q + t.
 // (16 right-hand sides on 16500 points: 139 to 133 ms a solve.)
-template <bool UP, typename Tin, typename Tadd, typename Tout>
-__global__ __launch_bounds__(NT) void k_tri_gemm16(const double* __restrict__ S, int64_t N,
-                                                   const Tin* __restrict__ x, const Tadd* add, double sign, Tout* y) {
+template <bool FACTOR, bool COL, typename Tin, typename Tadd, typename Tout>
+__global__ __launch_bounds__(NT) void k_tri_gemm16(const double* __restrict__ S, const double* __restrict__ diag,
+                                                   int64_t N, const Tin* __restrict__ x, const Tadd* add, double sign,
+                                                   Tout* y) {
+  constexpr bool UP = FACTOR != COL;   // M is an upper triangle
   __shared__ double red[4][16 * NR];
   const int64_t i0 = int64_t(blockIdx.x) * 16;
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63, p = l & 15, q = l >> 4;
@@ -673,7 +677,8 @@ __global__ __launch_bounds__(NT) void k_tri_gemm16(const double* __restrict__ S,
     for (int t = 0; t < 4; ++t) {
       const int64_t k = j + 4 * q + t;
       const bool in = k < j1 && (UP ? k >= row : k <= row);
-      a[t] = in ? S[row * N + k] : 0.0;
+      const double* from = FACTOR && k == row ? diag + row : COL ? S + k * N + row : S + row * N + k;
+      a[t] = in ? *from : 0.0;
       b[t] = k < j1 ? double(x[k * NR + p]) : 0.0;
     }
 #pragma unroll
@@ -932,18 +937,19 @@ void launch_cg_pupdate16(H2& h, int p, int64_t nrows, void* pv, const void* s, c
 }
 
 void launch_inverse_solve16(H2& h, int p, const void* r, void* e, double* y, double* t) {
-  const dim3 g(unsigned((h.Nl + 15) / 16)), b(NT);
-  const double *X = h.cinv, *L = h.chol;
-  const double* none = nullptr;
+  const int64_t N = h.Nl;
+  const dim3 g(unsigned((N + 15) / 16)), b(NT);
+  const double *S = h.cinv, *d = h.cdiag, *none = nullptr;
   auto solve = [&](auto tv) {
     using Tv = decltype(tv);
     const Tv* rv = static_cast<const Tv*>(r);
-    hipLaunchKernelGGL((k_tri_gemm16<false, Tv, double, double>), g, b, 0, h.stream, X, h.Nl, rv, none, 1.0, y);
-    hipLaunchKernelGGL((k_tri_gemm16<false, double, Tv, double>), g, b, 0, h.stream, L, h.Nl, y, rv, -1.0, t);
-    hipLaunchKernelGGL((k_tri_gemm16<false, double, double, double>), g, b, 0, h.stream, X, h.Nl, t, y, 1.0, y);
-    hipLaunchKernelGGL((k_tri_gemm16<true, double, double, double>), g, b, 0, h.stream, X, h.Nl, y, none, 1.0, t);
-    hipLaunchKernelGGL((k_tri_gemm16<true, double, double, double>), g, b, 0, h.stream, L, h.Nl, t, y, -1.0, y);
-    hipLaunchKernelGGL((k_tri_gemm16<true, double, double, Tv>), g, b, 0, h.stream, X, h.Nl, y, t, 1.0,
+    hipLaunchKernelGGL((k_tri_gemm16<false, false, Tv, double, double>), g, b, 0, h.stream, S, d, N, rv, none, 1.0, y);
+    hipLaunchKernelGGL((k_tri_gemm16<true, true, double, Tv, double>), g, b, 0, h.stream, S, d, N, y, rv, -1.0, t);
+    hipLaunchKernelGGL((k_tri_gemm16<false, false, double, double, double>), g, b, 0, h.stream, S, d, N, t, y, 1.0, y);
+    hipLaunchKernelGGL((k_tri_gemm16<false, true, double, double, double>), g, b, 0, h.stream, S, d, N, y, none, 1.0,
+                       t);
+    hipLaunchKernelGGL((k_tri_gemm16<true, false, double, double, double>), g, b, 0, h.stream, S, d, N, t, y, -1.0, y);
+    hipLaunchKernelGGL((k_tri_gemm16<false, true, double, double, Tv>), g, b, 0, h.stream, S, d, N, y, t, 1.0,
                        static_cast<Tv*>(e));
   };
   if (p == P64) solve(double{});

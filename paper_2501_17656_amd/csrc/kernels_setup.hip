@@ -700,8 +700,8 @@ __global__ __launch_bounds__(NT) void k_potrf_tile(double* A, int64_t N, int64_t
 // shorter), with B the block of L below A: X_B = -X_C (L_B X_A).  All pairs of
 // a step go together, so the chain is 2 log2(N / 64) products long instead of
 // N / 64 substitutions.  S (N x N, row-major) holds X in its lower triangle;
-// the upper one holds the transposes of the products L_B X_A meanwhile and
-// X^T in the end, so that rows of X and of X^T are both contiguous.
+// above the diagonal are the transposes of the products L_B X_A meanwhile and
+// L^T in the end.
 __global__ __launch_bounds__(NB) void k_tri_inv_diag(const double* __restrict__ L, int64_t N,
                                                      double* __restrict__ S) {
   __shared__ double D[NB][NB + 1], X[NB][NB + 1];
@@ -778,24 +778,13 @@ __global__ __launch_bounds__(NT) void k_tri_inv_step(const double* __restrict__ 
     }
 }
 
-// One triangle of S (row-major) = transpose of the other, 64 x 64 tiles (bi >=
-// bj): the upper one from the lower one (TO_UPPER) or the other way round.
-template <bool TO_UPPER>
-__global__ __launch_bounds__(NT) void k_tri_mirror(double* __restrict__ S, int64_t N) {
-  __shared__ double X[NB][NB + 1];
-  const int64_t i0 = int64_t(blockIdx.x) * NB, j0 = int64_t(blockIdx.y) * NB;
-  if (j0 > i0) return;
-  const int64_t r0 = TO_UPPER ? i0 : j0, c0 = TO_UPPER ? j0 : i0;   // the tile that is read
-  for (int e = threadIdx.x; e < NB * NB; e += NT) {
-    const int i = e / NB, j = e % NB;
-    X[i][j] = r0 + i < N && c0 + j < N ? S[(r0 + i) * N + c0 + j] : 0.0;
-  }
-  __syncthreads();
-  for (int e = threadIdx.x; e < NB * NB; e += NT) {
-    const int j = e / NB, i = e % NB;
-    const bool other = TO_UPPER ? c0 + j < r0 + i : c0 + j > r0 + i;   // read from the valid triangle
-    if (r0 + i < N && c0 + j < N && other) S[(c0 + j) * N + r0 + i] = X[i][j];
-  }
+// S above the diagonal = L^T (L column-major below its diagonal), diag = L's own.
+__global__ __launch_bounds__(NT) void k_tri_pack(const double* __restrict__ L, int64_t N, double* __restrict__ S,
+                                                 double* __restrict__ diag) {
+  const int64_t i = blockIdx.y, j = int64_t(blockIdx.x) * NT + threadIdx.x;
+  if (j >= N || j < i) return;
+  if (j > i) S[i * N + j] = L[i * N + j];
+  else diag[i] = L[i * N + i];
 }
 
 // ------------------------------------------------------------ block-Jacobi inverses
@@ -1098,7 +1087,7 @@ void launch_potrf(H2& h, double* A, int64_t N, double* work) {
   check_launch("potrf");
 }
 
-void launch_tri_inverse(H2& h, double* L, int64_t N, double* S) {
+void launch_tri_inverse(H2& h, const double* L, int64_t N, double* S, double* diag) {
   const unsigned nb = unsigned((N + NB - 1) / NB);
   hipLaunchKernelGGL(k_tri_inv_diag, dim3(nb), dim3(NB), 0, h.stream, L, N, S);
   for (int64_t s = NB; s < N; s *= 2) {
@@ -1106,9 +1095,7 @@ void launch_tri_inverse(H2& h, double* L, int64_t N, double* S) {
     hipLaunchKernelGGL(k_tri_inv_step<0>, grid, dim3(NT), 0, h.stream, L, N, s, S);
     hipLaunchKernelGGL(k_tri_inv_step<1>, grid, dim3(NT), 0, h.stream, L, N, s, S);
   }
-  hipLaunchKernelGGL(k_tri_mirror<true>, dim3(nb, nb), dim3(NT), 0, h.stream, S, N);
-  // L, column-major below its diagonal, is L^T in the upper triangle of rows
-  hipLaunchKernelGGL(k_tri_mirror<false>, dim3(nb, nb), dim3(NT), 0, h.stream, L, N);
+  hipLaunchKernelGGL(k_tri_pack, dim3(unsigned((N + NT - 1) / NT), unsigned(N)), dim3(NT), 0, h.stream, L, N, S, diag);
   check_launch("tri_inverse");
 }
 

@@ -260,28 +260,32 @@ __global__ __launch_bounds__(NT) void k_gemv_bwd(const double* __restrict__ L, i
 }
 
 // ------------------------------------------------------------ products with the inverse factor
-// y = add + sign M x, M = the lower (UP = false) or upper (UP = true) triangle of
-// S (row-major; add may be null or y).  For the inverse X of the Cholesky factor
-// and for the factor L, S holds the matrix below and its transpose above the
-// diagonal, so that all products are dot products with contiguous parts of
-// rows: columns 0 .. i of row i, or i .. N - 1.  One wave per row, eight loads of
-// 64 entries in flight.
+// The matrices of the direct solve lie in one square S (row-major): X, the inverse
+// of the Cholesky factor L, up to the diagonal, and L^T above it (the diagonal of L
+// in diag).
 //
 // Products with X alone are not backward stable: the residual of X^T (X r) grows
 // with the root of the condition number (13 times that of substitution at
 // condition 6e7, 130 at 2e12, 1000 rows).  Each triangular solve is therefore
 // corrected once with its own residual, y = X r, y += X (r - L y), which leaves
 // the residual of substitution as long as the factor's condition number (the
-// root of the operator's) is well below 2^53.
-template <bool UP, typename Tin, typename Tadd, typename Tout>
-__global__ __launch_bounds__(NT) void k_tri_gemv(const double* __restrict__ S, int64_t N,
-                                                 const Tin* __restrict__ x, const Tadd* add, double sign, Tout* y) {
+// root of the operator's) is well below 2^53.  The square of a 4096-row operator
+// (134 MB) stays in the 256 MB last-level cache through the six products of a
+// solve and between cycles.
+
+// y = add + sign M x, with M = X or (FACTOR) L^T: dot products with contiguous
+// parts of rows of S (add may be null or y).  One wave per row, eight loads of
+// 64 entries in flight.
+template <bool FACTOR, typename Tin, typename Tadd, typename Tout>
+__global__ __launch_bounds__(NT) void k_tri_gemv(const double* __restrict__ S, const double* __restrict__ diag,
+                                                 int64_t N, const Tin* __restrict__ x, const Tadd* add, double sign,
+                                                 Tout* y) {
   const int64_t i = __builtin_amdgcn_readfirstlane(int((blockIdx.x * NT + threadIdx.x) >> 6));
   if (i >= N) return;
   const int lane = threadIdx.x & 63;
   const double* row = S + i * N;
-  const int64_t j1 = UP ? N : i + 1;
-  int64_t j = (UP ? i : 0) + lane;
+  const int64_t j1 = FACTOR ? N : i + 1;
+  int64_t j = (FACTOR ? i + 1 : 0) + lane;
   double v0 = 0.0, v1 = 0.0;
   for (; j + 7 * 64 < j1; j += 8 * 64) {
     double a[8], b[8];
@@ -299,7 +303,45 @@ __global__ __launch_bounds__(NT) void k_tri_gemv(const double* __restrict__ S, i
   for (; j < j1; j += 64) v0 += row[j] * double(x[j]);
   v0 += v1;
   for (int o = 32; o > 0; o >>= 1) v0 += __shfl_xor(v0, o, 64);
-  if (lane == 0) y[i] = Tout(add ? double(add[i]) + sign * v0 : v0);
+  if (lane != 0) return;
+  if (FACTOR) v0 += diag[i] * double(x[i]);
+  y[i] = Tout(add ? double(add[i]) + sign * v0 : v0);
+}
+
+// The same with M = X^T or (FACTOR) L: sums down the columns of S.  A workgroup
+// takes 16 columns (a row's part is a cache line), each of its 16 waves 4 rows
+// of 64 at a time with eight loads in flight.
+constexpr int NT_COL = 1024;
+template <bool FACTOR, typename Tin, typename Tadd, typename Tout>
+__global__ __launch_bounds__(NT_COL) void k_tri_gemv_col(const double* __restrict__ S, const double* __restrict__ diag,
+                                                         int64_t N, const Tin* __restrict__ x, const Tadd* add,
+                                                         double sign, Tout* y) {
+  __shared__ double red[NT_COL / 64][16];
+  const int p = threadIdx.x & 15;
+  const int64_t c0 = int64_t(blockIdx.x) * 16, c = c0 + p, col = min(c, N - 1);
+  const int64_t r1 = FACTOR ? min(N, c0 + 16) : N;
+  double v = 0.0;
+  for (int64_t j0 = (FACTOR ? 0 : c0) + (threadIdx.x >> 4); j0 < r1; j0 += 8 * (NT_COL / 16)) {
+    double a[8], b[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int64_t j = j0 + q * (NT_COL / 16);
+      const bool in = j < r1 && (FACTOR ? j < c : j >= c);
+      a[q] = in ? S[j * N + col] : 0.0;
+      b[q] = in ? double(x[j]) : 0.0;
+    }
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v += a[q] * b[q];
+  }
+  v += __shfl_xor(v, 16, 64);
+  v += __shfl_xor(v, 32, 64);
+  if ((threadIdx.x & 63) < 16) red[threadIdx.x >> 6][p] = v;
+  __syncthreads();
+  if (threadIdx.x >= 16 || c >= N) return;
+  v = 0.0;
+  for (int w = 0; w < NT_COL / 64; ++w) v += red[w][p];
+  if (FACTOR) v += diag[c] * double(x[c]);
+  y[c] = Tout(add ? double(add[c]) + sign * v : v);
 }
 
 inline unsigned blocks(int64_t n) { return unsigned((n + NT - 1) / NT); }
@@ -432,19 +474,19 @@ void launch_chol_solve(H2& h, const double* L, int64_t N, double* x) {
 }
 
 void launch_inverse_solve(H2& h, int p, const void* r, void* e) {
-  const dim3 g(unsigned((h.Nl + NT / 64 - 1) / (NT / 64))), b(NT);
-  const double *X = h.cinv, *L = h.chol;
+  const int64_t N = h.Nl;
+  const dim3 g(unsigned((N + NT / 64 - 1) / (NT / 64))), b(NT), gc(unsigned((N + 15) / 16)), bc(NT_COL);
+  const double *S = h.cinv, *d = h.cdiag, *none = nullptr;
   double *y = h.vtree2, *t = h.vtree;
-  const double* none = nullptr;
   auto solve = [&](auto tv) {
     using Tv = decltype(tv);
     const Tv* rv = static_cast<const Tv*>(r);
-    hipLaunchKernelGGL((k_tri_gemv<false, Tv, double, double>), g, b, 0, h.stream, X, h.Nl, rv, none, 1.0, y);
-    hipLaunchKernelGGL((k_tri_gemv<false, double, Tv, double>), g, b, 0, h.stream, L, h.Nl, y, rv, -1.0, t);
-    hipLaunchKernelGGL((k_tri_gemv<false, double, double, double>), g, b, 0, h.stream, X, h.Nl, t, y, 1.0, y);
-    hipLaunchKernelGGL((k_tri_gemv<true, double, double, double>), g, b, 0, h.stream, X, h.Nl, y, none, 1.0, t);
-    hipLaunchKernelGGL((k_tri_gemv<true, double, double, double>), g, b, 0, h.stream, L, h.Nl, t, y, -1.0, y);
-    hipLaunchKernelGGL((k_tri_gemv<true, double, double, Tv>), g, b, 0, h.stream, X, h.Nl, y, t, 1.0,
+    hipLaunchKernelGGL((k_tri_gemv<false, Tv, double, double>), g, b, 0, h.stream, S, d, N, rv, none, 1.0, y);
+    hipLaunchKernelGGL((k_tri_gemv_col<true, double, Tv, double>), gc, bc, 0, h.stream, S, d, N, y, rv, -1.0, t);
+    hipLaunchKernelGGL((k_tri_gemv<false, double, double, double>), g, b, 0, h.stream, S, d, N, t, y, 1.0, y);
+    hipLaunchKernelGGL((k_tri_gemv_col<false, double, double, double>), gc, bc, 0, h.stream, S, d, N, y, none, 1.0, t);
+    hipLaunchKernelGGL((k_tri_gemv<true, double, double, double>), g, b, 0, h.stream, S, d, N, t, y, -1.0, y);
+    hipLaunchKernelGGL((k_tri_gemv_col<false, double, double, Tv>), gc, bc, 0, h.stream, S, d, N, y, t, 1.0,
                        static_cast<Tv*>(e));
   };
   if (p == P64) solve(double{});

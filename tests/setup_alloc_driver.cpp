@@ -55,7 +55,7 @@ void launch_pi_upper(H2&, int, const int*) {}
 void launch_assemble_dense(H2&, double*, int64_t) {}
 void launch_assemble_kernel_dense(H2&, double*, int64_t) {}
 void launch_potrf(H2& h, double*, int64_t, double*) { h.flags[0] = g_not_spd; }
-void launch_tri_inverse(H2&, double*, int64_t, double*) {}
+void launch_tri_inverse(H2&, const double*, int64_t, double*, double*) {}
 void launch_cast_precision(H2&, int) {}
 void launch_near_tiles(H2&) {}
 void launch_cast_near_tiles(H2&) {}
@@ -95,7 +95,7 @@ int main() {
     CHECK((h->d_top >= 0) == (eta > 0.1));
     const size_t bytes = h->arena.bytes, count = h->arena.ptrs.size();
     auto untouched = [&] {
-      return !h->mg_built && !h->chol && !h->cinv && h->arena.bytes == bytes && h->arena.ptrs.size() == count;
+      return !h->mg_built && !h->chol && !h->cinv && !h->cdiag && h->arena.bytes == bytes && h->arena.ptrs.size() == count;
     };
     // an operator that is not positive definite, twice
     g_not_spd = true;
@@ -116,13 +116,13 @@ int main() {
     }
     // the first attempt that succeeds lacks the inverse only
     const size_t square = size_t(h->Nl) * h->Nl * sizeof(double);
-    CHECK(h->mg_built && h->chol && !h->cinv);
+    CHECK(h->mg_built && h->chol && !h->cinv && !h->cdiag);
     CHECK(h->arena.bytes == bytes + square && h->arena.ptrs.size() == count + 1);
     delete h;
-    // and with room for everything there are both
+    // and with room for everything the inverse, which then holds the factor too
     CHECK(build_h2(pts.data(), n, 2, &kernel, &opts, nullptr, &h) == H2MG_OK);
-    CHECK(setup_mg(*h, 0) == H2MG_OK && h->chol && h->cinv);
-    CHECK(h->arena.bytes == bytes + 2 * square);
+    CHECK(setup_mg(*h, 0) == H2MG_OK && !h->chol && h->cinv && h->cdiag);
+    CHECK(h->arena.bytes == bytes + square + size_t(h->Nl) * sizeof(double));
     delete h;
   }
   std::printf("all checks passed\n");
