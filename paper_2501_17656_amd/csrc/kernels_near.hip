@@ -17,9 +17,9 @@
 //     leaves.
 //   * A column sum over the 8 lanes of a column takes three DPP steps per 8 U
 //     entries; eight columns are collected and written as one 64-word run.
-// Measured, one FP64 pass (before / after): 2270 / 388 us on 50000 points of a
-// Gaussian mixture (leaves of 49), 1059 / 126 us on a 300 x 300 grid (leaves of
-// 44), 40 / 14 us on 4096 points, 3073 / 2140 us (with the cheaper entries) on
+// Measured, one FP64 pass (128 x 128 tiles / now): 2270 / 420 us on 50000 points
+// of a Gaussian mixture (leaves of 49), 1059 / 125 us on a 300 x 300 grid (leaves
+// of 44), 40 / 14 us on 4096 points, 3073 / 1790 us (with the cheaper entries) on
 // 131072 points with full leaves, where three waves per SIMD issue an FP64
 // operation every 5.3 cycles (eight would reach 4.5).
 #include <hip/hip_runtime.h>
@@ -226,7 +226,7 @@ k_near(const int* __restrict__ tasks, int ntasks, NearIn<Tv> A, int dim, int chu
 // Registers for three waves a SIMD, as the near field alone, so a 64 x 64 tile
 // is read in two halves; the coupling waves go first when their data is there.
 // A product of 131072 points (3D, rank 64) took 2438 us with two launches and
-// 2246 with one, 50000 points (rank 27 in tiles of 32) 593 and 566; with
+// 2246 with one (2136 since the entries take one operation less), 50000 points (rank 27 in tiles of 32) 593 and 566; with
 // tiles of 16, which want more waves in flight than three, 90000 points took 190
 // and 199 us, 4096 points 35.6 and 36.8: those stay two launches.
 struct FarIn {
