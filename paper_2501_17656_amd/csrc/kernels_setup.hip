@@ -697,9 +697,13 @@ __global__ __launch_bounds__(NT) void k_potrf_tile(double* A, int64_t N, int64_t
 // ------------------------------------------------------------ inverse of the Cholesky factor
 // X = L^{-1} by doubling: X of every 64 x 64 diagonal block, then for s = 64,
 // 128, ... the pairs of neighbouring diagonal blocks A, C of order s (C may be
-// shorter), with B the block of L below A: X_B = -X_C (L_B X_A).  All pairs of
-// a step go together, so the chain is 2 log2(N / 64) products long instead of
-// N / 64 substitutions.  S (N x N, row-major) holds X in its lower triangle;
+// shorter), with B the block of L below A: X_B = -X_C T, T = L_B X_A.  All pairs of
+// a step go together, so the chain is 4 log2(N / 64) products long instead of
+// N / 64 substitutions.  Two of the four correct X_B with its residual, X_B -=
+// X_C (T + L_C X_B): without them its error is the product of both blocks'
+// condition numbers, and grows with every step (points in tree order, Gaussian
+// kernel, condition 4e14: the norm of I - X L is 0.6, with them 4e-3, as close
+// as substitution comes).  S (N x N, row-major) holds X in its lower triangle;
 // above the diagonal are the transposes of the products L_B X_A meanwhile and
 // L^T in the end.
 __global__ __launch_bounds__(NB) void k_tri_inv_diag(const double* __restrict__ L, int64_t N,
@@ -729,8 +733,10 @@ __global__ __launch_bounds__(NB) void k_tri_inv_diag(const double* __restrict__ 
 
 // One 64 x 64 tile of a doubling product per workgroup, on the FP64 matrix
 // cores; step 0: T = L_B X_A, stored transposed in the upper triangle of S;
-// step 1: X_B = -X_C T.  Tile (ti, tj) of pair z: rows of C, columns of A.
-// The inner range is cut to where the triangular operand is not zero.
+// step 1: X_B = -X_C T; step 2: T += L_C X_B; step 3: X_B -= X_C T.  Tile (ti, tj)
+// of pair z: rows of C, columns of A.  The inner range is cut to where the
+// triangular operand is not zero.  (Steps 2 and 3 read their result's place in
+// their own tile only.)
 template <int STEP>
 __global__ __launch_bounds__(NT) void k_tri_inv_step(const double* __restrict__ L, int64_t N, int64_t s,
                                                      double* __restrict__ S) {
@@ -747,11 +753,11 @@ __global__ __launch_bounds__(NT) void k_tri_inv_step(const double* __restrict__ 
   for (int64_t k = k0; k < k1; k += KB) {
     __syncthreads();
     for (int e = tid; e < KB * NB; e += NT) {
-      // P[q][i] = L or X_C at (i0 + i, k + q), Q[q][j] = X_A or T at (k + q, j0 + j)
-      if (STEP == 0) {
+      // P[q][i] = L or X_C at (i0 + i, k + q), Q[q][j] = X_A, X_B or T at (k + q, j0 + j)
+      if (STEP == 0 || STEP == 2) {
         const int i = e % NB, q = e / NB;
-        P[q][i] = i0 + i < c1 && k + q < k1 ? L[(i0 + i) + (k + q) * N] : 0.0;
-        Q[q][i] = k + q < k1 && j0 + i <= k + q ? S[(k + q) * N + j0 + i] : 0.0;
+        P[q][i] = i0 + i < c1 && k + q < k1 && (STEP == 0 || k + q <= i0 + i) ? L[(i0 + i) + (k + q) * N] : 0.0;
+        Q[q][i] = k + q < k1 && (STEP == 2 || j0 + i <= k + q) ? S[(k + q) * N + j0 + i] : 0.0;
       } else {
         const int q = e % KB, i = e / KB;
         P[q][i] = i0 + i < c1 && k + q <= i0 + i ? S[(i0 + i) * N + k + q] : 0.0;
@@ -774,7 +780,9 @@ __global__ __launch_bounds__(NT) void k_tri_inv_step(const double* __restrict__ 
       const int64_t i = i0 + 16 * w + 4 * t + lk, j = j0 + 16 * c + li;
       if (i >= c1) continue;
       if (STEP == 0) S[j * N + i] = acc[c][t];
-      else S[i * N + j] = -acc[c][t];
+      else if (STEP == 1) S[i * N + j] = -acc[c][t];
+      else if (STEP == 2) S[j * N + i] += acc[c][t];
+      else S[i * N + j] -= acc[c][t];
     }
 }
 
@@ -1094,6 +1102,8 @@ void launch_tri_inverse(H2& h, const double* L, int64_t N, double* S, double* di
     const dim3 grid(unsigned(s / NB), unsigned(s / NB), unsigned((N - s + 2 * s - 1) / (2 * s)));
     hipLaunchKernelGGL(k_tri_inv_step<0>, grid, dim3(NT), 0, h.stream, L, N, s, S);
     hipLaunchKernelGGL(k_tri_inv_step<1>, grid, dim3(NT), 0, h.stream, L, N, s, S);
+    hipLaunchKernelGGL(k_tri_inv_step<2>, grid, dim3(NT), 0, h.stream, L, N, s, S);
+    hipLaunchKernelGGL(k_tri_inv_step<3>, grid, dim3(NT), 0, h.stream, L, N, s, S);
   }
   hipLaunchKernelGGL(k_tri_pack, dim3(unsigned((N + NT - 1) / NT), unsigned(N)), dim3(NT), 0, h.stream, L, N, S, diag);
   check_launch("tri_inverse");

@@ -1,12 +1,14 @@
 """The direct solve of the coarsest operator on ill-conditioned matrices: its residual is that of
 substitution with the Cholesky factor.  With a tiny eta there are no far blocks, so one cycle is the
-direct solve of the whole matrix; residuals are formed on the host in extended precision."""
+direct solve of the whole matrix, in the order of the tree; residuals are formed on the host in
+extended precision."""
 import numpy as np
 import pytest
 import torch
 from scipy.linalg import cho_factor, cho_solve
 
 from paper_2501_17656_amd import H2Matrix
+from paper_2501_17656_amd.h2mg import Plan
 
 pytestmark = pytest.mark.gpu
 
@@ -16,12 +18,14 @@ def kernel_matrix(pts, ell, shift):
     return np.exp(-r2 / (2 * ell * ell)) + shift * np.eye(len(pts))
 
 
-# condition numbers of about 2e4, 1e7 to 6e7, and 4e11 to 2e12
-@pytest.mark.parametrize("ell,shift", [(0.1, 1e-2), (0.1, 1e-6), (0.2, 1e-10)])
-@pytest.mark.parametrize("n", [200, 1000])
+# condition numbers of about 1e3 to 1e4, 1e7 to 1e8, 4e11 to 4e12, and 4e13 to 4e14
+@pytest.mark.parametrize("ell,shift", [(0.1, 1e-2), (0.1, 1e-6), (0.2, 1e-10), (0.2, 1e-12)])
+@pytest.mark.parametrize("n", [200, 577, 1000, 2048])
 def test_residual_is_that_of_substitution(n, ell, shift):
     rng = np.random.default_rng(n)
     pts, B = rng.random((n, 2)), rng.standard_normal((n, 16))
+    pts = np.ascontiguousarray(pts[Plan(pts, 64, 1e-9, 3).perm()])   # the tree's order: its own permutation
+    assert (Plan(pts, 64, 1e-9, 3).perm() == np.arange(n)).all()
     A = kernel_matrix(pts, ell, shift)
     factor, wide = cho_factor(A, lower=True), A.astype(np.longdouble)
 
