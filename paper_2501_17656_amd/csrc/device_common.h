@@ -270,8 +270,8 @@ __device__ inline float lower_to(float s, float hi) { return __builtin_fminf(s, 
 // k (or its derivative) as a function of the squared distance (no shift),
 // for a kernel fixed at compile time.  MINED: r2 is finite and at least MIN_R2
 // (r = 0 included, so not for the kernels that ask for r2 = 0), and the exponent
-// above -2^30, in FP32 above -126: nothing is lowered or scaled.
-template <int KIND, int DERIV, typename T, bool MINED = false>
+// above -2^30: nothing is lowered.  NORMAL: the exponent is above -126 (FP32).
+template <int KIND, int DERIV, typename T, bool MINED = false, bool NORMAL = false>
 __device__ inline T kernel_fixed(const KernelConst<T>& k, T r2) {
   auto lower = [&](T s) { return MINED ? s : lower_to(s, k.far); };
   if constexpr (KIND == KER_LAPLACE) {
@@ -284,19 +284,19 @@ __device__ inline T kernel_fixed(const KernelConst<T>& k, T r2) {
   }
   if constexpr (KIND == KER_GAUSS) {
     const T s = lower(r2);
-    const T e = exp2_prod<MINED>(s, k.c);
+    const T e = exp2_prod<NORMAL>(s, k.c);
     if constexpr (DERIV == DER_NONE) return e;
     else if constexpr (DERIV == DER_LENGTH) return s * (k.inv_l * k.inv_l) * (k.inv_l * e);   // 1 / l^3 may overflow
     else return -k.inv_l * k.inv_l * e;
   } else if constexpr (KIND == KER_EXP) {
     const T rr = lower(sqrt_nn<MINED>(r2));
-    const T e = exp2_prod<MINED>(rr, k.c);
+    const T e = exp2_prod<NORMAL>(rr, k.c);
     if constexpr (DERIV == DER_NONE) return e;
     else if constexpr (DERIV == DER_LENGTH) return rr * (k.inv_l * k.inv_l) * e;
     else return -k.inv_l * e / rr;
   } else {
     const T rr = lower(sqrt_nn<MINED>(r2));
-    const T e = exp2_prod<MINED>(rr, k.c);
+    const T e = exp2_prod<NORMAL>(rr, k.c);
     if constexpr (DERIV == DER_NONE) return (T(1) + rr * k.z) * e;
     else if constexpr (DERIV == DER_LENGTH) return (rr * k.z) * (rr * k.z) * k.inv_l * e;
     else return T(-3) * k.inv_l * k.inv_l * e;

@@ -392,7 +392,7 @@ h2mg_status build_h2(const double* points_dev, int64_t n, int dim, const h2mg_ke
         }
         far2 = std::max(far2, d2);
       }
-      nf.mined32 = nf.mined && (h.kp.kind == KER_GAUSS ? far2 : std::sqrt(far2)) * -h.kp.c < 125.0;
+      nf.normal32 = nf.mined && (h.kp.kind == KER_GAUSS ? far2 : std::sqrt(far2)) * -h.kp.c < 125.0;
       for (int p = 0; p < nf.npairs; ++p)
         h.near_evals += int64_t(loff[prow[p] + 1] - loff[prow[p]]) * (loff[pcol[p] + 1] - loff[pcol[p]]);
     }

@@ -91,8 +91,8 @@ struct NearField {
   int ld = 0;                          // padded leaf length of partial buffers
   int chunk = 64, nchunk = 1;          // rows of a leaf taken at once, chunks of the largest leaf
   int nsplit = 1;                      // waves per task, each with its own share of the chunks
-  // distances and exponents are where the kernels need no clamps (FP64, FP32)
-  bool mined = false, mined32 = false;
+  bool mined = false;                  // distances and exponents are where the kernels need no clamps
+  bool normal32 = false;               // and no FP32 entry is subnormal
 };
 
 // Stored near field (optional, FP64).  Every leaf is cut into ceil(n / 64)

@@ -74,8 +74,9 @@ struct NearIn {
 // Rows [rt, rt + nrow) of leaf sl (U >= nrow / 8) against the pairs [p0, p1).
 // first: this wave has not written these pairs' column sums yet.  MINED: the
 // squared distance starts at MIN_R2 (its first addition is an FMA, so that
-// costs nothing) and the kernel need not bound its arguments.
-template <int U, int DIM, bool MINED, typename Tv, int KIND, int DERIV>
+// costs nothing) and the kernel need not bound its arguments.  NORMAL: no FP32
+// entry is subnormal.
+template <int U, int DIM, bool MINED, bool NORMAL, typename Tv, int KIND, int DERIV>
 __device__ __forceinline__ void near_rows(const NearIn<Tv>& A, int task, int part, int sl, int p0, int p1, int rt,
                                           int nrow, bool first) {
   const int lane = threadIdx.x & 63;
@@ -138,7 +139,7 @@ __device__ __forceinline__ void near_rows(const NearIn<Tv>& A, int task, int par
           if (a == 0) r2 = MINED ? __builtin_fma(dx, dx, double(MIN_R2<Tv>)) : dx * dx;
           else r2 = __builtin_fma(dx, dx, r2);
         }
-        const Tv k = kernel_fixed<KIND, DERIV, Tv, MINED>(kc, Tv(r2));
+        const Tv k = kernel_fixed<KIND, DERIV, Tv, MINED, NORMAL>(kc, Tv(r2));
         racc[u] += k * xj;
         cacc += k * xi[u];
       }
@@ -165,7 +166,7 @@ __device__ __forceinline__ void near_rows(const NearIn<Tv>& A, int task, int par
 // rows each (chunk <= 64, a multiple of 8).  With nsplit = 1 one wave does a
 // leaf's chunks in turn and adds their column sums; else each chunk has its
 // own place, and a chunk beyond a shorter leaf's rows writes zeros.
-template <typename Tv, int KIND, int DERIV>
+template <typename Tv, int KIND, int DERIV, bool NORMAL>
 __device__ __forceinline__ void near_wave(int wave, const int* __restrict__ tasks, int ntasks, const NearIn<Tv>& A,
                                           int dim, int chunk, int nchunk, bool mined) {
   constexpr bool MAY = KIND != KER_LAPLACE && DERIV != DER_RADIAL;   // no question about r = 0
@@ -185,18 +186,17 @@ __device__ __forceinline__ void near_wave(int wave, const int* __restrict__ task
     }
     auto run = [&](auto uc) {
       constexpr int U = decltype(uc)::value;
-      if (dim == 3) near_rows<U, 3, MAY, Tv, KIND, DERIV>(A, task, part, sl, p0, p1, rt, nrow, c == part);
-      else near_rows<U, 2, MAY, Tv, KIND, DERIV>(A, task, part, sl, p0, p1, rt, nrow, c == part);
+      if (dim == 3) near_rows<U, 3, MAY, NORMAL, Tv, KIND, DERIV>(A, task, part, sl, p0, p1, rt, nrow, c == part);
+      else near_rows<U, 2, MAY, NORMAL, Tv, KIND, DERIV>(A, task, part, sl, p0, p1, rt, nrow, c == part);
     };
-    // points on a line, distances beyond any use, and entries below FP32's normal
-    // range: one loop for every length
+    // points on a line, and distances beyond any use: one loop for every length
     if (dim == 1) {
-      near_rows<8, 1, false, Tv, KIND, DERIV>(A, task, part, sl, p0, p1, rt, nrow, c == part);
+      near_rows<8, 1, false, NORMAL, Tv, KIND, DERIV>(A, task, part, sl, p0, p1, rt, nrow, c == part);
       continue;
     }
     if (MAY && !mined) {
-      if (dim == 3) near_rows<8, 3, false, Tv, KIND, DERIV>(A, task, part, sl, p0, p1, rt, nrow, c == part);
-      else near_rows<8, 2, false, Tv, KIND, DERIV>(A, task, part, sl, p0, p1, rt, nrow, c == part);
+      if (dim == 3) near_rows<8, 3, false, NORMAL, Tv, KIND, DERIV>(A, task, part, sl, p0, p1, rt, nrow, c == part);
+      else near_rows<8, 2, false, NORMAL, Tv, KIND, DERIV>(A, task, part, sl, p0, p1, rt, nrow, c == part);
       continue;
     }
     switch ((nrow + 7) >> 3) {
@@ -212,10 +212,10 @@ __device__ __forceinline__ void near_wave(int wave, const int* __restrict__ task
   }
 }
 
-template <typename Tv, int KIND, int DERIV>
+template <typename Tv, int KIND, int DERIV, bool NORMAL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void
 k_near(const int* __restrict__ tasks, int ntasks, NearIn<Tv> A, int dim, int chunk, int nchunk, bool mined) {
-  near_wave<Tv, KIND, DERIV>(wave_id(), tasks, ntasks, A, dim, chunk, nchunk, mined);
+  near_wave<Tv, KIND, DERIV, NORMAL>(wave_id(), tasks, ntasks, A, dim, chunk, nchunk, mined);
 }
 
 // Near field and couplings of a fine FP64 product in one launch.  The first is
@@ -248,7 +248,7 @@ k_near_far(const int* __restrict__ tasks, int ntasks, NearIn<double> A, int dim,
   const int wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
   const uint32_t b = blockIdx.x, f = __umulhi(b, far_share);
   if (__umulhi(b + 1, far_share) == f) {
-    near_wave<double, KIND, DER_NONE>(int(b - f) * 4 + wv, tasks, ntasks, A, dim, chunk, nchunk, mined);
+    near_wave<double, KIND, DER_NONE, true>(int(b - f) * 4 + wv, tasks, ntasks, A, dim, chunk, nchunk, mined);
     return;
   }
   __builtin_amdgcn_s_setprio(3);         // few instructions, each behind a load
@@ -303,18 +303,19 @@ void launch_near(H2& h, int p, const void* xtree) {
   const dim3 g(unsigned((int64_t(nf.ntasks) * nf.nsplit + 3) / 4)), b(256);
   KernelParams kp = h.kp;
   if (h.diag) kp.shift = 0.0;          // the per-point diagonal is added by k_fine_reduce
-  auto go = [&](auto tv, auto kc, auto dc) {
+  auto go = [&](auto tv, auto kc, auto dc, auto nc) {
     using Tv = decltype(tv);
     constexpr int K = decltype(kc)::value, D = decltype(dc)::value;
     const NearIn<Tv> A{nf.pair_col, nf.pair_slot, h.leaf_off, h.pts, h.scale, static_cast<const Tv*>(xtree),
                        reinterpret_cast<Tv*>(h.near_partial), reinterpret_cast<Tv*>(h.near_colpart), kp, nf.ld,
                        nf.nsplit};
-    hipLaunchKernelGGL((k_near<Tv, K, D>), g, b, 0, h.stream, nf.task, nf.ntasks, A, h.dim, nf.chunk, nf.nchunk,
-                       p == P64 ? nf.mined : nf.mined32);
+    hipLaunchKernelGGL((k_near<Tv, K, D, decltype(nc)::value>), g, b, 0, h.stream, nf.task, nf.ntasks, A, h.dim,
+                       nf.chunk, nf.nchunk, nf.mined);
   };
   dispatch_kernel(h.kp.kind, h.kp.deriv, [&](auto kc, auto dc) {
-    if (p == P64) go(double{}, kc, dc);
-    else go(float{}, kc, dc);
+    if (p == P64) go(double{}, kc, dc, std::true_type{});
+    else if (nf.normal32) go(float{}, kc, dc, std::true_type{});
+    else go(float{}, kc, dc, std::false_type{});
   });
   check_launch("near");
   h.time_end(p == P64 ? KS_NEAR64 : KS_NEAR32, ev, double(h.near_evals));
